@@ -1,0 +1,351 @@
+"""The work that users have this framework do, as cases that can be timed.
+
+listed() names them, draw() gives more of the same ranges, prepare() makes
+what a program holds before the call (seeded inputs on the GPU, a handle
+with its mesh), run() is one pass through the public entry points, work()
+the least a pass has to move and compute, and exact() the same result from
+plain torch in 64 bits.
+
+Clusters are the framework's own recipe (workload.py): icospheres of level 2
+to 4 (162, 642 or 2562 vertices) or 48 x 16 tori at about the density of its
+100-, 1000- and 5000-bubble clusters.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_1905_01341_amd import bfm, forms
+from paper_1905_01341_amd import workload as wl
+
+DEV = "cuda:0"
+INV4PI = 0.25 / math.pi
+
+
+def listed():
+    return [
+        # one bubble, the paper's plain method: the smallest solve, all latency
+        dict(name="solve_plain_1", op="solve", form="plain", shape="sphere", bubbles=1, level=3, p=16, tol=1e-10),
+        # a small cluster with the two-level preconditioner and refinement
+        dict(name="solve_tuned_12", op="solve", form="tuned", shape="sphere", bubbles=12, level=3, p=16, tol=1e-7),
+        # the paper's plain FP64 method on a cluster of ordinary size
+        dict(name="solve_plain_100", op="solve", form="plain", shape="sphere", bubbles=100, level=3, p=16, tol=1e-8),
+        # the headline: one step's solve of the 1000-bubble cluster
+        dict(name="solve_tuned_1000", op="solve", form="tuned", shape="sphere", bubbles=1000, level=3, p=16, tol=1e-7),
+        # the scale run: 3.2 million vertices
+        dict(name="solve_tuned_5000", op="solve", form="tuned", shape="sphere", bubbles=5000, level=3, p=16, tol=1e-7),
+        # toroidal bubbles: refinement without a preconditioner, many iterations
+        dict(name="solve_torus_100", op="solve", form="tuned", shape="torus", bubbles=100, level=0, p=16, tol=1e-8),
+        # products with the operators for a caller's own iteration
+        dict(name="matvec_single_100", op="matvec", kind="L", bubbles=100, level=4, p=16),
+        dict(name="matvec_both_400", op="matvec", kind="LM", bubbles=400, level=3, p=12),
+        # singular diagonals and right-hand side of large meshes
+        dict(name="diagonals_100", op="diagonals", bubbles=100, level=4, p=20),
+        # the residual of a solution at sampled rows, by direct sums
+        dict(name="direct_2000", op="direct", kind="LM", n=256200, rows=2000),
+        # the first (Runge-Kutta) step of a simulation: state in, step, state out
+        dict(name="step_30", op="step", bubbles=30, level=3, p=16, tol=1e-7),
+        # training the initial guess: loss and gradients of one cluster's samples
+        dict(name="mlp_gradient_1000", op="mlp", rows=1000),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    op = rng.choice(["solve", "solve", "solve", "solve", "torus", "matvec", "matvec", "diagonals", "direct", "step",
+                     "mlp"])
+    if op == "solve":
+        if rng.random() < 0.4:
+            level = rng.choice([2, 3, 3, 4])
+            most = {2: 700, 3: 170, 4: 44}[level]
+            return dict(op="solve", form="plain", shape="sphere", bubbles=_log(rng, 1, most), level=level,
+                        p=rng.choice([12, 16, 16, 20]), tol=rng.choice([1e-8, 1e-10]))
+        level = rng.choice([3, 3, 3, 4])
+        most = {3: 4500, 4: 1100}[level]
+        return dict(op="solve", form="tuned", shape="sphere", bubbles=_log(rng, 3, most), level=level, p=16,
+                    tol=rng.choice([1e-7, 1e-8]))
+    if op == "torus":
+        return dict(op="solve", form="tuned", shape="torus", bubbles=_log(rng, 1, 800), level=0, p=16, tol=1e-8)
+    if op == "matvec":
+        level = rng.choice([2, 3, 4])
+        most = {2: 4000, 3: 1500, 4: 400}[level]
+        return dict(op="matvec", kind=rng.choice(["L", "M", "LM"]), bubbles=_log(rng, 1, most), level=level,
+                    p=rng.choice([8, 12, 16, 20]))
+    if op == "diagonals":
+        level = rng.choice([2, 3, 4])
+        most = {2: 4000, 3: 1500, 4: 400}[level]
+        return dict(op="diagonals", bubbles=_log(rng, 1, most), level=level, p=rng.choice([16, 20, 20]))
+    if op == "direct":
+        n = _log(rng, 500, 640000)
+        return dict(op="direct", kind=rng.choice(["L", "M", "LM"]), n=n, rows=min(n, _log(rng, 1, 5000)))
+    if op == "step":
+        return dict(op="step", bubbles=_log(rng, 2, 300), level=3, p=16, tol=rng.choice([1e-7, 1e-8]))
+    return dict(op="mlp", rows=_log(rng, 50, 8192))
+
+
+# -- inputs -------------------------------------------------------------------
+
+
+def _side(nb, shape):
+    """Cube side of nb bubbles at the density of the framework's clusters."""
+    return (6.5 if shape == "torus" else 9.0) * max(nb, 2) ** (1.0 / 3.0)
+
+
+def _cluster(case, seed):
+    nb = case["bubbles"]
+    if case.get("shape") == "torus":
+        return wl.torus_cluster(nb, 48, 16, _side(nb, "torus"), 0.5, 1.0, 0.5, seed)
+    return wl.cluster(nb, case["level"], _side(nb, "sphere"), 0.5, 1.0, 0.5, seed, perturb=0.05)
+
+
+def _phi(case, cl, seed):
+    if case.get("shape") == "torus":
+        return wl.smooth_torus_phi(cl, seed)
+    if case.get("form") == "plain" or case["op"] in ("matvec", "diagonals"):
+        return wl.rough_phi(cl, seed)
+    return wl.smooth_phi(cl, seed)
+
+
+def _dev(a):
+    return torch.tensor(a, dtype=torch.float64, device=DEV).contiguous()
+
+
+def _options(case):
+    """The two forms as the benchmark runs them, at the orders and near-field
+    shape its autotuner picks on the 1000-bubble cluster."""
+    if case.get("form") == "plain":
+        return forms.options("plain", p=case["p"], gmres_tol=case["tol"])
+    if case.get("shape") == "torus":
+        return forms.options("tuned", p=case["p"], p_lo=8, p_diag=20, p2p_shape=1, gmres_tol=case["tol"],
+                             precond=bfm.PRECOND_NONE)
+    return forms.options("tuned", p=case["p"], p_lo=8, p_diag=20, p2p_shape=1, gmres_tol=case["tol"])
+
+
+def _direct_inputs(case, seed):
+    """Points of a bubble cluster cut to n, their weights and normals, two
+    densities and the sampled rows."""
+    n = case["n"]
+    nb = -(-n // 642)
+    cl = wl.cluster(nb, 3, _side(nb, "sphere"), 0.5, 1.0, 0.5, seed, perturb=0.05)
+    s, nrm = _geometry(cl)
+    rng = np.random.default_rng(seed + 1)
+    x, y = rng.uniform(-1.0, 1.0, n), rng.uniform(-1.0, 1.0, n)
+    rows = torch.tensor(wl.subset_rows(n, case["rows"], seed + 2), dtype=torch.int64, device=DEV)
+    return _dev(cl.xyz[:n]), s[:n].contiguous(), nrm[:n].contiguous(), _dev(x), _dev(y), rows
+
+
+MLP_SIZES = [174, 512, 512, 512, 81]
+
+
+def _mlp_inputs(case, seed):
+    """Weights of a young network, and samples of unit scale."""
+    rng = np.random.default_rng(seed)
+    params = np.concatenate([np.concatenate([(rng.standard_normal((a, b)) / math.sqrt(a)).ravel(),
+                                             0.1 * rng.standard_normal(b)])
+                             for a, b in zip(MLP_SIZES[:-1], MLP_SIZES[1:])]).astype(np.float32)
+    x = rng.standard_normal((case["rows"], 174)).astype(np.float32)
+    t = rng.standard_normal((case["rows"], 81)).astype(np.float32)
+    return params, x, t
+
+
+PHYSICS = dict(sigma=0.073, kappa=1.4, p0=1.0, pa=0.5, period=5.0, forcing_sign=1.0, filter_degree=9)
+
+
+def prepare(case, seed):
+    op = case["op"]
+    if op == "direct":
+        xyz, s, nrm, x, y, rows = _direct_inputs(case, seed)
+        return dict(op=op, kind=case["kind"], xyz=xyz, s=s, nrm=nrm, x=x, y=y, rows=rows)
+    if op == "mlp":
+        params, x, t = _mlp_inputs(case, seed)
+        sv = bfm.Solver(device=0)
+        sv.mlp_init(0)
+        sv.mlp_set_params(params)
+        return dict(op=op, sv=sv, x=x, t=t)
+    cl = _cluster(case, seed)
+    phi = _phi(case, cl, seed + 1)
+    if op == "matvec":
+        sv = bfm.Solver(device=0, p=case["p"])
+        sv.set_cluster(cl)
+        return dict(op=op, kind=case["kind"], sv=sv, x=phi, y=wl.rough_phi(cl, seed + 2))
+    if op == "diagonals":
+        sv = bfm.Solver(device=0, p=16, p_diag=case["p"])
+        sv.set_cluster(cl)
+        return dict(op=op, sv=sv, phi=phi)
+    sv = bfm.Solver(device=0, **_options(case))
+    sv.set_cluster(cl)
+    if op == "step":
+        sv.set_physics(**PHYSICS)
+        return dict(op=op, sv=sv, xyz=cl.xyz, phi=phi, dt=2e-3)
+    phi_t = _dev(phi)
+    return dict(op=op, sv=sv, xyz=_dev(cl.xyz), phi=phi_t, q=torch.zeros_like(phi_t))
+
+
+def run(state):
+    op = state["op"]
+    if op == "direct":
+        k = state["kind"]
+        return bfm.direct_dev(state["xyz"], state["s"], state["nrm"],
+                              1.0 if "L" in k else 0.0, state["x"] if "L" in k else None,
+                              1.0 if "M" in k else 0.0, state["y"] if "M" in k else None, rows_t=state["rows"])
+    sv = state["sv"]
+    if op == "mlp":
+        grad, loss = sv.mlp_gradient(state["x"], state["t"])
+        return {"grad": grad, "loss": loss}
+    if op == "matvec":
+        k = state["kind"]
+        return sv.matvec(1.0 if "L" in k else 0.0, state["x"] if "L" in k else None,
+                         1.0 if "M" in k else 0.0, state["y"] if "M" in k else None)
+    if op == "diagonals":
+        m, l, b = sv.diagonals(state["phi"])
+        return {"M": m, "L": l, "b": b}
+    if op == "step":
+        sv.state_set(state["xyz"], state["phi"], 0.0)
+        sv.step(state["dt"])
+        xyz, phi, t = sv.state_get()
+        return {"xyz": xyz, "phi": phi, "t": t}
+    # one step's solve: the vertices have moved, so geometry, octree,
+    # diagonals and right-hand side are part of it
+    bfm._check(sv.lib.bfm_set_positions_dev(sv.h, bfm._dptr(state["xyz"])))
+    sv.solve_dev(state["phi"], state["q"])
+    return state["q"]
+
+
+# -- what a pass cannot do without ----------------------------------------------
+
+
+def _vertices(case):
+    if case.get("shape") == "torus":
+        return 768 * case["bubbles"]
+    return (10 * 4 ** case["level"] + 2) * case["bubbles"]
+
+
+def work(case):
+    """Bytes: every input read and every output written once. Flops: all
+    pairs for the direct sums; else the near field alone, at the thousand or
+    so pairs per point and 11 (single layer), 20 (both) or 37 (five channels)
+    flops per pair, times the products that a solve of that form runs."""
+    op = case["op"]
+    if op == "direct":
+        n, r = case["n"], case["rows"]
+        per = {"L": 11, "M": 19, "LM": 20}[case["kind"]]
+        return {"bytes": 8 * (n * (4 + (1 if "L" in case["kind"] else 0) + (4 if "M" in case["kind"] else 0)) + 2 * r),
+                "flops": per * n * r}
+    if op == "mlp":
+        w = sum(a * b for a, b in zip(MLP_SIZES[:-1], MLP_SIZES[1:]))
+        return {"bytes": 4 * (case["rows"] * (174 + 81) + 2 * w), "flops": 6 * w * case["rows"]}
+    n = _vertices(case)
+    pairs = n * min(n - 1, 1000)
+    if op == "matvec":
+        return {"bytes": 8 * n * 2 + 56 * n, "flops": (11 if case["kind"] == "L" else 20) * pairs}
+    if op == "diagonals":
+        return {"bytes": 8 * n * 4 + 56 * n, "flops": 37 * pairs}
+    products = 100 if (case.get("form") == "plain" or case.get("shape") == "torus") else 10
+    solves = 4 if op == "step" else 1
+    return {"bytes": solves * (24 + 8 + 8 + 24) * n, "flops": solves * (37 + 11 * products) * pairs}
+
+
+# -- the same in 64 bits ---------------------------------------------------------
+
+
+def _geometry(cl):
+    """Vertex weights (a third of the areas around) and unit normals."""
+    xyz = torch.tensor(cl.xyz, dtype=torch.float64)
+    tri = torch.tensor(cl.tri, dtype=torch.int64)
+    c = 0.5 * torch.linalg.cross(xyz[tri[:, 1]] - xyz[tri[:, 0]], xyz[tri[:, 2]] - xyz[tri[:, 0]])
+    a = torch.linalg.norm(c, dim=1)
+    s, nrm = torch.zeros(len(xyz), dtype=torch.float64), torch.zeros_like(xyz)
+    for k in range(3):
+        s.index_add_(0, tri[:, k], a / 3.0)
+        nrm.index_add_(0, tri[:, k], c)
+    return s.to(DEV), (nrm / torch.linalg.norm(nrm, dim=1, keepdim=True)).to(DEV)
+
+
+def _blocks(xyz, nrm, rows):
+    """(rows of the block, 1/r, n_j . (r_i - r_j) / r^3), zero for j = i,
+    without the 1/(4 pi)."""
+    n = len(xyz)
+    step = max(1, (1 << 26) // n)
+    for k in range(0, len(rows), step):
+        i = rows[k:k + step]
+        dx = [xyz[i, a][:, None] - xyz[None, :, a] for a in range(3)]
+        r2 = dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2]
+        r2[torch.arange(len(i), device=DEV), i] = math.inf
+        g = r2.rsqrt()
+        d = (dx[0] * nrm[:, 0] + dx[1] * nrm[:, 1] + dx[2] * nrm[:, 2]) * (g / r2)
+        yield k, i, g, d
+
+
+def _sum(a, v):
+    return (a * v).sum(dim=1)
+
+
+def _products(xyz, nrm, rows, ql, wm):
+    """sum_j ql_j / r [+] wm_j n_j . (r_i - r_j) / r^3, over 4 pi, at rows."""
+    out = torch.empty(len(rows), dtype=torch.float64, device=DEV)
+    for k, i, g, d in _blocks(xyz, nrm, rows):
+        v = 0.0
+        if ql is not None:
+            v = v + _sum(g, ql)
+        if wm is not None:
+            v = v + _sum(d, wm)
+        out[k:k + len(i)] = INV4PI * v
+    return out
+
+
+def _diagonals(xyz, s, nrm, phi):
+    """M_ii, L_ii and b of the singular diagonals' identities."""
+    n = len(xyz)
+    m, l, b = (torch.empty(n, dtype=torch.float64, device=DEV) for _ in range(3))
+    for k, i, g, d in _blocks(xyz, nrm, torch.arange(n, device=DEV)):
+        e = slice(k, k + len(i))
+        sm = INV4PI * _sum(d, s)
+        m[e] = -0.5 - sm
+        v = 0.0
+        for a in range(3):
+            v = v + nrm[i, a] * (_sum(d, s * xyz[:, a]) - xyz[i, a] * _sum(d, s) - _sum(g, s * nrm[:, a]))
+        l[e] = INV4PI * v
+        b[e] = -phi[i] * (1.0 + sm) + INV4PI * _sum(d, s * phi)
+    return m, l, b
+
+
+def exact(case, seed):
+    op = case["op"]
+    if op == "mlp":
+        params, x, t = (torch.tensor(a, dtype=torch.float64) for a in _mlp_inputs(case, seed))
+        params.requires_grad_(True)
+        h, at = x, 0
+        for k, (a, b) in enumerate(zip(MLP_SIZES[:-1], MLP_SIZES[1:])):
+            h = h @ params[at:at + a * b].view(a, b) + params[at + a * b:at + a * b + b]
+            at += a * b + b
+            if k < 3:
+                h = h * torch.sigmoid(h)
+        loss = 0.5 * ((h - t) ** 2).sum() / case["rows"]
+        loss.backward()
+        return {"grad": params.grad, "loss": float(loss)}
+    if op == "direct":
+        xyz, s, nrm, x, y, rows = _direct_inputs(case, seed)
+        return _products(xyz, nrm, rows, s * x if "L" in case["kind"] else None, s * y if "M" in case["kind"] else None)
+    n = _vertices(case)
+    if op == "step" or n > (300_000 if op in ("matvec", "diagonals") else 10_000):
+        return None
+    cl = _cluster(case, seed)
+    phi = _phi(case, cl, seed + 1)
+    s, nrm = _geometry(cl)
+    xyz, phi_t = _dev(cl.xyz), _dev(phi)
+    rows = torch.arange(n, device=DEV)
+    if op == "matvec":
+        y = _dev(wl.rough_phi(cl, seed + 2))
+        return _products(xyz, nrm, rows, s * phi_t if "L" in case["kind"] else None,
+                         s * y if "M" in case["kind"] else None).cpu().numpy()
+    m, l, b = _diagonals(xyz, s, nrm, phi_t)
+    if op == "diagonals":
+        return {"M": m.cpu().numpy(), "L": l.cpu().numpy(), "b": b.cpu().numpy()}
+    a = torch.empty(n, n, dtype=torch.float64, device=DEV)
+    for k, i, g, d in _blocks(xyz, nrm, rows):
+        a[k:k + len(i)] = INV4PI * g * s
+    a[rows, rows] = l
+    return torch.linalg.solve(a, b)
