@@ -114,14 +114,14 @@ def _dev(a):
 
 
 def _options(case):
-    """The two forms as the benchmark runs them, at the orders and near-field
-    shape its autotuner picks on the 1000-bubble cluster."""
+    """The two forms as the benchmark runs them, the tuned one at the orders,
+    near-field shape and leaf occupancy (over 128 points) its autotuner picks
+    on the 1000-bubble cluster."""
     if case.get("form") == "plain":
         return forms.options("plain", p=case["p"], gmres_tol=case["tol"])
-    if case.get("shape") == "torus":
-        return forms.options("tuned", p=case["p"], p_lo=8, p_diag=20, p2p_shape=1, gmres_tol=case["tol"],
-                             precond=bfm.PRECOND_NONE)
-    return forms.options("tuned", p=case["p"], p_lo=8, p_diag=20, p2p_shape=1, gmres_tol=case["tol"])
+    precond = bfm.PRECOND_NONE if case.get("shape") == "torus" else bfm.PRECOND_SH_COARSE
+    return forms.options("tuned", p=case["p"], p_lo=8, p_diag=20, p2p_shape=1, leaf_target=128, gmres_tol=case["tol"],
+                         precond=precond)
 
 
 def _direct_inputs(case, seed):
