@@ -33,7 +33,7 @@ PEAK_FP64_TFLOPS = 78.6  # MI355X FP64 vector and FP64 matrix (dense)
 # to the value it was measured with.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_c1000.txt")
 KERNEL_SOURCES = {"p2p": ("fmm_near.hip", "fmm_kernels.h", "fmm.h", "tree.h", "common.h"),
-                  "m2l": ("fmm.hip", "fmm_rot.hip", "fmm.h", "common.h"),
+                  "m2l": ("fmm.hip", "fmm_rot.hip", "fmm_azim.hip", "fmm.h", "common.h"),
                   "leaf": ("fmm_leaf.hip", "fmm_kernels.h", "fmm.h", "tree.h", "common.h")}
 
 
@@ -114,24 +114,22 @@ def measured_traffic(cls, kernel, workload, lmax, p):
 
 
 def m2l_kernel_name(p, shape, orders=0):
-    """Instantiation(s) of the FP64 M2L translation kernel for order p and
-    launch shape (template arguments: applied p^2, rows per block, waves,
-    class, element type, stored p^2); with reduced orders for distant
-    offsets, the three distance classes' launches joined by ' + '."""
-    def rows_of(pp):
-        mid = 48 if pp == 144 else (80 if pp == 400 else (64 if pp >= 64 else pp))
-        wide = pp if pp <= 144 else (128 if pp == 256 else mid)
-        return {0: (wide, 8), 1: (mid, 4), 2: (16, 4)}[shape]
-    ld = p * p
-    orders_p = [p] if not orders else [p, 4 * ((p + 4) // 5), 4 * ((3 * p + 19) // 20)]
+    """Instantiation(s) of the FP64 M2L kernels for order p and launch shape:
+    the azimuth-reduced translation (template arguments: applied order, stored
+    order, row-block pairs, waves, kind) and the sum per target box of each
+    order group (reduced orders for distant offsets make two or three), or
+    the rotation-factored form (applied order, stored order), joined by
+    ' + '."""
+    orders_p = [p] if not orders else list(dict.fromkeys([p, 4 * ((p + 4) // 5), 4 * ((3 * p + 19) // 20)]))
     names = []
-    for po in orders_p:
-        if shape == 3:  # rotation-factored: applied order, stored order
+    for k, po in enumerate(orders_p):
+        if shape == 3:
             names.append(f"bfm::k_m2l_rot<{po}, {p}>")
             continue
-        pp = po * po
-        rows, waves = rows_of(pp)
-        names.append(f"bfm::k_translate<{pp}, {rows}, {waves}, 0, double, {ld}>")
+        pairs, waves = {0: (None, 8), 1: (None, 4), 2: (1, 1)}[shape]
+        pairs = pairs or (1 if po <= 4 else (5 if po == 12 else 3))
+        names.append(f"bfm::k_translate_az<{po}, {p}, {pairs}, {waves}, 0> + "
+                     f"bfm::k_az_reduce<{po}, {'true' if k == 0 else 'false'}>")
     return " + ".join(names)
 
 
@@ -275,11 +273,17 @@ def roofline_entry(cls, prof, prof_steps, stats, opt, p_diag, nv, workload):
         bound, tcls = "mfma", "m2l"
         nch = 5 if group == "diag_" else 1
         # every operator read once, every box's multipole read and local
-        # expansion written once (rotation-factored operators: two rotations
-        # of sum (2n+1)^2 and a translation along the axis of sum (p-m)^2)
+        # expansion written once (FP64: 34 operators of a cosine and a sine
+        # block; rotation-factored: two rotations of sum (2n+1)^2 and a
+        # translation along the axis of sum (p-m)^2 per offset)
         shape_used = stats["diag_m2l_shape" if group else "m2l_shape"] if not lo_prec else -1
-        op_words = (2 * p * (4 * p * p - 1) // 3 + p * (p + 1) * (2 * p + 1) // 6) if shape_used == 3 else pp * pp
-        alg_bytes = unit_bytes * (316 * op_words + 2 * stats["boxes"] * pp * nch)
+        if lo_prec:
+            op_words = 316 * pp * pp
+        elif shape_used == 3:
+            op_words = 316 * (2 * p * (4 * p * p - 1) // 3 + p * (p + 1) * (2 * p + 1) // 6)
+        else:
+            op_words = 34 * (pp * pp + pp) // 2
+        alg_bytes = unit_bytes * (op_words + 2 * stats["boxes"] * pp * nch)
     elif kind == "p2p":
         kname = p2p_kernel_name(group)
         bound, tcls = "alu", "p2p"

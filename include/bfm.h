@@ -117,11 +117,12 @@ typedef struct bfm_options {
     int use_graph;     /* != 0: GMRES replays each product (preconditioner + fast multipole
                           product) from one captured HIP graph per octree */
     int m2l_shape;     /* M2L launch shape: -1 = by size, 0 = wide tiles, 1 = row slabs,
-                          2 = narrow slabs (dense p^2 x p^2 operators), 3 = rotation-factored
-                          M2L (rotate the multipole to the offset's axis, translate along it,
-                          rotate back: 4 p^3 instead of 2 p^4 flops per translation, FP64
-                          products only; the diagonal/right-hand-side pass follows it); set
-                          by bfm_autotune */
+                          2 = narrow slabs (FP64 products: azimuth rotated out, p^4 flops
+                          per translation; low-precision ones: dense p^2 x p^2 operators),
+                          3 = rotation-factored M2L (rotate the multipole to the offset's
+                          axis, translate along it, rotate back: 4 p^3 flops per translation,
+                          FP64 products only; the diagonal/right-hand-side pass follows it);
+                          set by bfm_autotune */
     int m2l_orders;    /* 0: every M2L translation at the product's order p (Section 3.9);
                           1: offsets d = (c_target - c_source)/h (box sides) translated at
                           orders falling with |d|: p for |d|^2 <= 5, 4 ceil(p/5) for 6..10,
@@ -361,8 +362,9 @@ int bfm_tree_stats(bfm_ctx *ctx, int n, int64_t *stats);
  * and returns, for the first nclass classes (host arrays of nclass entries),
  * the summed event time in ms, the number of launches and the summed
  * algorithmic work of those launches (flops for the product kernels:
- * near-field pairs x flops per pair, 2 p^4 per translated expansion column;
- * 0 for P2M, L2P and classes 5..7).
+ * near-field pairs x flops per pair; per translated expansion column of
+ * order p, p^4 + p^2 in FP64 (the cosine and the sine block), 2 p^4 in low
+ * precision; 0 for P2M, L2P and classes 5..7).
  */
 #define BFM_KERNEL_CLASSES 18
 int bfm_profile(bfm_ctx *ctx, int enable);

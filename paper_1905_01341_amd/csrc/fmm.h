@@ -34,7 +34,16 @@ struct FmmWork {
     int nch_cap = 0;
     int64_t nbox_cap = 0;
     DevBuf<double> mexp, lexp;      // [nbox][nch][P]
-    DevBuf<double> ops_m2m, ops_l2l, ops_m2l;  // operators, column-major per op: [op][k][row]
+    // FP64 operators with the azimuth taken out (fmm_azim.hip): one M2M and one
+    // L2L operator, the M2L operators by order group (az_goff: first double of
+    // each), the operator and the rotation factors of every offset (316, then
+    // the 8 octants), packed positions of the factors' entries
+    DevBuf<double> az_m2m, az_l2l, az_m2l;
+    DevBuf<double> az_part;  // per-task M2L results of one batch
+    DevBuf<int> az_canon, az_off;
+    DevBuf<double2> az_fac;
+    size_t az_goff[3] = {0, 0, 0};
+    int az_p = 0, az_orders = -1;
     DevBuf<float> mexp32, lexp32;   // low-precision expansions [nbox][P]
     DevBuf<float> part32;           // low-precision M2L results per task [ntasks][P]
     DevBuf<float> opf_m2m, opf_l2l, opf_m2l;   // FP32 operators, same layout

@@ -9,12 +9,11 @@
 //   L2P   evaluate leaf locals at the leaf's points             (per leaf)
 //   P2P   leaf x (leaf + neighbours), LDS-staged source tiles   (per leaf)
 //
-// The three translations share one kernel: tasks grouped by operator, each
-// wave multiplies one P x P operator by 16 gathered expansion columns on the
-// matrix cores and adds the result into the target expansions atomically.
-// Arithmetic by product group: FP64 MFMA (v_mfma_f64_16x16x4f64) for the
-// FP64 products; for the low-precision products of iterative refinement,
-// FP32 expansions with FP32 MFMA (v_mfma_f32_16x16x4f32) or with split-BF16
+// The three translations share one kernel per arithmetic: tasks grouped by
+// operator, each wave multiplies one operator by 16 gathered expansion
+// columns on the matrix cores. FP64 products: fmm_azim.hip. The
+// low-precision products of iterative refinement: FP32 expansions with dense
+// P x P operators on FP32 MFMA (v_mfma_f32_16x16x4f32) or with split-BF16
 // operands (a = hi + lo, hi = bf16(a), lo = bf16(a - hi)) on
 // v_mfma_f32_16x16x32_bf16: three products hi*hi + hi*lo + lo*hi accumulated
 // in FP32.
@@ -30,23 +29,13 @@
 
 namespace bfm {
 
-typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef float flt4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// One 16 x 16 x 4 matrix-core step per operand type. Operand layout (both
-// types): A[i][k] from lane 16 k + i, B[k][j] from lane 16 k + j. Result
+// One 16 x 16 x 4 matrix-core step. Operand layout: A[i][k] from lane 16 k + i, B[k][j] from lane 16 k + j. Result
 // layout: lane l, element r holds column l % 16 and row rowof(l / 16, r).
 template <class T>
 struct Mma;
-template <>
-struct Mma<double> {
-    typedef dbl4 acc_t;
-    static __device__ inline acc_t step(double a, double b, acc_t c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    static __device__ inline int rowof(int q, int r) { return q + 4 * r; }
-};
 template <>
 struct Mma<float> {
     typedef flt4 acc_t;
@@ -57,7 +46,7 @@ struct Mma<float> {
 };
 
 // ---------------------------------------------------------------------------
-// Grouped translation GEMM (FP64 MFMA). A workgroup of WAVES waves owns
+// Grouped translation GEMM (FP32 MFMA). A workgroup of WAVES waves owns
 // WAVES x 16 columns (task x channel) of one operator's group and a slab of
 // ROWS output rows; the operator slab is streamed through LDS in chunks of 16
 // input coefficients and shared by all waves; each wave multiplies it by its
@@ -76,7 +65,7 @@ constexpr int kXcds = 8;  // accelerator complex dies of an MI355X
 // degrees below sqrt(PP)) - smaller for distant offsets when the product
 // reduces their order. The launch covers operators op0 .. op0 + nops - 1,
 // whose tiles are g0 .. g0 + ntiles - 1 of the prefix tile_off.
-template <int PP, int ROWS, int WAVES, int KIND, class R = double, int LD = PP>
+template <int PP, int ROWS, int WAVES, int KIND, class R = float, int LD = PP>
 __global__ void __launch_bounds__(64 * WAVES) k_translate(int op0, int nops, const int *tile_off, int g0,
                                                           int ntiles, const int *op_off, const int *tsrc,
                                                           const int *tdst, int nch, int swap,
@@ -526,17 +515,18 @@ void fmm_prepare_ops(FmmWork &w, int p, hipStream_t st) {
     int dev = 0;
     BFM_HIP(hipGetDevice(&dev));
     leaf_tables_upload(dev);
+    if (w.prec == BFM_PREC_FP64) {
+        az_ops_upload(w, p, st);
+        w.ops_p = p;
+        w.ops_prec = w.prec;
+        return;
+    }
     if (w.ops_p == p && w.ops_prec == w.prec) return;
     const int P = p * p;
     std::vector<double> h2m, h2l;
     const std::vector<double> *hl = nullptr;
     host_ops(p, h2m, h2l, hl);
-    if (w.prec == BFM_PREC_FP64) {
-        upload(w.ops_m2m, h2m, st);
-        upload(w.ops_l2l, h2l, st);
-        upload(w.ops_m2l, *hl, st);
-        BFM_HIP(hipStreamSynchronize(st));
-    } else if (w.prec == BFM_PREC_FP32) {
+    if (w.prec == BFM_PREC_FP32) {
         std::vector<float> f2m(h2m.begin(), h2m.end()), f2l(h2l.begin(), h2l.end()), fl(hl->begin(), hl->end());
         upload(w.opf_m2m, f2m, st);
         upload(w.opf_l2l, f2l, st);
@@ -656,7 +646,23 @@ static void translate_rot(FmmWork &w, TaskList &tl, int nch, const double *in, d
     prof_end(w, pi, st, flops);
 }
 
-template <int P_, class R = double>
+// FP64 translation of a task list (fmm_azim.hip).
+template <int P_>
+static void translate64(FmmWork &w, int cls, TaskList &tl, int nch, bool swap, const double *in, double *out,
+                        hipStream_t st) {
+    if (cls == KC_M2L && w.m2l_shape == 3) {
+        w.m2l_shape_used = 3;
+        return translate_rot<P_>(w, tl, nch, in, out, st);
+    }
+    const int pi = prof_begin(w, cls, st);
+    double flops = 0.0;
+    const int shape = launch_translate_az<P_>(AzLaunch{&w, nch, swap, in, out, st}, tl, cls == KC_M2L,
+                                              cls == KC_M2L ? w.m2l_shape : -1, &flops);
+    if (cls == KC_M2L) w.m2l_shape_used = shape;
+    prof_end(w, pi, st, flops);
+}
+
+template <int P_, class R>
 static void translate(FmmWork &w, int cls, TaskList &tl, int nch, bool swap, const R *T, const R *in, R *out,
                       hipStream_t st) {
     constexpr int PP = P_ * P_;
@@ -668,12 +674,6 @@ static void translate(FmmWork &w, int cls, TaskList &tl, int nch, bool swap, con
     const int64_t wave_tiles = (cols + 15) / 16;
     int shape = (wave_tiles * (PP / mid_rows(PP)) >= 512) ? 1 : 2;
     if (cls == KC_M2L && w.m2l_shape >= 0 && w.m2l_shape <= 2) shape = w.m2l_shape;
-    if constexpr (std::is_same<R, double>::value) {
-        if (cls == KC_M2L && w.m2l_shape == 3) {
-            w.m2l_shape_used = 3;
-            return translate_rot<P_>(w, tl, nch, in, out, st);
-        }
-    }
     if (cls == KC_M2L) w.m2l_shape_used = shape;
     const int width = (shape == 0) ? 128 : 64;
     prepare_tiles(tl, nch, width, st);
@@ -791,8 +791,12 @@ static void run_fmm(FmmWork &w, const Tree &tc, const Sources &src, double *y, h
     double *L = w.lexp.ensure(ncoef);
     k_zero<double><<<1024, 256, 0, st>>>(M, (int64_t)ncoef);
     BFM_LAUNCHED();
-    k_zero<double><<<1024, 256, 0, st>>>(L, (int64_t)ncoef);
-    BFM_LAUNCHED();
+    // the M2L writes every target expansion; only the rotation-factored form
+    // adds into it, and no task list means no M2L
+    if (w.m2l_shape == 3 || t.m2l.ntasks <= 0) {
+        k_zero<double><<<1024, 256, 0, st>>>(L, (int64_t)ncoef);
+        BFM_LAUNCHED();
+    }
     // near field (writes y) on the near-field stream when there is one,
     // beside the far-field chain; the L2P adds into y after it
     // (kernel timing runs them one after the other, so that each kernel's
@@ -813,10 +817,9 @@ static void run_fmm(FmmWork &w, const Tree &tc, const Sources &src, double *y, h
     launch_p2m<P_, NCH, MONO, DIP>(t, src, M, st);
     prof_end(w, pi, st, 0.0);
     for (int l = lmax; l >= 3; --l)
-        translate<P_>(w, KC_M2M_L2L, *t.m2m[l], NCH, false, w.ops_m2m.get(), M, M, st);
-    translate<P_>(w, KC_M2L, t.m2l, NCH, false, w.ops_m2l.get(), M, L, st);
-    for (int l = 3; l <= lmax; ++l)
-        translate<P_>(w, KC_M2M_L2L, *t.m2m[l], NCH, true, w.ops_l2l.get(), L, L, st);
+        translate64<P_>(w, KC_M2M_L2L, *t.m2m[l], NCH, false, M, M, st);
+    translate64<P_>(w, KC_M2L, t.m2l, NCH, false, M, L, st);
+    for (int l = 3; l <= lmax; ++l) translate64<P_>(w, KC_M2M_L2L, *t.m2m[l], NCH, true, L, L, st);
     if (ns != st) BFM_HIP(hipStreamWaitEvent(st, w.ev_join, 0));
     pi = prof_begin(w, KC_L2P, st);
     launch_l2p<P_, NCH>(t, L, y, st);

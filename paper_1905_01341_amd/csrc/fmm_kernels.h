@@ -42,6 +42,23 @@ template <int PO, int PS>
 void launch_m2l_rot(const FmmWork &w, int op0, int nops, int g0, int ntiles, const int *tile_off,
                     const TaskList &tl, int nch, const double *in, double *out, hipStream_t st);
 
+// FP64 translations with the azimuth taken out (fmm_azim.hip): operators of
+// order p (and w.m2l_orders) uploaded to w (no-op if current); the
+// translation of a whole task list (M2L, or a level's M2M / L2L with swap) at
+// order P, added into out. shape 0..2, or -1: by size; returns the shape used
+// and the products' flops.
+struct AzLaunch {
+    FmmWork *w;
+    int nch;
+    bool swap;
+    const double *in;
+    double *out;
+    hipStream_t st;
+};
+void az_ops_upload(FmmWork &w, int p, hipStream_t st);
+template <int P>
+int launch_translate_az(const AzLaunch &a, TaskList &tl, bool m2l, int shape, double *flops);
+
 // y[c][i] = sum over every other point (all pairs).
 template <int NCH, bool MONO, bool DIP>
 void launch_direct(const Tree &t, const Sources &src, double *y, hipStream_t st);
