@@ -687,11 +687,12 @@ int bfm_mlp_forward(bfm_ctx *c, int64_t rows, const float *x, float *y) {
         BFM_CHECK(rows >= 1 && rows <= (1 << 24), BFM_EINVAL, "rows must be in [1, 2^24]");
         DeviceScope ds(c->device);
         hipStream_t st = c->stream;
-        DevBuf<float> dx, dy;
+        Mlp &net = mlp_get(c);
+        DevBuf<float> &dx = net.io_x, &dy = net.io_y;
         dx.ensure((size_t)rows * BFM_MLP_INPUTS);
         dy.ensure((size_t)rows * BFM_MLP_OUTPUTS);
         BFM_HIP(hipMemcpyAsync(dx.get(), x, sizeof(float) * rows * BFM_MLP_INPUTS, hipMemcpyHostToDevice, st));
-        mlp_forward_rows(mlp_get(c), rows, dx.get(), dy.get(), st);
+        mlp_forward_rows(net, rows, dx.get(), dy.get(), st);
         BFM_HIP(hipMemcpyAsync(y, dy.get(), sizeof(float) * rows * BFM_MLP_OUTPUTS, hipMemcpyDeviceToHost, st));
         BFM_HIP(hipStreamSynchronize(st));
     });
@@ -703,12 +704,12 @@ int bfm_mlp_gradient(bfm_ctx *c, int64_t rows, const float *x, const float *t, f
         BFM_CHECK(rows >= 1 && rows <= (1 << 24), BFM_EINVAL, "rows must be in [1, 2^24]");
         DeviceScope ds(c->device);
         hipStream_t st = c->stream;
-        DevBuf<float> dx, dt;
+        Mlp &net = mlp_get(c);
+        DevBuf<float> &dx = net.io_x, &dt = net.io_y;
         dx.ensure((size_t)rows * BFM_MLP_INPUTS);
         dt.ensure((size_t)rows * BFM_MLP_OUTPUTS);
         BFM_HIP(hipMemcpyAsync(dx.get(), x, sizeof(float) * rows * BFM_MLP_INPUTS, hipMemcpyHostToDevice, st));
         BFM_HIP(hipMemcpyAsync(dt.get(), t, sizeof(float) * rows * BFM_MLP_OUTPUTS, hipMemcpyHostToDevice, st));
-        Mlp &net = mlp_get(c);
         const double l = mlp_gradient_rows(net, rows, dx.get(), dt.get(), st);
         if (grad) mlp_get_params(net, grad, true, st);
         if (loss) *loss = l;

@@ -34,6 +34,8 @@ struct Mlp {
     DevBuf<__bf16> X[kLayers], XT, GT, Gb;
     DevBuf<float> Z[kLayers], G, dX, T, part, norm;
     DevBuf<double> loss_acc;
+    // device copies of the caller's rows and outputs, and of the flat parameters
+    DevBuf<float> io_x, io_y, flat;
 
     // features
     ShBasis sh;

@@ -31,76 +31,139 @@ static unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 // kRow(l, r) and column l % 16 of the 16 x 16 block.
 __device__ inline int mfma_row(int l, int r) { return 4 * (l >> 4) + r; }
 
-// C[M x N] (FP32, row-major) (+)= A[M x K] B[K x N] + bias[N]. A is BF16 with
-// K contiguous per row (A[m * lda + k]); B is BF16 with K contiguous per
-// column (B[n * ldb + k]). K % 32 == 0, lda and ldb multiples of 8.
-// 256 threads: 4 waves, each a 32 x 32 block (2 x 2 MFMA tiles).
-__global__ void __launch_bounds__(256) k_gemm_bf16(int M, int N, int K, const __bf16 *A, int lda,
-                                                   const __bf16 *B, int ldb, float *C, int ldc,
-                                                   const float *bias, int accumulate) {
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int m0 = blockIdx.x * 64 + (wave >> 1) * 32, n0 = blockIdx.y * 64 + (wave & 1) * 32;
-    const int kofs = 8 * (l >> 4);
-    f32x4 acc[2][2];
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        bf16x8 a[2], b[2];
-        for (int i = 0; i < 2; ++i) {
-            const int row = m0 + 16 * i + (l & 15);
-            if (row < M) {
-                a[i] = *reinterpret_cast<const bf16x8 *>(A + (int64_t)row * lda + k0 + kofs);
-            } else {
-                for (int e = 0; e < 8; ++e) a[i][e] = (__bf16)0.0f;
-            }
-            const int col = n0 + 16 * i + (l & 15);
-            if (col < N) {
-                b[i] = *reinterpret_cast<const bf16x8 *>(B + (int64_t)col * ldb + k0 + kofs);
-            } else {
-                for (int e = 0; e < 8; ++e) b[i][e] = (__bf16)0.0f;
-            }
-        }
-        for (int i = 0; i < 2; ++i)
-            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j)
-            for (int r = 0; r < 4; ++r) {
-                const int row = m0 + 16 * i + mfma_row(l, r), col = n0 + 16 * j + (l & 15);
-                if (row < M && col < N) {
-                    float v = acc[i][j][r] + (bias ? bias[col] : 0.f);
-                    if (accumulate) v += C[(int64_t)row * ldc + col];
-                    C[(int64_t)row * ldc + col] = v;
-                }
-            }
-}
-
 __device__ inline float silu_f(float z) { return z / (1.f + __expf(-z)); }
 __device__ inline float silu_g(float z) {
     const float s = 1.f / (1.f + __expf(-z));
     return s * (1.f + z * (1.f - s));
 }
 
-// out[r][c] = bf16(silu(Z[r][c])) (act) or bf16(Z[r][c]); rows x cols
-__global__ void k_act_bf16(const float *Z, int64_t total, int act, __bf16 *out) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < total) out[i] = (__bf16)(act ? silu_f(Z[i]) : Z[i]);
+// Epilogues of the BF16 GEMM.
+enum { EPI_PLAIN = 0, EPI_BIAS = 1, EPI_SILU = 2, EPI_SILU_BACK = 3 };
+
+// C[M x N] (FP32, row-major) = A[M x K] B[K x N], then by EPI: nothing; + bias;
+// + bias and X = bf16(silu(C)); times silu'(Z). A is BF16 with K contiguous
+// per row (A[m * lda + k]); B is BF16 with K contiguous per column
+// (B[n * ldb + k]). K % 32 == 0, lda and ldb multiples of 8.
+// One 32 x 32 tile per workgroup (2 x 2 MFMA tiles), small so that a layer's
+// few hundred tiles reach every CU: at these sizes the loop is bound by the
+// latency of its loads, which go out four K steps at a time. SPLIT = 4: four
+// waves take a quarter of K each (the weight gradients, K = batch rows, whose
+// 256 tiles alone leave most of the chip idle) and their sums are added
+// through LDS; SPLIT = 1 keeps the K order of the forward values. Measured on
+// 1000 rows: 13.3 us a GEMM with 64 x 64 tiles of four waves, loads waited for
+// step by step, and three more launches a layer for what the epilogues and
+// k_grad_prep now do; 7 to 12 us so, the pass 1.50 -> 0.40 ms with the column
+// sums over 32-row tiles (208 us a layer before).
+template <int SPLIT, int EPI>
+__global__ void __launch_bounds__(64 * SPLIT) k_gemm_bf16(int M, int N, int K, const __bf16 *__restrict__ A, int lda,
+                                                          const __bf16 *__restrict__ B, int ldb,
+                                                          float *__restrict__ C, int ldc,
+                                                          const float *__restrict__ bias,
+                                                          const float *__restrict__ Z, __bf16 *__restrict__ X) {
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
+    const int kofs = 8 * (l >> 4);
+    // rows and columns past the matrix repeat the last one and are not stored
+    const __bf16 *pa[2], *pb[2];
+    for (int i = 0; i < 2; ++i) {
+        pa[i] = A + (int64_t)min(m0 + 16 * i + (l & 15), M - 1) * lda + kofs;
+        pb[i] = B + (int64_t)min(n0 + 16 * i + (l & 15), N - 1) * ldb + kofs;
+    }
+    f32x4 acc[2][2];
+    for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int steps = K / 32, s0 = steps * wave / SPLIT, s1 = steps * (wave + 1) / SPLIT;
+    for (int s = s0; s < s1; s += 4) {
+        bf16x8 a[4][2], b[4][2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k0 = 32 * min(s + u, s1 - 1);  // past the end: the last step again, not multiplied
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[u][i] = *reinterpret_cast<const bf16x8 *>(pa[i] + k0);
+                b[u][i] = *reinterpret_cast<const bf16x8 *>(pb[i] + k0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (s + u >= s1) break;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+        }
+    }
+    if constexpr (SPLIT > 1) {
+        __shared__ float red[SPLIT - 1][16][64];
+        if (wave > 0)
+            for (int e = 0; e < 16; ++e) red[wave - 1][e][l] = acc[e >> 3][(e >> 2) & 1][e & 3];
+        __syncthreads();
+        if (wave > 0) return;
+        for (int w = 0; w < SPLIT - 1; ++w)
+            for (int e = 0; e < 16; ++e) acc[e >> 3][(e >> 2) & 1][e & 3] += red[w][e][l];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = m0 + 16 * i + mfma_row(l, r), col = n0 + 16 * j + (l & 15);
+                if (row >= M || col >= N) continue;
+                const int64_t at = (int64_t)row * ldc + col;
+                float v = acc[i][j][r];
+                if (EPI == EPI_BIAS || EPI == EPI_SILU) v += bias[col];
+                if (EPI == EPI_SILU_BACK) v *= silu_g(Z[at]);
+                C[at] = v;
+                if (EPI == EPI_SILU) X[at] = (__bf16)silu_f(v);
+            }
 }
 
-// out[c][r] = bf16(in[r][c]) (in FP32 or BF16), rows x cols -> cols x rows
-template <class T>
-__global__ void k_transpose_bf16(const T *in, int rows, int cols, __bf16 *out) {
+// Operands of a layer's weight gradient and of the step below it, in one
+// launch: XT[c][r] = X[r][c]; GT[c][r] = bf16(G[r][c]), Gb[r][c] likewise
+// (Gb may be null), and part[r / 32][c] = the sum of G over 32 rows. rows, in
+// and out are multiples of 32; blocks of 32 x 8 threads, in/32 + out/32 by
+// rows/32 of them.
+__global__ void __launch_bounds__(256) k_grad_prep(const __bf16 *__restrict__ X, const float *__restrict__ G, int rows,
+                                                   int in, int out, __bf16 *__restrict__ XT,
+                                                   __bf16 *__restrict__ GT, __bf16 *__restrict__ Gb,
+                                                   float *__restrict__ part) {
     __shared__ float tile[32][33];
-    const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+    const bool isx = (int)blockIdx.x < in / 32;
+    const int cols = isx ? in : out;
+    const int r0 = blockIdx.y * 32, c0 = (isx ? blockIdx.x : blockIdx.x - in / 32) * 32;
     for (int k = threadIdx.y; k < 32; k += 8) {
-        const int r = r0 + k, c = c0 + threadIdx.x;
-        tile[k][threadIdx.x] = (r < rows && c < cols) ? (float)in[(int64_t)r * cols + c] : 0.f;
+        const int64_t at = (int64_t)(r0 + k) * cols + c0 + threadIdx.x;
+        const float v = isx ? (float)X[at] : G[at];
+        tile[k][threadIdx.x] = v;
+        if (!isx && Gb) Gb[at] = (__bf16)v;
     }
     __syncthreads();
-    for (int k = threadIdx.y; k < 32; k += 8) {
-        const int c = c0 + k, r = r0 + threadIdx.x;
-        if (c < cols && r < rows) out[(int64_t)c * rows + r] = (__bf16)tile[threadIdx.x][k];
+    __bf16 *outp = isx ? XT : GT;
+    for (int k = threadIdx.y; k < 32; k += 8)
+        outp[(int64_t)(c0 + k) * rows + r0 + threadIdx.x] = (__bf16)tile[threadIdx.x][k];
+    if (!isx && threadIdx.y == 0) {
+        float v = 0.f;
+        for (int k = 0; k < 32; ++k) v += tile[k][threadIdx.x];
+        part[(int64_t)blockIdx.y * out + c0 + threadIdx.x] = v;
     }
+}
+
+// db[c] = sum over the nt row tiles of part[t][c]: 32 columns x 8 groups of
+// tiles per block
+__global__ void __launch_bounds__(256) k_colsum(const float *__restrict__ part, int nt, int cols,
+                                                float *__restrict__ db) {
+    __shared__ float red[8][32];
+    const int c = blockIdx.x * 32 + (threadIdx.x & 31), grp = threadIdx.x >> 5;
+    float v = 0.f;
+#pragma unroll 4
+    for (int t = grp; t < nt; t += 8) v += part[(int64_t)t * cols + c];
+    red[grp][threadIdx.x & 31] = v;
+    __syncthreads();
+    if (grp != 0) return;
+    for (int q = 1; q < 8; ++q) v += red[q][threadIdx.x & 31];
+    db[c] = v;
 }
 
 // G = (Y - T) / nrows on the first `used` columns and `nrows` rows, 0 elsewhere;
@@ -127,20 +190,6 @@ __global__ void k_loss_grad(const float *Y, const float *T, int rows, int cols, 
         __syncthreads();
     }
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-__global__ void k_silu_back(float *G, const float *Z, int64_t total) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < total) G[i] *= silu_g(Z[i]);
-}
-
-// db[c] = sum_r G[r][c]
-__global__ void k_colsum(const float *G, int rows, int cols, float *db) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    float s = 0.f;
-    for (int r = 0; r < rows; ++r) s += G[(int64_t)r * cols + c];
-    db[c] = s;
 }
 
 __global__ void k_adam(float *p, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
@@ -449,21 +498,47 @@ void mlp_set_params(Mlp &net, const float *host, hipStream_t st) {
     net.ready = true;
 }
 
+// flat[e] of the host layout, gathered from the padded arrays
+struct PackArgs {
+    const float *W[Mlp::kLayers], *b[Mlp::kLayers];
+    int ti[Mlp::kLayers], to[Mlp::kLayers], ld[Mlp::kLayers];
+};
+__global__ void k_pack_params(PackArgs a, int total, float *flat) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= total) return;
+    int r = e;
+#pragma unroll
+    for (int k = 0; k < Mlp::kLayers; ++k) {
+        const int nw = a.ti[k] * a.to[k];
+        if (r < nw) {
+            flat[e] = a.W[k][(int64_t)(r / a.to[k]) * a.ld[k] + r % a.to[k]];
+            return;
+        }
+        r -= nw;
+        if (r < a.to[k]) {
+            flat[e] = a.b[k][r];
+            return;
+        }
+        r -= a.to[k];
+    }
+}
+
 void mlp_get_params(Mlp &net, float *host, bool grads, hipStream_t st) {
     BFM_CHECK(net.ready, BFM_EINVAL, "network not initialised");
-    float *p = host;
+    PackArgs a{};
     for (int k = 0; k < Mlp::kLayers; ++k) {
-        const int out = net.dims[k + 1], ti = net.true_in(k), to = net.true_out(k);
-        std::vector<float> W((size_t)net.dims[k] * out), b(out);
-        BFM_HIP(hipMemcpyAsync(W.data(), (grads ? net.dW[k] : net.W[k]).get(), sizeof(float) * W.size(),
-                               hipMemcpyDeviceToHost, st));
-        BFM_HIP(hipMemcpyAsync(b.data(), (grads ? net.db[k] : net.b[k]).get(), sizeof(float) * out,
-                               hipMemcpyDeviceToHost, st));
-        BFM_HIP(hipStreamSynchronize(st));
-        for (int i = 0; i < ti; ++i)
-            for (int o = 0; o < to; ++o) *p++ = W[(size_t)i * out + o];
-        for (int o = 0; o < to; ++o) *p++ = b[o];
+        a.W[k] = (grads ? net.dW[k] : net.W[k]).get();
+        a.b[k] = (grads ? net.db[k] : net.b[k]).get();
+        a.ti[k] = net.true_in(k);
+        a.to[k] = net.true_out(k);
+        a.ld[k] = net.dims[k + 1];
     }
+    const int total = (int)mlp_num_params(net);
+    float *flat = net.flat.ensure(total);
+    k_pack_params<<<nblk(total, 256), 256, 0, st>>>(a, total, flat);
+    BFM_LAUNCHED();
+    BFM_HIP(hipMemcpyAsync(host, flat, sizeof(float) * total, hipMemcpyDeviceToHost, st));
+    BFM_HIP(hipStreamSynchronize(st));
 }
 
 void mlp_set_norm(Mlp &net, const float *host, hipStream_t st) {
@@ -488,12 +563,13 @@ static const float *sd_x(const Mlp &n) { return n.norm.get() + Mlp::kIn; }
 static const float *mu_y(const Mlp &n) { return n.norm.get() + 2 * Mlp::kIn; }
 static const float *sd_y(const Mlp &n) { return n.norm.get() + 2 * Mlp::kIn + Mlp::kOut; }
 
+template <int SPLIT, int EPI>
 static void gemm(int M, int N, int K, const __bf16 *A, int lda, const __bf16 *B, int ldb, float *C, int ldc,
-                 const float *bias, hipStream_t st) {
+                 const float *bias, const float *Z, __bf16 *X, hipStream_t st) {
     BFM_CHECK(K % 32 == 0 && lda % 8 == 0 && ldb % 8 == 0 && lda >= K && ldb >= K, BFM_EINVAL,
               "BF16 GEMM shape");
-    dim3 g(nblk(M, 64), nblk(N, 64));
-    k_gemm_bf16<<<g, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, bias, 0);
+    k_gemm_bf16<SPLIT, EPI><<<dim3(nblk(M, 32), nblk(N, 32)), 64 * SPLIT, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc,
+                                                                                  bias, Z, X);
     BFM_LAUNCHED();
 }
 
@@ -502,49 +578,45 @@ static void forward(Mlp &net, int R, hipStream_t st) {
     for (int k = 0; k < Mlp::kLayers; ++k) {
         const int in = net.dims[k], out = net.dims[k + 1];
         float *Z = net.Z[k].ensure((size_t)R * out);
-        gemm(R, out, in, net.X[k].get(), in, net.Wt[k].get(), in, Z, out, net.b[k].get(), st);
-        if (k + 1 < Mlp::kLayers) {
-            __bf16 *Xn = net.X[k + 1].ensure((size_t)R * out);
-            k_act_bf16<<<nblk((int64_t)R * out, 256), 256, 0, st>>>(Z, (int64_t)R * out, 1, Xn);
-            BFM_LAUNCHED();
-        }
+        if (k + 1 < Mlp::kLayers)
+            gemm<1, EPI_SILU>(R, out, in, net.X[k].get(), in, net.Wt[k].get(), in, Z, out, net.b[k].get(), nullptr,
+                              net.X[k + 1].ensure((size_t)R * out), st);
+        else
+            gemm<1, EPI_BIAS>(R, out, in, net.X[k].get(), in, net.Wt[k].get(), in, Z, out, net.b[k].get(), nullptr,
+                              nullptr, st);
     }
 }
 
-// Backward pass for `rows` valid rows (of R) against standardised targets
-// net.T [rows][kOut]; adds the summed loss to net.loss_acc[0].
+// Backward pass for `rows` valid rows (of R, a multiple of 64) against
+// standardised targets net.T [rows][kOut]; adds the summed loss to
+// net.loss_acc[0].
 static void backward(Mlp &net, int rows, int R, hipStream_t st) {
     const int L = Mlp::kLayers;
     const int outL = net.dims[L];
     float *G = net.G.ensure((size_t)R * Mlp::kHidden);
     const int nbk = (int)nblk((int64_t)R * outL, 256);
-    float *part = net.part.ensure(nbk);
+    float *part = net.part.ensure(std::max<size_t>(nbk, (size_t)(R / 32) * Mlp::kHidden));
     k_loss_grad<<<nbk, 256, 0, st>>>(net.Z[L - 1].get(), net.T.get(), R, outL, Mlp::kOut, rows, G, part);
     BFM_LAUNCHED();
     k_sum_parts<<<1, 256, 0, st>>>(part, nbk, net.loss_acc.get());
     BFM_LAUNCHED();
-    dim3 tb(32, 8);
     for (int k = L - 1; k >= 0; --k) {
         const int in = net.dims[k], out = net.dims[k + 1];
-        // dW = X^T G ([in][out], K = R): both operands transposed so that K is contiguous
         __bf16 *XT = net.XT.ensure((size_t)in * R);
         __bf16 *GT = net.GT.ensure((size_t)out * R);
-        k_transpose_bf16<__bf16><<<dim3(nblk(in, 32), nblk(R, 32)), tb, 0, st>>>(net.X[k].get(), R, in, XT);
+        __bf16 *Gb = k > 0 ? net.Gb.ensure((size_t)R * out) : nullptr;
+        k_grad_prep<<<dim3(in / 32 + out / 32, R / 32), dim3(32, 8), 0, st>>>(net.X[k].get(), G, R, in, out, XT, GT, Gb,
+                                                                              part);
         BFM_LAUNCHED();
-        k_transpose_bf16<float><<<dim3(nblk(out, 32), nblk(R, 32)), tb, 0, st>>>(G, R, out, GT);
-        BFM_LAUNCHED();
-        gemm(in, out, R, XT, R, GT, R, net.dW[k].get(), out, nullptr, st);
-        k_colsum<<<nblk(out, 256), 256, 0, st>>>(G, R, out, net.db[k].get());
+        // dW = X^T G ([in][out], K = R): both operands transposed so that K is contiguous
+        gemm<4, EPI_PLAIN>(in, out, R, XT, R, GT, R, net.dW[k].get(), out, nullptr, nullptr, nullptr, st);
+        k_colsum<<<out / 32, 256, 0, st>>>(part, R / 32, out, net.db[k].get());
         BFM_LAUNCHED();
         if (k > 0) {
-            // dX = G W^T ([R][in], K = out), then through the SiLU of layer k - 1
-            __bf16 *Gb = net.Gb.ensure((size_t)R * out);
-            k_act_bf16<<<nblk((int64_t)R * out, 256), 256, 0, st>>>(G, (int64_t)R * out, 0, Gb);
-            BFM_LAUNCHED();
+            // dX = G W^T ([R][in], K = out) times the SiLU's derivative at layer k - 1
             float *dX = net.dX.ensure((size_t)R * Mlp::kHidden);
-            gemm(R, in, out, Gb, out, net.Wn[k].get(), out, dX, in, nullptr, st);
-            k_silu_back<<<nblk((int64_t)R * in, 256), 256, 0, st>>>(dX, net.Z[k - 1].get(), (int64_t)R * in);
-            BFM_LAUNCHED();
+            gemm<1, EPI_SILU_BACK>(R, in, out, Gb, out, net.Wn[k].get(), out, dX, in, nullptr, net.Z[k - 1].get(),
+                                   nullptr, st);
             std::swap(net.G.ptr, net.dX.ptr);
             std::swap(net.G.cap, net.dX.cap);
             G = net.G.get();
