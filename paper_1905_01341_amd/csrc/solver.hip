@@ -2,6 +2,7 @@
 // eq3_1), the product with L (eq3_27) and restarted GMRES (Section 3.8),
 // all on the handle's stream. Solve vectors live in the octree's sorted
 // point order so that the fast multipole product needs no gather/scatter.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -338,81 +339,160 @@ void matvec_sorted(bfm_ctx *c, double f, const double *x_s, double g, const doub
 // ---------------------------------------------------------------------------
 // GMRES (restarted, classical Gram-Schmidt with one reorthogonalisation,
 // Givens rotations on the device). Reductions are two-stage with a fixed
-// block count, so sums are bitwise reproducible run to run.
+// block count for a given n, so sums are bitwise reproducible run to run.
+//
+// An Arnoldi step's orthogonalisation is a chain of short passes over the
+// basis; with every dot product, reduction, update, norm, rotation and
+// scaling in a launch of its own it was ten launches and a copy, 45 us of
+// mostly launch latency (642 to 642,000 points). Each pass now starts by adding up the partial
+// sums the pass before it left (every block does, which costs less than a
+// launch) and ends with the partial sums of the next: dots of w; update and
+// dots again (the basis is read once for both); update and norm; rotation
+// and scaling. Up to kSmallGs points one workgroup does the whole step.
+// Measured: see gs_step.
 
 constexpr int kRedBlocks = 512;
 constexpr int kRedThreads = 256;
+constexpr int kGsFuse = 32;          // basis vectors a fused pass holds in registers
+constexpr int64_t kSmallGs = 4096;   // points up to which one workgroup runs the step
+constexpr int kMaxRestart = 128;
 
-// part[k * kRedBlocks + blk] = partial of sum_i V[k][i] w[i], k in [0, nv)
-__global__ void __launch_bounds__(kRedThreads) k_mdot(const double *V, int nvec, int64_t ld,
-                                                      const double *w, int64_t n, double *part) {
-    __shared__ double red[8][kRedThreads];
-    for (int k0 = 0; k0 < nvec; k0 += 8) {
-        const int kn = (nvec - k0) < 8 ? (nvec - k0) : 8;
-        double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n;
-             i += (int64_t)kRedBlocks * kRedThreads) {
-            const double wi = w[i];
+// two points a thread at least: every block adds up all blocks' partials
+static int red_blocks(int64_t n) { return (int)std::min<int64_t>(kRedBlocks, nblk(n, 2 * kRedThreads)); }
+
+// Sums a wave's 64 lanes of KM values (a power of two up to 64): every
+// exchange halves the values a lane keeps, so KM values cost about KM
+// exchanges instead of 6 KM. On return lane l's v[0] is the sum of value
+// wave_slot<KM>(l).
+template <int KM>
+__device__ inline int wave_slot(int lane) {
+    int slot = 0;
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (u < kn) acc[u] += V[(k0 + u) * ld + i] * wi;
+    for (int w = KM / 2, mask = 32; w >= 1; w /= 2, mask /= 2) slot += (lane & mask) ? w : 0;
+    return slot;
+}
+template <int W, int MASK, int KM>
+__device__ __forceinline__ void wave_sum_step(double (&v)[KM], int lane) {
+    if constexpr (W >= 1) {
+        const bool up = (lane & MASK) != 0;
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            const double send = up ? v[i] : v[i + W];
+            v[i] = (up ? v[i + W] : v[i]) + __shfl_xor(send, MASK);
         }
-        for (int u = 0; u < 8; ++u) red[u][threadIdx.x] = acc[u];
-        __syncthreads();
-        for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s)
-                for (int u = 0; u < 8; ++u) red[u][threadIdx.x] += red[u][threadIdx.x + s];
-            __syncthreads();
-        }
-        if (threadIdx.x < (unsigned)kn) part[(k0 + threadIdx.x) * kRedBlocks + blockIdx.x] = red[threadIdx.x][0];
-        __syncthreads();
+        wave_sum_step<W / 2, MASK / 2, KM>(v, lane);
+    } else if constexpr (MASK >= 1) {
+        v[0] += __shfl_xor(v[0], MASK);
+        wave_sum_step<0, MASK / 2, KM>(v, lane);
     }
 }
+template <int KM>
+__device__ __forceinline__ void wave_sum(double (&v)[KM], int lane) {
+    wave_sum_step<KM / 2, 32, KM>(v, lane);
+}
 
-// out[k] = sum_b part[k * kRedBlocks + b] (+ out[k] if accumulate)
-__global__ void __launch_bounds__(kRedThreads) k_reduce(const double *part, int nvec, double *out,
-                                                        int accumulate) {
-    __shared__ double red[kRedThreads];
-    const int k = blockIdx.x;
-    if (k >= nvec) return;
-    double a = 0.0;
-    for (int b = threadIdx.x; b < kRedBlocks; b += kRedThreads) a += part[k * kRedBlocks + b];
-    red[threadIdx.x] = a;
+// part[k * kRedBlocks + block] = the block's sum of v[k], k < kn (256 threads)
+template <int KM>
+__device__ inline void block_part(double (&v)[KM], int kn, double *part, double (*red)[KM]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    wave_sum<KM>(v, lane);
+    red[wave][wave_slot<KM>(lane)] = v[0];  // lanes of one slot write the same value
     __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
+    if ((int)threadIdx.x < kn)
+        part[threadIdx.x * kRedBlocks + blockIdx.x] =
+            ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+}
+
+// h[k] = sum over the nblk partials of value k, k < nvec (a block of 256):
+// eight lanes a value, so that 32 values' loads are in flight at once
+__device__ inline void part_sum(const double *part, int nblk, int nvec, double *h) {
+    const int l8 = threadIdx.x & 7;
+    for (int k = threadIdx.x >> 3; k < nvec; k += kRedThreads / 8) {
+        double a = 0.0;
+#pragma unroll 8
+        for (int b = l8; b < nblk; b += 8) a += part[k * kRedBlocks + b];
+        for (int o = 4; o > 0; o >>= 1) a += __shfl_xor(a, o);
+        if (l8 == 0) h[k] = a;
     }
-    if (threadIdx.x == 0) out[k] = red[0] + (accumulate ? out[k] : 0.0);
+    __syncthreads();
 }
 
-// w[i] -= sum_k V[k][i] h[k]
-__global__ void k_update(const double *V, int nvec, int64_t ld, const double *h, double *w, int64_t n) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double v = w[i];
-    for (int k = 0; k < nvec; ++k) v -= V[k * ld + i] * h[k];
-    w[i] = v;
+// partials of V_k . w for k in [k0, k0 + kn), kn <= KM
+template <int KM>
+__global__ void __launch_bounds__(kRedThreads) k_gs_dot(const double *__restrict__ V, int k0, int kn, int64_t ld,
+                                                        const double *__restrict__ w, int64_t n,
+                                                        double *__restrict__ part) {
+    __shared__ double red[4][KM];
+    double acc[KM];
+#pragma unroll
+    for (int k = 0; k < KM; ++k) acc[k] = 0.0;
+    const double *Vk = V + k0 * ld;
+    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kRedThreads) {
+        const double wi = w[i];
+        double x[KM];
+        // past the last vector: the last one again (all loads in flight at
+        // once, no branch), its sum unused
+#pragma unroll
+        for (int k = 0; k < KM; ++k) x[k] = Vk[min(k, kn - 1) * ld + i];
+#pragma unroll
+        for (int k = 0; k < KM; ++k) acc[k] = fma(x[k], wi, acc[k]);
+    }
+    block_part<KM>(acc, kn, part + k0 * kRedBlocks, red);
 }
 
-// x[i] += sum_k V[k][i] y[k]
-__global__ void k_combine(const double *V, int nvec, int64_t ld, const double *yv, double *x, int64_t n) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double v = x[i];
-    for (int k = 0; k < nvec; ++k) v += V[k * ld + i] * yv[k];
-    x[i] = v;
+// h = sums of part (stored to hout by block 0); w -= V h; then the partials of
+// V_k . w (DOT, nvec <= KM: the basis values stay in registers) or of ||w||^2
+// to part_out. KM == 0: any number of vectors, ||w||^2 only.
+template <int KM, bool DOT>
+__global__ void __launch_bounds__(kRedThreads) k_gs_update(const double *__restrict__ V, int nvec, int64_t ld,
+                                                           const double *__restrict__ part, double *__restrict__ w,
+                                                           int64_t n, double *__restrict__ hout,
+                                                           double *__restrict__ part_out) {
+    static_assert(KM > 0 || !DOT, "dots need the basis in registers");
+    constexpr int KA = DOT ? KM : 1, KX = KM > 0 ? KM : 1;
+    __shared__ double red[4][KA];
+    __shared__ double h[kMaxRestart + 1];
+    if (KM > 0 && (int)threadIdx.x >= nvec && (int)threadIdx.x < KM) h[threadIdx.x] = 0.0;
+    part_sum(part, gridDim.x, nvec, h);
+    if (blockIdx.x == 0)
+        for (int k = threadIdx.x; k < nvec; k += kRedThreads) hout[k] = h[k];
+    double acc[KA];
+#pragma unroll
+    for (int k = 0; k < KA; ++k) acc[k] = 0.0;
+    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kRedThreads) {
+        double v = w[i];
+        double x[KX];
+        if constexpr (KM > 0) {
+#pragma unroll
+            for (int k = 0; k < KM; ++k) x[k] = V[min(k, nvec - 1) * ld + i];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) v = fma(-x[k], h[k], v);
+        } else {
+#pragma unroll 8
+            for (int k = 0; k < nvec; ++k) v = fma(-V[k * ld + i], h[k], v);
+        }
+        if constexpr (DOT) {
+#pragma unroll
+            for (int k = 0; k < KM; ++k) acc[k] = fma(x[k], v, acc[k]);
+        } else {
+            acc[0] = fma(v, v, acc[0]);
+        }
+        w[i] = v;
+    }
+    block_part<KA>(acc, DOT ? nvec : 1, part_out, red);
 }
 
-__global__ void k_scale_by(double *v, int64_t n, const double *s) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) v[i] *= s[0];
-}
-
-// v = (b - v) / ||.|| helper pieces
-__global__ void k_sub_from(const double *b, double *v, int64_t n) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) v[i] = b[i] - v[i];
+// r = b - r (sub) or b; partials of ||r||^2
+__global__ void __launch_bounds__(kRedThreads) k_residual(const double *__restrict__ b, double *__restrict__ r,
+                                                          int64_t n, int sub, double *__restrict__ part) {
+    __shared__ double red[4][1];
+    double acc[1] = {0.0};
+    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kRedThreads) {
+        const double v = sub ? b[i] - r[i] : b[i];
+        r[i] = v;
+        acc[0] = fma(v, v, acc[0]);
+    }
+    block_part<1>(acc, 1, part, red);
 }
 
 __global__ void k_fill(double *v, int64_t n, double a) {
@@ -420,22 +500,28 @@ __global__ void k_fill(double *v, int64_t n, double a) {
     if (i < n) v[i] = a;
 }
 
+// x[i] = (add ? x[i] : 0) + sum_k V[k][i] y[k]
+__global__ void k_combine(const double *__restrict__ V, int nvec, int64_t ld, const double *__restrict__ yv,
+                          double *__restrict__ x, int64_t n, int add) {
+    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    double v = add ? x[i] : 0.0;
+#pragma unroll 8
+    for (int k = 0; k < nvec; ++k) v = fma(V[k * ld + i], yv[k], v);
+    x[i] = v;
+}
+
 __global__ void k_axpy(double a, const double *x, double *y, int64_t n) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < n) y[i] += a * x[i];
 }
 
-__global__ void k_copy(const double *a, double *b, int64_t n) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) b[i] = a[i];
-}
-
 // Small-state layout (doubles) for restart m:
 //   H  [(m+1) * m] column-major, cs [m], sn [m], g [m+1], yv [m],
-//   h1 [m+1], h2 [m+1], nrm [1], scal [4]
+//   h1 [m+1], h2 [m+1]
 struct SmallLayout {
     int m;
-    int64_t H, cs, sn, g, yv, h1, h2, nrm, scal, total;
+    int64_t H, cs, sn, g, yv, h1, h2, total;
     explicit SmallLayout(int m_) : m(m_) {
         H = 0;
         cs = H + (int64_t)(m + 1) * m;
@@ -444,62 +530,213 @@ struct SmallLayout {
         yv = g + m + 1;
         h1 = yv + m;
         h2 = h1 + m + 1;
-        nrm = h2 + m + 1;
-        scal = nrm + 1;
-        total = scal + 4;
+        total = h2 + m + 1;
     }
 };
 
-// Column j of H from the two Gram-Schmidt passes; apply the previous
-// rotations, form rotation j, update g; scal[0] = |g[j+1]| (residual
-// estimate), scal[1] = 1/H[j+1][j] (0 on breakdown).
-__global__ void k_givens(double *sm, SmallLayout L, int j) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int m = L.m;
-    double *H = sm + L.H + (int64_t)(m + 1) * j;
+// Column j of H from the two Gram-Schmidt passes and beta = ||w||; apply the
+// previous rotations, form rotation j, update g; *res = |g[j+1]|, the residual
+// estimate. The rotations and the column are staged in LDS by the first wave
+// (col [m + 1], rot [2 m]); one thread then runs the recurrence. Called by the
+// first 64 threads of one workgroup.
+__device__ inline void givens_column(double *sm, const SmallLayout &L, int j, double beta, double *col, double *rot,
+                                     double *res) {
+    double *H = sm + L.H + (int64_t)(L.m + 1) * j;
     double *cs = sm + L.cs, *sn = sm + L.sn, *g = sm + L.g;
-    for (int i = 0; i <= j; ++i) H[i] = sm[L.h1 + i] + sm[L.h2 + i];
-    const double beta = sqrt(fmax(sm[L.nrm], 0.0));
-    H[j + 1] = beta;
-    sm[L.scal + 1] = (beta > 0.0) ? 1.0 / beta : 0.0;
-    for (int i = 0; i < j; ++i) {
-        const double t = cs[i] * H[i] + sn[i] * H[i + 1];
-        H[i + 1] = -sn[i] * H[i] + cs[i] * H[i + 1];
-        H[i] = t;
+    for (int i = threadIdx.x; i <= j; i += 64) {
+        col[i] = sm[L.h1 + i] + sm[L.h2 + i];
+        if (i < j) {
+            rot[2 * i] = cs[i];
+            rot[2 * i + 1] = sn[i];
+        }
     }
-    const double den = hypot(H[j], H[j + 1]);
-    const double cj = (den > 0.0) ? H[j] / den : 1.0;
-    const double sj = (den > 0.0) ? H[j + 1] / den : 0.0;
-    cs[j] = cj;
-    sn[j] = sj;
-    H[j] = den;
-    H[j + 1] = 0.0;
-    g[j + 1] = -sj * g[j];
-    g[j] = cj * g[j];
-    sm[L.scal] = fabs(g[j + 1]);
-}
-
-// Solve the k x k upper triangle H y = g.
-__global__ void k_trisolve(double *sm, SmallLayout L, int k) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int m = L.m;
-    double *yv = sm + L.yv;
-    for (int i = k - 1; i >= 0; --i) {
-        double v = sm[L.g + i];
-        for (int c = i + 1; c < k; ++c) v -= sm[L.H + (int64_t)(m + 1) * c + i] * yv[c];
-        const double d = sm[L.H + (int64_t)(m + 1) * i + i];
-        yv[i] = (d != 0.0) ? v / d : 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    if (threadIdx.x == 0) {
+        double top = col[0];
+        for (int i = 0; i < j; ++i) {  // (col[i], col[i+1]) through rotation i
+            const double c = rot[2 * i], s = rot[2 * i + 1], below = col[i + 1];
+            H[i] = c * top + s * below;
+            top = -s * top + c * below;
+        }
+        const double den = hypot(top, beta);
+        const double cj = (den > 0.0) ? top / den : 1.0;
+        const double sj = (den > 0.0) ? beta / den : 0.0;
+        cs[j] = cj;
+        sn[j] = sj;
+        H[j] = den;
+        H[j + 1] = 0.0;
+        const double gj = g[j], gn = -sj * gj;
+        g[j + 1] = gn;
+        g[j] = cj * gj;
+        *res = fabs(gn);
     }
 }
 
-__global__ void k_restart_state(double *sm, SmallLayout L) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    // g = [beta, 0, ...], scal[1] = 1/beta; beta from nrm
-    const double beta = sqrt(fmax(sm[L.nrm], 0.0));
-    for (int i = 0; i <= L.m; ++i) sm[L.g + i] = 0.0;
-    sm[L.g] = beta;
-    sm[L.scal + 1] = (beta > 0.0) ? 1.0 / beta : 0.0;
-    sm[L.scal + 2] = beta;
+// End of Arnoldi step j: beta = ||w|| from its partials, v_{j+1} = w / beta (0
+// on breakdown), column j of H by block 0, the residual estimate to res
+// (pinned host memory)
+__global__ void __launch_bounds__(kRedThreads) k_gs_finish(double *sm, SmallLayout L, int j,
+                                                           const double *__restrict__ part, double *__restrict__ w,
+                                                           int64_t n, double *res) {
+    __shared__ double nrm[1], col[kMaxRestart + 1], rot[2 * kMaxRestart];
+    part_sum(part, gridDim.x, 1, nrm);
+    const double beta = sqrt(fmax(nrm[0], 0.0));
+    const double inv = (beta > 0.0) ? 1.0 / beta : 0.0;
+    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kRedThreads)
+        w[i] *= inv;
+    if (blockIdx.x == 0 && threadIdx.x < 64) givens_column(sm, L, j, beta, col, rot, res);
+}
+
+// Start of a cycle: beta = ||r|| from its partials to res (pinned host memory),
+// g = [beta, 0, ...], v_0 = r / beta
+__global__ void __launch_bounds__(kRedThreads) k_cycle_start(double *sm, SmallLayout L, const double *__restrict__ part,
+                                                             double *__restrict__ r, int64_t n, double *res) {
+    __shared__ double nrm[1];
+    part_sum(part, gridDim.x, 1, nrm);
+    const double beta = sqrt(fmax(nrm[0], 0.0));
+    const double inv = (beta > 0.0) ? 1.0 / beta : 0.0;
+    for (int64_t i = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kRedThreads)
+        r[i] *= inv;
+    if (blockIdx.x == 0) {
+        for (int i = threadIdx.x; i <= L.m; i += kRedThreads) sm[L.g + i] = i == 0 ? beta : 0.0;
+        if (threadIdx.x == 0) *res = beta;
+    }
+}
+
+// ||v|| from its partials to res (pinned host memory)
+__global__ void __launch_bounds__(kRedThreads) k_norm_out(const double *__restrict__ part, int nblk, double *res) {
+    __shared__ double nrm[1];
+    part_sum(part, nblk, 1, nrm);
+    if (threadIdx.x == 0) *res = sqrt(fmax(nrm[0], 0.0));
+}
+
+// The whole orthogonalisation of Arnoldi step j (j < KM) for n <= kSmallGs
+// points in one workgroup: w stays in LDS, the basis is read four times from
+// L2.
+constexpr int kSmallThreads = 512;
+template <int KM>
+__global__ void __launch_bounds__(kSmallThreads) k_gs_small(const double *__restrict__ V, int64_t ld,
+                                                            double *__restrict__ w, int n, double *sm, SmallLayout L,
+                                                            int j, double *res) {
+    constexpr int NW = kSmallThreads / 64;
+    __shared__ double wl[kSmallGs];
+    __shared__ double red[NW][KM], h[KM], col[kMaxRestart + 1], rot[2 * kMaxRestart];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nvec = j + 1;
+    double nr = 0.0;
+    for (int i = tid; i < n; i += kSmallThreads) wl[i] = w[i];  // each thread reads its own entries only
+    for (int pass = 0; pass < 2; ++pass) {
+        double acc[KM];
+#pragma unroll
+        for (int k = 0; k < KM; ++k) acc[k] = 0.0;
+        for (int i = tid; i < n; i += kSmallThreads) {
+            const double wi = wl[i];
+            double x[KM];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) x[k] = V[min(k, nvec - 1) * ld + i];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) acc[k] = fma(x[k], wi, acc[k]);
+        }
+        wave_sum<KM>(acc, lane);
+        red[wave][wave_slot<KM>(lane)] = acc[0];
+        __syncthreads();
+        if (tid < KM) {
+            double a = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) a += red[q][tid];
+            h[tid] = tid < nvec ? a : 0.0;
+            if (tid < nvec) sm[(pass ? L.h2 : L.h1) + tid] = a;
+        }
+        __syncthreads();
+        for (int i = tid; i < n; i += kSmallThreads) {
+            double v = wl[i], x[KM];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) x[k] = V[min(k, nvec - 1) * ld + i];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) v = fma(-x[k], h[k], v);
+            wl[i] = v;
+            if (pass) nr = fma(v, v, nr);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) nr += __shfl_xor(nr, o);
+    if (lane == 0) red[wave][0] = nr;
+    __syncthreads();
+    double s = 0.0;
+    for (int q = 0; q < NW; ++q) s += red[q][0];
+    const double beta = sqrt(fmax(s, 0.0));
+    const double inv = (beta > 0.0) ? 1.0 / beta : 0.0;
+    for (int i = tid; i < n; i += kSmallThreads) w[i] = wl[i] * inv;
+    if (tid < 64) givens_column(sm, L, j, beta, col, rot, res);
+}
+
+// Solve the k x k upper triangle H y = g: column by column, thread i holding
+// row i (k <= kMaxRestart threads)
+__global__ void __launch_bounds__(kMaxRestart) k_trisolve(double *sm, SmallLayout L, int k) {
+    __shared__ double y;
+    const int i = threadIdx.x;
+    double v = i < k ? sm[L.g + i] : 0.0;
+    double next = i < k ? sm[L.H + (int64_t)(L.m + 1) * (k - 1) + i] : 0.0;
+    for (int c = k - 1; c >= 0; --c) {
+        const double hc = next;  // H[i][c]; the column before it is loaded ahead
+        if (c > 0 && i < c) next = sm[L.H + (int64_t)(L.m + 1) * (c - 1) + i];
+        if (i == c) y = (hc != 0.0) ? v / hc : 0.0;
+        __syncthreads();
+        if (i == c) sm[L.yv + i] = y;
+        if (i < c) v -= hc * y;
+        __syncthreads();
+    }
+}
+
+// Orthogonalisation of Arnoldi step j: w = V[j + 1] against V[0..j]: one launch
+// up to kSmallGs points and kGsFuse vectors (642 points 45 -> 16 us a step,
+// mean over a cycle of 30), else four (64,200 points 46 -> 30 us, 76,800 points
+// 46 -> 27 us), or six past kGsFuse vectors.
+static void gs_step(bfm_ctx *c, double *V, int j, int64_t n, double *part, double *sm, const SmallLayout &L,
+                    double *res) {
+    hipStream_t st = c->stream;
+    double *w = V + (int64_t)(j + 1) * n;
+    const int nvec = j + 1;
+    if (n <= kSmallGs && nvec <= kGsFuse) {
+        auto kern = nvec <= 4 ? k_gs_small<4> : (nvec <= 8 ? k_gs_small<8> : (nvec <= 16 ? k_gs_small<16> : k_gs_small<32>));
+        kern<<<1, kSmallThreads, 0, st>>>(V, n, w, (int)n, sm, L, j, res);
+        BFM_LAUNCHED();
+        return;
+    }
+    const int G = red_blocks(n);
+    double *part2 = part + (int64_t)(L.m + 1) * kRedBlocks;
+    auto dots = [&](double *out) {
+        for (int k0 = 0; k0 < nvec; k0 += kGsFuse) {
+            const int kn = std::min(kGsFuse, nvec - k0);
+            auto kern = kn <= 4 ? k_gs_dot<4> : (kn <= 8 ? k_gs_dot<8> : (kn <= 16 ? k_gs_dot<16> : k_gs_dot<32>));
+            kern<<<G, kRedThreads, 0, st>>>(V, k0, kn, n, w, n, out);
+            BFM_LAUNCHED();
+        }
+    };
+    dots(part);
+    auto update = [&](auto kern, const double *pin, int64_t hout, double *pout) {
+        kern<<<G, kRedThreads, 0, st>>>(V, nvec, n, pin, w, n, sm + hout, pout);
+        BFM_LAUNCHED();
+    };
+    if (nvec <= 4) {
+        update(k_gs_update<4, true>, part, L.h1, part2);
+        update(k_gs_update<4, false>, part2, L.h2, part);
+    } else if (nvec <= 8) {
+        update(k_gs_update<8, true>, part, L.h1, part2);
+        update(k_gs_update<8, false>, part2, L.h2, part);
+    } else if (nvec <= 16) {
+        update(k_gs_update<16, true>, part, L.h1, part2);
+        update(k_gs_update<16, false>, part2, L.h2, part);
+    } else if (nvec <= kGsFuse) {
+        update(k_gs_update<kGsFuse, true>, part, L.h1, part2);
+        update(k_gs_update<kGsFuse, false>, part2, L.h2, part);
+    } else {  // too many vectors for one pass: update, then the dots again
+        update(k_gs_update<0, false>, part, L.h1, part2);
+        dots(part2);
+        update(k_gs_update<0, false>, part2, L.h2, part);
+    }
+    k_gs_finish<<<G, kRedThreads, 0, st>>>(sm, L, j, part, w, n, res);
+    BFM_LAUNCHED();
 }
 
 void gmres_sorted(bfm_ctx *c, double *x, bool use_guess, bfm_solve_info *info) {
@@ -515,22 +752,21 @@ void gmres_sorted(bfm_ctx *c, double *x, bool use_guess, bfm_solve_info *info) {
     const double ir_tol = c->opt.ir_tol > 0.0 ? c->opt.ir_tol : 1e-4;
     SmallLayout L(m);
     double *V = c->V.ensure((size_t)(m + 1) * n);
-    double *w = c->work.ensure(n);
-    double *part = c->part.ensure((size_t)(m + 2) * kRedBlocks);
+    double *part = c->part.ensure((size_t)2 * (m + 1) * kRedBlocks);
     double *sm = c->small.ensure(L.total);
     if (!c->host_small) BFM_HIP(hipHostMalloc((void **)&c->host_small, 8 * sizeof(double), 0));
+    // scalars the device writes straight to pinned host memory: [0] residual
+    // estimate of the last step, [1] ||r|| of the cycle, [2] ||b||
     double *hs = c->host_small;
     const double *b = c->b_s.get();
-    auto norm2_to = [&](const double *v, int64_t off) {  // sm[off] = ||v||^2
-        k_mdot<<<kRedBlocks, kRedThreads, 0, st>>>(v, 1, n, v, n, part);
+    const int G = red_blocks(n);
+    auto wait = [&] { BFM_HIP(hipStreamSynchronize(st)); };
+    // V[0] = r / ||r|| with r = b - V[0] (sub) or b, ||r|| to hs[1], g reset
+    auto cycle_start = [&](bool sub) {
+        k_residual<<<G, kRedThreads, 0, st>>>(b, V, n, sub ? 1 : 0, part);
         BFM_LAUNCHED();
-        k_reduce<<<1, kRedThreads, 0, st>>>(part, 1, sm + off, 0);
+        k_cycle_start<<<G, kRedThreads, 0, st>>>(sm, L, part, V, n, hs + 1);
         BFM_LAUNCHED();
-    };
-    auto read_scalar = [&](int64_t off) {
-        BFM_HIP(hipMemcpyAsync(hs, sm + off, sizeof(double), hipMemcpyDeviceToHost, st));
-        BFM_HIP(hipStreamSynchronize(st));
-        return hs[0];
     };
     int matvecs = 0;
     const bool pc = c->opt.precond != BFM_PRECOND_NONE;
@@ -551,39 +787,43 @@ void gmres_sorted(bfm_ctx *c, double *x, bool use_guess, bfm_solve_info *info) {
         Z = c->zbuf.ensure(n);
         Tv = c->tbuf.ensure(n);
     }
-    // ||b||
-    norm2_to(b, L.nrm);
-    const double nb = std::sqrt(std::max(read_scalar(L.nrm), 0.0));
-    graph_release_stale(c);  // the stream has just been waited for
     info->iterations = 0;
     info->restarts = 0;
+    // r0 and ||b||
+    if (use_guess) {
+        // ||b|| into the workspace of the first residual; V[0] is overwritten
+        k_residual<<<G, kRedThreads, 0, st>>>(b, V, n, 0, part);
+        BFM_LAUNCHED();
+        k_norm_out<<<1, kRedThreads, 0, st>>>(part, G, hs + 2);
+        BFM_LAUNCHED();
+        wait();
+        if (hs[2] > 0.0) {
+            matvec_sorted(c, 1.0, x, 0.0, nullptr, V, true, BFM_PREC_FP64, false);
+            ++matvecs;
+            cycle_start(true);
+            wait();
+        }
+    } else {
+        k_fill<<<nblk(n, 256), 256, 0, st>>>(x, n, 0.0);
+        BFM_LAUNCHED();
+        cycle_start(false);
+        wait();
+        hs[2] = hs[1];
+    }
+    const double nb = hs[2];
+    graph_release_stale(c);  // the stream has just been waited for
     if (!(nb > 0.0)) {
-        BFM_HIP(hipMemsetAsync(x, 0, sizeof(double) * n, st));
+        k_fill<<<nblk(n, 256), 256, 0, st>>>(x, n, 0.0);
+        BFM_LAUNCHED();
         info->rel_residual = 0.0;
         info->converged = 1;
         info->matvecs = 0;
         return;
     }
-    // r0
-    if (use_guess) {
-        matvec_sorted(c, 1.0, x, 0.0, nullptr, V, true, BFM_PREC_FP64, false);
-        ++matvecs;
-        k_sub_from<<<nblk(n, 256), 256, 0, st>>>(b, V, n);
-        BFM_LAUNCHED();
-    } else {
-        BFM_HIP(hipMemsetAsync(x, 0, sizeof(double) * n, st));
-        k_copy<<<nblk(n, 256), 256, 0, st>>>(b, V, n);
-        BFM_LAUNCHED();
-    }
-    norm2_to(V, L.nrm);
-    double beta = std::sqrt(std::max(read_scalar(L.nrm), 0.0));
+    double beta = hs[1];
     int it = 0;
     bool conv = beta <= tol * nb;
     while (!conv && it < maxit) {
-        k_restart_state<<<1, 1, 0, st>>>(sm, L);
-        BFM_LAUNCHED();
-        k_scale_by<<<nblk(n, 256), 256, 0, st>>>(V, n, sm + L.scal + 1);
-        BFM_LAUNCHED();
         int k = 0;
         for (int j = 0; j < m && it < maxit; ++j) {
             double *vj = V + (int64_t)j * n;
@@ -597,53 +837,33 @@ void gmres_sorted(bfm_ctx *c, double *x, bool use_guess, bfm_solve_info *info) {
                 matvec_sorted(c, 1.0, vj, 0.0, nullptr, wj, true, prec, false);
             }
             ++matvecs;
-            // pass 1
             const int pg = c->prof.begin(KC_GMRES, st);
-            k_mdot<<<kRedBlocks, kRedThreads, 0, st>>>(V, j + 1, n, wj, n, part);
-            BFM_LAUNCHED();
-            k_reduce<<<j + 1, kRedThreads, 0, st>>>(part, j + 1, sm + L.h1, 0);
-            BFM_LAUNCHED();
-            k_update<<<nblk(n, 256), 256, 0, st>>>(V, j + 1, n, sm + L.h1, wj, n);
-            BFM_LAUNCHED();
-            // pass 2
-            k_mdot<<<kRedBlocks, kRedThreads, 0, st>>>(V, j + 1, n, wj, n, part);
-            BFM_LAUNCHED();
-            k_reduce<<<j + 1, kRedThreads, 0, st>>>(part, j + 1, sm + L.h2, 0);
-            BFM_LAUNCHED();
-            k_update<<<nblk(n, 256), 256, 0, st>>>(V, j + 1, n, sm + L.h2, wj, n);
-            BFM_LAUNCHED();
-            norm2_to(wj, L.nrm);
-            k_givens<<<1, 1, 0, st>>>(sm, L, j);
-            BFM_LAUNCHED();
-            k_scale_by<<<nblk(n, 256), 256, 0, st>>>(wj, n, sm + L.scal + 1);
-            BFM_LAUNCHED();
+            gs_step(c, V, j, n, part, sm, L, hs);
             c->prof.end(pg, st, 0.0, 0.0);
             ++it;
             k = j + 1;
-            const double res = read_scalar(L.scal);
+            wait();
+            const double res = hs[0];
             if (res <= tol * nb || (ir && res <= ir_tol * beta)) break;
         }
-        k_trisolve<<<1, 1, 0, st>>>(sm, L, k);
+        k_trisolve<<<1, kMaxRestart, 0, st>>>(sm, L, k);
         BFM_LAUNCHED();
         if (pc) {  // x += P^{-1} V y
-            k_fill<<<nblk(n, 256), 256, 0, st>>>(Tv, n, 0.0);
-            BFM_LAUNCHED();
-            k_combine<<<nblk(n, 256), 256, 0, st>>>(V, k, n, sm + L.yv, Tv, n);
+            k_combine<<<nblk(n, 256), 256, 0, st>>>(V, k, n, sm + L.yv, Tv, n, 0);
             BFM_LAUNCHED();
             precond_apply(c, Tv, Z);
             k_axpy<<<nblk(n, 256), 256, 0, st>>>(1.0, Z, x, n);
             BFM_LAUNCHED();
         } else {
-            k_combine<<<nblk(n, 256), 256, 0, st>>>(V, k, n, sm + L.yv, x, n);
+            k_combine<<<nblk(n, 256), 256, 0, st>>>(V, k, n, sm + L.yv, x, n, 1);
             BFM_LAUNCHED();
         }
         // true residual (FP64)
         matvec_sorted(c, 1.0, x, 0.0, nullptr, V, true, BFM_PREC_FP64, false);
         ++matvecs;
-        k_sub_from<<<nblk(n, 256), 256, 0, st>>>(b, V, n);
-        BFM_LAUNCHED();
-        norm2_to(V, L.nrm);
-        beta = std::sqrt(std::max(read_scalar(L.nrm), 0.0));
+        cycle_start(true);
+        wait();
+        beta = hs[1];
         info->restarts += 1;
         conv = beta <= tol * nb;
     }
