@@ -123,6 +123,7 @@ void solve_impl(bfm_ctx *c, const double *phi_dev, double *q_dev, int guess, bfm
     // most of the device free (beside the diagonal pass its serial chain of
     // small kernels would wait for every wave of the pass's large launches)
     if (c->opt.precond == BFM_PRECOND_SH_COARSE && c->pre.nd > 0 && c->pre.genus == 0) {
+        precond_build(c);  // the build reads the template's basis
         coarse_mark(c);
         coarse_launch(c);
     }

@@ -29,14 +29,15 @@ struct Precond {
     std::vector<double> ang_h;   // template torus angles (theta around the tube, phi around the axis) [nd][2]
     std::vector<int> tri_h;      // template triangles (first bubble, local indices)
     ShBasis basis;
-    DevBuf<double> fac, R, X, C, Y;
-    DevBuf<double> gws;                // split-K partial products of the GEMMs
+    DevBuf<double> fac, R, X, C;
+    DevBuf<double> TS, TU;             // G^T s, G^T U per bubble [nc x nb] (two-level form)
     // coarse space of per-bubble constants (two-level form)
     DevBuf<double> U;                  // own-bubble column sums of s^T L, caller order [nv]
     DevBuf<double> ccen, carea;        // area-weighted centroids [nb][3], areas [nb]
     DevBuf<double> cusum;              // bubble sums of U [nb] (the coarse matrix's diagonal)
     DevBuf<double> Ainv, gj_row, gj_col, gj_piv;  // inverse coarse matrix [nb x nb] and Gauss-Jordan work
-    DevBuf<double> csum, cy;           // per-bubble sums [3][nb], coarse correction [nb]
+    DevBuf<double> csum, cy;           // per-bubble sums of the input [2][nb], coarse right-hand side and
+                                       // monopole strengths [2][nb]; coarse correction [nb]
 };
 // Near-field correction matrices (corr.hip). Pattern, original order: per
 // vertex i the near triangles tv[tptr[i]..tptr[i+1]) as (v0, v1, v2, the
@@ -172,7 +173,8 @@ void sh_basis_build(const Precond &P, int nmax, ShBasis &B, hipStream_t st, bool
 void torus_basis_build(const Precond &P, int h, ShBasis &B, hipStream_t st);
 void precond_build(bfm_ctx *c);
 void precond_radii(bfm_ctx *c);
-void precond_apply(bfm_ctx *c, const double *in_s, double *out_s);
+// out_s = P^{-1} in_s, or out_s += (add)
+void precond_apply(bfm_ctx *c, const double *in_s, double *out_s, bool add = false);
 // coarse correction of the two-level form on stream st (geometry of the
 // current mesh only)
 void coarse_build(bfm_ctx *c, hipStream_t st);
@@ -191,10 +193,9 @@ void spd_inverse(double *A, int n, DevBuf<double> &piv, DevBuf<double> &row, Dev
 // C = A B, column-major FP64 (precond.hip)
 void gemm_nn_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc,
                  hipStream_t st);
-// C = rowscale o (A B) + beta D (rowscale, D may be null; C may alias D);
-// ws non-null allows a split of K (partial products kept in ws)
-void gemm_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc,
-              const double *rowscale, double beta, const double *D, int ldd, DevBuf<double> *ws, hipStream_t st);
+// C = A B + beta D (D may be null; C may alias D)
+void gemm_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc, double beta,
+              const double *D, int ldd, hipStream_t st);
 
 // the solve of bfm_solve_dev: tree, diagonals and b, optional guess, GMRES
 // (guess: BFM_GUESS_*); throws BFM_ENOCONV when GMRES stops at gmres_maxit

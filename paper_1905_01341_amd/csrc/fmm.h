@@ -23,6 +23,16 @@ struct Sources {
     // near field, kDiagRec doubles each: x, y, z, n_x, n_y, n_z, q1, q2, q3,
     // w0, w1, w2, w3, w4 (channels 0 and 4 carry no monopole)
     const double *packed = nullptr;
+    // optional, one channel: the strengths are formed by the product itself
+    // before anything else, qout = f ps x and wout = g ps yv (a null x or yv:
+    // left alone); q and w then point at qout and wout
+    const double *ps = nullptr, *x = nullptr, *yv = nullptr;
+    double f = 0.0, g = 0.0;
+    double *qout = nullptr, *wout = nullptr;
+    // optional, one channel: the last step writes
+    // out = sums / (4 pi) [+ f lii x] [+ g mii yv] instead of the raw sums
+    double *out = nullptr;
+    const double *lii = nullptr, *mii = nullptr;
 };
 
 struct FmmWork {

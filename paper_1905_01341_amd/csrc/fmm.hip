@@ -19,6 +19,7 @@
 // in FP32.
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 #include <cstring>
@@ -381,7 +382,7 @@ __global__ void __launch_bounds__(64) k_m2l_reduce(const int *dst_off, const int
     static_assert(G == 1 || G * NV == 64, "groups tile the wave");
     const int64_t k = blockIdx.x;
     const int a = dst_off[k], e = dst_off[k + 1];
-    if (a == e) return;  // no far-field sources at this box's level (L stays zero)
+    // (a box without far-field sources gets zeros)
     float *lb = L + (box0 + k) * LD;
     const int lane = threadIdx.x, grp = lane / (G > 1 ? NV : 64);
     auto add = [](float4 &s, const float4 v) {
@@ -423,6 +424,26 @@ __global__ void __launch_bounds__(64) k_m2l_reduce(const int *dst_off, const int
             }
         }
         if (cv < NV && grp == 0) *reinterpret_cast<float4 *>(lb + c) = s;
+    }
+}
+
+// Start of a product, one launch: the multipole expansions and (ny > 0) the
+// sums cleared, and with ps the source strengths q = f ps x, w = g ps yv (null
+// x or yv: left alone). nM is a multiple of four.
+template <class R>
+__global__ void __launch_bounds__(256) k_prepare(R *M, int64_t nM, double *y, int64_t ny, const double *ps, int64_t n,
+                                                 double f, const double *x, double g, const double *yv, double *q,
+                                                 double *w) {
+    const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    constexpr int V = 16 / sizeof(R);
+    uint4 *M4 = reinterpret_cast<uint4 *>(M);
+    for (int64_t i = i0; i < nM / V; i += step) M4[i] = make_uint4(0, 0, 0, 0);
+    for (int64_t i = i0; i < ny; i += step) y[i] = 0.0;
+    if (!ps) return;
+    for (int64_t i = i0; i < n; i += step) {
+        const double s = ps[i];
+        if (x) q[i] = f * s * x[i];
+        if (yv) w[i] = g * s * yv[i];
     }
 }
 
@@ -748,22 +769,20 @@ static void translate_bf3(FmmWork &w, int cls, TaskList &tl, bool swap, const ui
         constexpr int P1 = m2l_class_order(P_, 1), P2 = m2l_class_order(P_, 2);
         int cut1 = (int)tl.ntasks, cut2 = (int)tl.ntasks;
         if (w.m2l_orders) {
-            int first[kM2LClasses + 1];
+            int first[kM2LClasses + 1], gfirst[kM2LClasses + 1], order[kM2LClasses];
             for (int c = 0; c <= kM2LClasses; ++c) first[c] = m2l_class_first_op(c);
+            const int ng = m2l_order_groups(P_, 1, gfirst, order);  // one launch per order
             flops = 0.0;
-            for (int c = 0; c < kM2LClasses; ++c) {
-                const int g0 = tiles_before(tl, 1, kBfTile, first[c]);
-                const int g1 = tiles_before(tl, 1, kBfTile, first[c + 1]);
-                const int64_t nk = tl.op_off_h[first[c + 1]] - tl.op_off_h[first[c]];
-                const int po = m2l_class_order(P_, c);
-                flops += 2.0 * (double)po * po * po * po * (double)nk;
-                const int nops = first[c + 1] - first[c];
-                if (c == 0)
-                    launch_bf3<PP, PP, true>(first[c], nops, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
-                else if (c == 1)
-                    launch_bf3<P1 * P1, PP, true>(first[c], nops, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
+            for (int k = 0; k < ng; ++k) {
+                const int o0 = gfirst[k], o1 = gfirst[k + 1], po = order[k];
+                const int g0 = tiles_before(tl, 1, kBfTile, o0), g1 = tiles_before(tl, 1, kBfTile, o1);
+                flops += 2.0 * (double)po * po * po * po * (double)(tl.op_off_h[o1] - tl.op_off_h[o0]);
+                if (po == P_)
+                    launch_bf3<PP, PP, true>(o0, o1 - o0, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
+                else if (po == P1)
+                    launch_bf3<P1 * P1, PP, true>(o0, o1 - o0, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
                 else
-                    launch_bf3<P2 * P2, PP, true>(first[c], nops, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
+                    launch_bf3<P2 * P2, PP, true>(o0, o1 - o0, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
             }
             cut1 = tl.op_off_h[first[1]];
             cut2 = tl.op_off_h[first[2]];
@@ -781,6 +800,14 @@ static void translate_bf3(FmmWork &w, int cls, TaskList &tl, bool swap, const ui
     prof_end(w, pi, st, flops);
 }
 
+template <class R>
+static void prepare(const Tree &t, const Sources &src, R *M, size_t ncoef, double *y, int64_t ny, hipStream_t st) {
+    const int64_t most = std::max<int64_t>({(int64_t)(ncoef * sizeof(R) / 16), ny, src.ps ? t.n : 0, 1});
+    k_prepare<R><<<(unsigned)std::min<int64_t>(2048, nblk(most, 256)), 256, 0, st>>>(
+        M, (int64_t)ncoef, y, ny, src.ps, t.n, src.f, src.x, src.g, src.yv, src.qout, src.wout);
+    BFM_LAUNCHED();
+}
+
 template <int P_, int NCH, bool MONO, bool DIP>
 static void run_fmm(FmmWork &w, const Tree &tc, const Sources &src, double *y, hipStream_t st) {
     Tree &t = const_cast<Tree &>(tc);
@@ -789,8 +816,7 @@ static void run_fmm(FmmWork &w, const Tree &tc, const Sources &src, double *y, h
     const size_t ncoef = (size_t)t.nbox * NCH * PP;
     double *M = w.mexp.ensure(ncoef);
     double *L = w.lexp.ensure(ncoef);
-    k_zero<double><<<1024, 256, 0, st>>>(M, (int64_t)ncoef);
-    BFM_LAUNCHED();
+    prepare<double>(t, src, M, ncoef, y, near_adds<NCH, MONO, DIP>(t) ? (int64_t)NCH * t.n : 0, st);
     // the M2L writes every target expansion; only the rotation-factored form
     // adds into it, and no task list means no M2L
     if (w.m2l_shape == 3 || t.m2l.ntasks <= 0) {
@@ -822,7 +848,7 @@ static void run_fmm(FmmWork &w, const Tree &tc, const Sources &src, double *y, h
     for (int l = 3; l <= lmax; ++l) translate64<P_>(w, KC_M2M_L2L, *t.m2m[l], NCH, true, L, L, st);
     if (ns != st) BFM_HIP(hipStreamWaitEvent(st, w.ev_join, 0));
     pi = prof_begin(w, KC_L2P, st);
-    launch_l2p<P_, NCH>(t, L, y, st);
+    launch_l2p<P_, NCH>(t, src, L, y, st);
     prof_end(w, pi, st, 0.0);
 }
 
@@ -836,10 +862,12 @@ static void run_fmm_lo(FmmWork &w, const Tree &tc, const Sources &src, double *y
     const size_t ncoef = (size_t)t.nbox * PP;
     float *M = w.mexp32.ensure(ncoef);
     float *L = w.lexp32.ensure(ncoef);
-    k_zero<float><<<1024, 256, 0, st>>>(M, (int64_t)ncoef);
-    BFM_LAUNCHED();
-    k_zero<float><<<1024, 256, 0, st>>>(L, (int64_t)ncoef);
-    BFM_LAUNCHED();
+    prepare<float>(t, src, M, ncoef, y, near_adds<1, MONO, DIP>(t) ? t.n : 0, st);
+    // the split-BF16 M2L writes every target expansion, the FP32 one adds
+    if (w.prec == BFM_PREC_FP32 || t.m2l.ntasks <= 0) {
+        k_zero<float><<<1024, 256, 0, st>>>(L, (int64_t)ncoef);
+        BFM_LAUNCHED();
+    }
     hipStream_t ns = (w.near && !(w.prof && w.prof->on)) ? w.near : st;
     if (ns != st) {
         BFM_HIP(hipEventRecord(w.ev_fork, st));
@@ -867,7 +895,7 @@ static void run_fmm_lo(FmmWork &w, const Tree &tc, const Sources &src, double *y
     }
     if (ns != st) BFM_HIP(hipStreamWaitEvent(st, w.ev_join, 0));
     pi = prof_begin(w, KC_L2P, st);
-    launch_l2p<P_, 1, float>(t, L, y, st);
+    launch_l2p<P_, 1, float>(t, src, L, y, st);
     prof_end(w, pi, st, 0.0);
 }
 

@@ -447,20 +447,6 @@ static size_t az_opw(int q) {
     return (size_t)cc * cc * 512;
 }
 
-// Order groups of the M2L offsets: consecutive distance classes applied at
-// one order. Returns the number of groups; first[g] = first offset, order[g].
-int az_groups(int p, int orders, int *first, int *order) {
-    int ng = 0;
-    for (int c = 0; c < kM2LClasses; ++c) {
-        const int q = orders ? m2l_class_order(p, c) : p;
-        if (ng && order[ng - 1] == q) continue;
-        first[ng] = m2l_class_first_op(c);
-        order[ng++] = q;
-    }
-    first[ng] = kNumM2LOps;
-    return ng;
-}
-
 namespace {
 struct AzHost {
     std::vector<double> m2m, l2l, m2l;
@@ -491,7 +477,7 @@ static AzHost az_build(int p, int orders) {
         az_factors(d[0], d[1], d[2], &h.fac[(size_t)o * kAzTab]);
     }
     int first[kM2LClasses + 1], order[kM2LClasses];
-    const int ng = az_groups(p, orders, first, order);
+    const int ng = m2l_order_groups(p, orders, first, order);
     struct Job {
         int op, q;
         size_t at;
@@ -645,7 +631,7 @@ int launch_translate_az(const AzLaunch &a, TaskList &tl, bool m2l, int shape, do
     }
     constexpr int P1 = m2l_class_order(P, 1), P2 = m2l_class_order(P, 2);
     int first[kM2LClasses + 1], order[kM2LClasses];
-    const int ng = az_groups(P, w.m2l_orders, first, order);
+    const int ng = m2l_order_groups(P, w.m2l_orders, first, order);
     for (int g = 0; g < ng; ++g) {
         *flops += col_flops(order[g]) * (double)(tl.op_off_h[first[g + 1]] - tl.op_off_h[first[g]]) * a.nch;
         const double *T = w.az_m2l.get() + w.az_goff[g];

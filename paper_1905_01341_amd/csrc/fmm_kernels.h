@@ -17,9 +17,17 @@ template <int P_, int NCH, bool MONO, bool DIP, class R = double>
 void launch_p2m(const Tree &t, const Sources &src, R *M, hipStream_t st);
 
 // y[c][i] += local expansion of point i's leaf evaluated at the point
-// (expansion and arithmetic in R; y stays FP64).
+// (expansion and arithmetic in R; y stays FP64), or the product's result where
+// src.out is set.
 template <int P_, int NCH, class R = double>
-void launch_l2p(const Tree &t, const R *L, double *y, hipStream_t st);
+void launch_l2p(const Tree &t, const Sources &src, const R *L, double *y, hipStream_t st);
+
+// Whether the near field of these channels adds into y, which must then be
+// cleared first (else it writes every sum).
+template <int NCH, bool MONO, bool DIP>
+inline bool near_adds(const Tree &t) {
+    return (NCH == 1 && MONO && !DIP) || t.near_split;
+}
 
 // y[c][i] = near-field sum of receiver i (leaf and neighbour leaves).
 template <int NCH, bool MONO, bool DIP>

@@ -283,12 +283,20 @@ __global__ void __launch_bounds__(64) k_p2m(const int2 *__restrict__ items, int6
 // the harmonics built in registers order by order. The leaf's coefficients
 // and the recurrence constants are first copied to LDS with coalesced loads;
 // every step reads them at a wave-uniform LDS address.
-template <int P_, int NCH, class R>
+// FIN (one channel): the product's result fin.out = (y + ...) / (4 pi) [+ f lii x]
+// [+ g mii yv] is written instead of the sum.
+struct L2PFinal {
+    double f, g;
+    const double *x, *yv, *lii, *mii;
+    double *out;
+};
+template <int P_, int NCH, class R, bool FIN>
 __global__ void __launch_bounds__(64) k_l2p(const int2 *__restrict__ items, int64_t leaf0,
                                             const int *__restrict__ leaf_pt, const double *__restrict__ centre,
                                             double h, const double *__restrict__ px, const double *__restrict__ py,
                                             const double *__restrict__ pz, int64_t n,
-                                            const R *__restrict__ lexp, double *__restrict__ y) {
+                                            const R *__restrict__ lexp, double *__restrict__ y, L2PFinal fin) {
+    static_assert(!FIN || NCH == 1, "one channel");
     constexpr int PP = P_ * P_;
     constexpr int NT = P_ * (P_ + 1) / 2;
     __shared__ R Ls[NCH * PP];
@@ -382,7 +390,13 @@ __global__ void __launch_bounds__(64) k_l2p(const int2 *__restrict__ items, int6
 #pragma unroll
     for (int u = 0; u < kPPL; ++u) {
         const int j = rb + 64 * u + lane;
-        if (j < re) {
+        if (j >= re) continue;
+        if constexpr (FIN) {
+            double v = kInv4Pi * (y[j] + (double)acc[u][0] * ih);
+            if (fin.lii && fin.x) v += fin.f * fin.lii[j] * fin.x[j];
+            if (fin.mii && fin.yv) v += fin.g * fin.mii[j] * fin.yv[j];
+            fin.out[j] = v;
+        } else {
 #pragma unroll
             for (int c = 0; c < NCH; ++c) y[(int64_t)c * n + j] += (double)acc[u][c] * ih;
         }
@@ -401,13 +415,16 @@ void launch_p2m(const Tree &t, const Sources &src, R *M, hipStream_t st) {
 }
 
 template <int P_, int NCH, class R>
-void launch_l2p(const Tree &t, const R *L, double *y, hipStream_t st) {
+void launch_l2p(const Tree &t, const Sources &src, const R *L, double *y, hipStream_t st) {
     if (t.n_leaf_items <= 0) return;
     const int64_t leaf0 = t.lvl_off[t.lmax];
     const double hleaf = t.side / (double)(1 << t.lmax);
-    k_l2p<P_, NCH, R><<<(unsigned)t.n_leaf_items, 64, 0, st>>>(t.leaf_items.get(), leaf0, t.leaf_pt.get(),
-                                                           t.box_centre.get(), hleaf, t.px.get(), t.py.get(),
-                                                           t.pz.get(), t.n, L, y);
+    const L2PFinal fin{src.f, src.g, src.x, src.yv, src.lii, src.mii, src.out};
+    auto kern = k_l2p<P_, NCH, R, false>;
+    if constexpr (NCH == 1)
+        if (src.out) kern = k_l2p<P_, NCH, R, true>;
+    kern<<<(unsigned)t.n_leaf_items, 64, 0, st>>>(t.leaf_items.get(), leaf0, t.leaf_pt.get(), t.box_centre.get(),
+                                                  hleaf, t.px.get(), t.py.get(), t.pz.get(), t.n, L, y, fin);
     BFM_LAUNCHED();
 }
 
@@ -416,12 +433,12 @@ void launch_l2p(const Tree &t, const R *L, double *y, hipStream_t st) {
     template void launch_p2m<P, 1, false, true>(const Tree &, const Sources &, double *, hipStream_t); \
     template void launch_p2m<P, 1, true, true>(const Tree &, const Sources &, double *, hipStream_t);  \
     template void launch_p2m<P, 5, true, true>(const Tree &, const Sources &, double *, hipStream_t);  \
-    template void launch_l2p<P, 1>(const Tree &, const double *, double *, hipStream_t);               \
-    template void launch_l2p<P, 5>(const Tree &, const double *, double *, hipStream_t);               \
+    template void launch_l2p<P, 1>(const Tree &, const Sources &, const double *, double *, hipStream_t); \
+    template void launch_l2p<P, 5>(const Tree &, const Sources &, const double *, double *, hipStream_t); \
     template void launch_p2m<P, 1, true, false, float>(const Tree &, const Sources &, float *, hipStream_t); \
     template void launch_p2m<P, 1, false, true, float>(const Tree &, const Sources &, float *, hipStream_t); \
     template void launch_p2m<P, 1, true, true, float>(const Tree &, const Sources &, float *, hipStream_t);  \
-    template void launch_l2p<P, 1, float>(const Tree &, const float *, double *, hipStream_t);
+    template void launch_l2p<P, 1, float>(const Tree &, const Sources &, const float *, double *, hipStream_t);
 BFM_LEAF_INST(4)
 BFM_LEAF_INST(8)
 BFM_LEAF_INST(12)

@@ -701,11 +701,6 @@ __global__ void __launch_bounds__(kP2PThreads) k_p2p32(const int4 *__restrict__ 
     }
 }
 
-__global__ void k_clear(double *p, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0;
-}
-
 // All-pairs sum (checking path): 64 receivers per wave x every source.
 template <int NCH, bool MONO, bool DIP>
 __global__ void __launch_bounds__(kP2PThreads) k_direct(const double *__restrict__ px,
@@ -741,18 +736,12 @@ void launch_p2p(const Tree &t, const Sources &src, double *y, hipStream_t st) {
     if constexpr (NCH == 1 && MONO && !DIP) {
         // one channel of monopoles: each pair once, added to both points
         BFM_CHECK(t.n_sym_items > 0, BFM_EINVAL, "symmetric near-field items missing");
-        k_clear<<<1024, 256, 0, st>>>(y, t.n);
-        BFM_LAUNCHED();
         k_p2p_sym<<<(unsigned)t.n_sym_items, kP2PThreads, 0, st>>>(t.sym_items.get(), t.leaf_pt.get(),
                                                                    t.near_rng.get(), t.near_cnt.get(), t.px.get(),
                                                                    t.py.get(), t.pz.get(), t.n, src.q, t.sym_chunk,
                                                                    y);
         BFM_LAUNCHED();
         return;
-    }
-    if (t.near_split) {
-        k_clear<<<1024, 256, 0, st>>>(y, (int64_t)NCH * t.n);
-        BFM_LAUNCHED();
     }
     auto kern = t.near_split ? k_p2p<NCH, MONO, DIP, true> : k_p2p<NCH, MONO, DIP, false>;
     kern<<<(unsigned)t.n_near_items, kP2PThreads, 0, st>>>(t.near_items.get(), t.leaf_pt.get(), t.near_rng.get(),
@@ -764,10 +753,6 @@ void launch_p2p(const Tree &t, const Sources &src, double *y, hipStream_t st) {
 
 void launch_p2p_packed(const Tree &t, const double *packed, double *y, hipStream_t st) {
     if (t.n_near_items <= 0) return;
-    if (t.near_split) {
-        k_clear<<<1024, 256, 0, st>>>(y, (int64_t)5 * t.n);
-        BFM_LAUNCHED();
-    }
     auto kern = t.near_split ? k_p2p_diag<true> : k_p2p_diag<false>;
     kern<<<(unsigned)t.n_near_items, kP2PThreads, 0, st>>>(t.near_items.get(), t.leaf_pt.get(), t.near_rng.get(),
                                                            t.near_cnt.get(), t.px.get(), t.py.get(), t.pz.get(),
@@ -789,8 +774,6 @@ void launch_p2p32(const Tree &t, const Sources &src, double *y, hipStream_t st) 
     const int64_t leaf0 = t.lvl_off[t.lmax];
     if constexpr (MONO && !DIP) {
         BFM_CHECK(t.n_sym_items > 0, BFM_EINVAL, "symmetric near-field items missing");
-        k_clear<<<1024, 256, 0, st>>>(y, t.n);
-        BFM_LAUNCHED();
         k_p2p_sym32<<<(unsigned)t.n_sym_items, kP2PThreads, 0, st>>>(
             t.sym_items.get(), t.leaf_pt.get(), t.near_rng.get(), t.near_cnt.get(), t.box_centre.get(), leaf0,
             t.px.get(), t.py.get(), t.pz.get(), src.q, t.sym_chunk, y);
@@ -798,8 +781,6 @@ void launch_p2p32(const Tree &t, const Sources &src, double *y, hipStream_t st) 
         return;
     }
     if (t.near_split) {
-        k_clear<<<1024, 256, 0, st>>>(y, t.n);
-        BFM_LAUNCHED();
     }
     auto kern = t.near_split ? k_p2p32<MONO, DIP, true> : k_p2p32<MONO, DIP, false>;
     kern<<<(unsigned)t.n_near_items, kP2PThreads, 0, st>>>(t.near_items.get(), t.leaf_pt.get(), t.near_rng.get(),

@@ -208,6 +208,18 @@ int m2l_class_first_op(int cls) {
     return (int)v.size();
 }
 
+int m2l_order_groups(int p, int orders, int *first, int *order) {
+    int ng = 0;
+    for (int c = 0; c < kM2LClasses; ++c) {
+        const int q = orders ? m2l_class_order(p, c) : p;
+        if (ng && order[ng - 1] == q) continue;
+        first[ng] = m2l_class_first_op(c);
+        order[ng++] = q;
+    }
+    first[ng] = kNumM2LOps;
+    return ng;
+}
+
 static_assert(m2l_class_order(20, 0) == 20 && m2l_class_order(20, 1) == 16 && m2l_class_order(20, 2) == 12,
               "class orders at p = 20");
 static_assert(m2l_class_order(16, 1) == 16 && m2l_class_order(16, 2) == 12 && m2l_class_order(12, 1) == 12 &&

@@ -29,6 +29,10 @@ constexpr int m2l_class_order(int p, int cls) {
     return cls <= 0 ? p : (cls == 1 ? 4 * ((p + 4) / 5) : 4 * ((3 * p + 19) / 20));
 }
 constexpr int kM2LClasses = 3;
+// Order groups: consecutive distance classes applied at one order (every class
+// at p unless `orders`). Returns their number; first[g] = first operator
+// (first[number]: 316), order[g].
+int m2l_order_groups(int p, int orders, int *first, int *order);
 void build_m2l(int p, int op, double *T);
 // Rotation-factored M2L of operator op: T = B T_z A (see ops.cpp). A and B:
 // one row-major (2n+1) x (2n+1) block per degree n < p at m2l_rot_offset(n)

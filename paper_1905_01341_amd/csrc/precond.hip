@@ -217,15 +217,12 @@ __global__ void k_bubble_radius(const double *s, int nd, double *R) {
     if (threadIdx.x == 0) R[b] = sqrt(red[0] / (4.0 * 3.14159265358979323846));
 }
 
-// C = rowscale o (A B) + beta D, column-major FP64 on MFMA
+// C = A B + beta D, column-major FP64 on MFMA
 // (v_mfma_f64_16x16x4f64). A workgroup of 4 waves owns a 64 x 64 tile of C
 // (each wave a 32 x 32 quarter, 2 x 2 MFMA blocks); K advances in chunks of
 // 32 staged through LDS, the next chunk's elements loaded into registers
-// while the current one is multiplied. With gridDim.z = S > 1 the K range is
-// split into S slices and slice z writes its raw partial product to
-// W + z M N (ld M); k_gemm_sum then adds the slices in a fixed order and
-// applies rowscale and beta D. rowscale and D may be null. C may alias D
-// (each element is read and written by the same lane) but not A or B.
+// while the current one is multiplied. D may be null. C may alias D (each
+// element is read and written by the same lane) but not A or B.
 // MFMA operand layout: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]
 // of a 16 x 4 by 4 x 16 product; element r of the result holds row
 // l / 16 + 4 r, column l % 16.
@@ -233,10 +230,9 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 constexpr int kGemmKC = 32;  // K chunk
 
-__global__ void __launch_bounds__(256) k_gemm_nn(int M, int N, int K, int kslice, const double *A, int lda,
-                                                 const double *B, int ldb, double *C, int ldc,
-                                                 const double *rowscale, double beta, const double *D, int ldd,
-                                                 double *W) {
+__global__ void __launch_bounds__(256) k_gemm_nn(int M, int N, int K, const double *A, int lda,
+                                                 const double *B, int ldb, double *C, int ldc, double beta,
+                                                 const double *D, int ldd) {
     // A and B chunks ([k][row], [k][col]); after the products the same LDS
     // holds the 64 x 64 result tile ([col][row]) for coalesced stores
     __shared__ double sbuf[2 * kGemmKC * (64 + 1)];
@@ -246,7 +242,6 @@ __global__ void __launch_bounds__(256) k_gemm_nn(int M, int N, int K, int kslice
     double(*Cs)[64 + 1] = reinterpret_cast<double(*)[64 + 1]>(sbuf);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
-    const int ka = blockIdx.z * kslice, kb = min(K, ka + kslice);
     const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
     dbl4 acc[2][2];
     for (int a = 0; a < 2; ++a)
@@ -260,14 +255,14 @@ __global__ void __launch_bounds__(256) k_gemm_nn(int M, int N, int K, int kslice
             const int e = tid + 256 * u;
             const int ii = e & 63, kk = e >> 6;
             const int gi = i0 + ii, gk = k0 + kk;
-            ra[u] = (gi < M && gk < kb) ? A[(int64_t)gk * lda + gi] : 0.0;
+            ra[u] = (gi < M && gk < K) ? A[(int64_t)gk * lda + gi] : 0.0;
             const int kq = e & 31, jj = e >> 5;
             const int gj = j0 + jj, gk2 = k0 + kq;
-            rb[u] = (gj < N && gk2 < kb) ? B[(int64_t)gj * ldb + gk2] : 0.0;
+            rb[u] = (gj < N && gk2 < K) ? B[(int64_t)gj * ldb + gk2] : 0.0;
         }
     };
-    if (ka < kb) load(ka);
-    for (int k0 = ka; k0 < kb; k0 += kGemmKC) {
+    if (K > 0) load(0);
+    for (int k0 = 0; k0 < K; k0 += kGemmKC) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int e = tid + 256 * u;
@@ -275,7 +270,7 @@ __global__ void __launch_bounds__(256) k_gemm_nn(int M, int N, int K, int kslice
             Bs[e & 31][e >> 5] = rb[u];
         }
         __syncthreads();
-        if (k0 + kGemmKC < kb) load(k0 + kGemmKC);  // in flight during the products
+        if (k0 + kGemmKC < K) load(k0 + kGemmKC);  // in flight during the products
 #pragma unroll
         for (int k4 = 0; k4 < kGemmKC / 4; ++k4) {
             const int kk = 4 * k4 + lane / 16;
@@ -302,72 +297,153 @@ __global__ void __launch_bounds__(256) k_gemm_nn(int M, int N, int K, int kslice
 #pragma unroll
             for (int r = 0; r < 4; ++r) Cs[wj + 16 * b + lane % 16][wi + 16 * a + lane / 16 + 4 * r] = acc[a][b][r];
     __syncthreads();
-    double *Wz = W ? W + (int64_t)blockIdx.z * M * N : nullptr;
     const int gi = i0 + lane;
 #pragma unroll 4
     for (int cc = wave; cc < 64; cc += 4) {
         const int gj = j0 + cc;
         if (gi < M && gj < N) {
             double val = Cs[cc][lane];
-            if (Wz) {
-                Wz[(int64_t)gj * M + gi] = val;
-            } else {
-                if (rowscale) val *= rowscale[gi];
-                if (D) val += beta * D[(int64_t)gj * ldd + gi];
-                C[(int64_t)gj * ldc + gi] = val;
-            }
+            if (D) val += beta * D[(int64_t)gj * ldd + gi];
+            C[(int64_t)gj * ldc + gi] = val;
         }
     }
 }
 
-// C = rowscale o (sum over the S slices of W) + beta D
-__global__ void k_gemm_sum(int M, int N, int S, const double *W, double *C, int ldc, const double *rowscale,
-                           double beta, const double *D, int ldd) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t mn = (int64_t)M * N;
-    if (e >= mn) return;
-    const int i = (int)(e % M), j = (int)(e / M);
-    double v = 0.0;
-    for (int z = 0; z < S; ++z) v += W[z * mn + e];
-    if (rowscale) v *= rowscale[i];
-    if (D) v += beta * D[(int64_t)j * ldd + i];
-    C[(int64_t)j * ldc + i] = v;
-}
-
-void gemm_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc,
-              const double *rowscale, double beta, const double *D, int ldd, DevBuf<double> *ws, hipStream_t st) {
+void gemm_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc, double beta,
+              const double *D, int ldd, hipStream_t st) {
     if (M <= 0 || N <= 0) return;
-    const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    // split K when the tiles alone leave most of the chip idle and the
-    // slices stay at least two chunks deep
-    int S = 1;
-    if (ws && tiles < 256) S = std::max(1, std::min((512 + tiles - 1) / tiles, K / (2 * kGemmKC)));
-    const int kslice = ((K + S - 1) / S + kGemmKC - 1) / kGemmKC * kGemmKC;
-    S = std::max(1, (K + kslice - 1) / kslice);
-    dim3 g((M + 63) / 64, (N + 63) / 64, S);
-    double *W = S > 1 ? ws->ensure((size_t)S * M * N) : nullptr;
-    k_gemm_nn<<<g, 256, 0, st>>>(M, N, K, kslice, A, lda, B, ldb, C, ldc, rowscale, beta, D, ldd, W);
+    k_gemm_nn<<<dim3((M + 63) / 64, (N + 63) / 64), 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, beta, D, ldd);
     BFM_LAUNCHED();
-    if (S > 1) {
-        k_gemm_sum<<<nblk((int64_t)M * N, 256), 256, 0, st>>>(M, N, S, W, C, ldc, rowscale, beta, D, ldd);
-        BFM_LAUNCHED();
-    }
 }
 
 // C = A B, all column-major (the plain product of k_gemm_nn)
 void gemm_nn_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc,
                  hipStream_t st) {
-    gemm_f64(M, N, K, A, lda, B, ldb, C, ldc, nullptr, 0.0, nullptr, 0, nullptr, st);
+    gemm_f64(M, N, K, A, lda, B, ldb, C, ldc, 0.0, nullptr, 0, st);
 }
 
-// out_s[i] = Y[perm[i]] / R[b] (+ cy[b]), b the bubble of perm[i]  (sorted order)
-__global__ void k_precond_out(const double *Y, const int *perm, int64_t n, int nd, const double *R,
-                              const double *cy, double *out) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int o = perm[i];
-    const int b = o / nd;
-    out[i] = Y[o] / R[b] + (cy ? cy[b] : 0.0);
+// X[b][v] = in_s at vertex v of bubble b (caller order), with the bubble's sums
+// xsum[0][b] = s . X, xsum[1][b] = U . X (U null: none). One workgroup per bubble.
+__global__ void __launch_bounds__(256) k_pre_gather(const double *__restrict__ in_s, const int *__restrict__ iperm,
+                                                    const double *__restrict__ s, const double *__restrict__ U, int nd,
+                                                    int nb, double *__restrict__ X, double *__restrict__ xsum) {
+    __shared__ double red[2][4];
+    const int b = blockIdx.x;
+    double a0 = 0.0, a1 = 0.0;
+    for (int v = threadIdx.x; v < nd; v += 256) {
+        const int64_t o = (int64_t)b * nd + v;
+        const double x = in_s[iperm[o]];
+        X[o] = x;
+        if (U) {
+            a0 = fma(s[o], x, a0);
+            a1 = fma(U[o], x, a1);
+        }
+    }
+    if (!U) return;
+    for (int o = 32; o > 0; o >>= 1) {
+        a0 += __shfl_xor(a0, o);
+        a1 += __shfl_xor(a1, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = a0;
+        red[1][threadIdx.x >> 6] = a1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const double *r = red[threadIdx.x];
+        xsum[(int64_t)threadIdx.x * nb + b] = ((r[0] + r[1]) + r[2]) + r[3];
+    }
+}
+
+// C[i][b] = fac[i] sum_v T(i, v) X[b][v] (fac null: 1), T(i, v) = T[v * sv + i * si],
+// C column-major [nc x nb]. One 16 x 16 tile (coefficients x bubbles) per
+// workgroup, the sum over v split over its four waves: a product of this size
+// (169 x 642 x 1000) is bound by the latency of a wave's chain of loads, and 16
+// x 16 tiles with four waves each give it 2772 short chains. 64 x 64 tiles
+// with a split sum and its own reduction launch took 14 + 4 us at 1000 bubbles.
+__global__ void __launch_bounds__(256) k_pre_coef(int nc, int nb, int nd, const double *__restrict__ T, int sv, int si,
+                                                  const double *__restrict__ X, const double *__restrict__ fac,
+                                                  double *__restrict__ C) {
+    constexpr int B = 8;  // MFMA steps whose loads are in flight together
+    __shared__ double red[3][4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4, rl = lane & 15;
+    const int i0 = blockIdx.x * 16, b0 = blockIdx.y * 16;
+    const double *xb = X + (int64_t)min(b0 + rl, nb - 1) * nd;
+    const double *tb = T + (int64_t)min(i0 + rl, nc - 1) * si;
+    const int steps = (nd + 3) / 4, s0 = steps * wave / 4, s1 = steps * (wave + 1) / 4;
+    dbl4 acc = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int s = s0; s < s1; s += B) {
+        double x[B], t[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int v = 4 * (s + u) + kq;
+            const int vc = min(v, nd - 1);
+            const bool ok = s + u < s1 && v < nd;
+            const double xv = xb[vc];
+            x[u] = ok ? xv : 0.0;
+            t[u] = tb[(int64_t)vc * sv];
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u], t[u], acc, 0, 0, 0);
+    }
+    if (wave > 0)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave - 1][r][lane] = acc[r];
+    __syncthreads();
+    if (wave > 0) return;
+    const int i = i0 + rl;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {  // bubble b0 + kq + 4 r, coefficient i0 + rl
+        const int b = b0 + kq + 4 * r;
+        const double v = ((acc[r] + red[0][r][lane]) + red[1][r][lane]) + red[2][r][lane];
+        if (b < nb && i < nc) C[(int64_t)b * nc + i] = fac ? fac[i] * v : v;
+    }
+}
+
+// out_s at vertex v of bubble b (+)= ((G C + cc X)[v][b]) / R[b] (+ cy[b]); G
+// column-major [nd x nc]. One wave per 32 vertices x 16 bubbles.
+__global__ void __launch_bounds__(64) k_pre_out(int nc, int nb, int nd, const double *__restrict__ G,
+                                                const double *__restrict__ C, double cc,
+                                                const double *__restrict__ X, const double *__restrict__ R,
+                                                const double *__restrict__ cy, const int *__restrict__ iperm, int add,
+                                                double *__restrict__ out) {
+    constexpr int B = 8;
+    const int lane = threadIdx.x, kq = lane >> 4, rl = lane & 15;
+    const int v0 = blockIdx.x * 32, b0 = blockIdx.y * 16;
+    const double *cb = C + (int64_t)min(b0 + rl, nb - 1) * nc;
+    const int va = min(v0 + rl, nd - 1), vb = min(v0 + 16 + rl, nd - 1);
+    const int steps = (nc + 3) / 4;
+    dbl4 acc[2] = {dbl4{0.0, 0.0, 0.0, 0.0}, dbl4{0.0, 0.0, 0.0, 0.0}};
+    for (int s = 0; s < steps; s += B) {
+        double c[B], ga[B], gb[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int i = 4 * (s + u) + kq, ic = min(i, nc - 1);
+            const double cv = cb[ic];
+            c[u] = i < nc ? cv : 0.0;
+            ga[u] = G[(int64_t)ic * nd + va];
+            gb[u] = G[(int64_t)ic * nd + vb];
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[u], ga[u], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[u], gb[u], acc[1], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int v = v0 + 16 * h + rl;
+        if (v >= nd) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int b = b0 + kq + 4 * r;
+            if (b >= nb) continue;
+            const int64_t o = (int64_t)b * nd + v;
+            const double y = fma(cc, X[o], acc[h][r]) / R[b] + (cy ? cy[b] : 0.0);
+            double *d = out + iperm[o];
+            *d = add ? *d + y : y;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -563,72 +639,53 @@ __global__ void k_gj_fix(double *A, int n, int k0, int bs, const double *Rn, con
         A[(int64_t)(k0 + c) * n + i] = -Pn[(int64_t)c * bs + (i - k0)];
 }
 
-// per bubble: sums[0][b] = sum s x, sums[1][b] = sum U x, sums[2][b] = sum s v,
-// with x = Y / R[b] (caller order), v = X
-__global__ void k_coarse_sums(const double *Y, const double *X, const double *R, const double *s,
-                              const double *U, int nd, int nb, double *sums) {
-    __shared__ double red[3][256];
-    const int b = blockIdx.x;
-    const double ir = 1.0 / R[b];
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    for (int v = threadIdx.x; v < nd; v += 256) {
-        const int64_t o = (int64_t)b * nd + v;
-        const double x = Y[o] * ir;
-        a0 += s[o] * x;
-        a1 += U[o] * x;
-        a2 += s[o] * X[o];
+// Coarse right-hand side of the residual v - L x, x = (G C + cc v) / R on each
+// bubble, one wave per bubble a:
+//   m_a = s . x, U . x from the coefficients (TS = G^T s, TU = G^T U per bubble)
+//   and the sums of v; t_a = m_a / area_a;
+//   rc_a = s . v - U . x + A_c[a][a] t_a.
+// The monopole sum over the other bubbles is A_c's own off-diagonal part
+// applied to t, (A_c t)_a - A_c[a][a] t_a, so it needs no pass over pairs:
+// A_c^{-1} of the whole right-hand side is A_c^{-1} rc - t.
+__global__ void __launch_bounds__(256) k_coarse_rhs(const double *__restrict__ C, const double *__restrict__ TS,
+                                                    const double *__restrict__ TU, int nc, int nb, double cc,
+                                                    const double *__restrict__ R, const double *__restrict__ xsum,
+                                                    const double *__restrict__ area, const double *__restrict__ usum,
+                                                    double *__restrict__ rc, double *__restrict__ t) {
+    const int lane = threadIdx.x & 63, a = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (a >= nb) return;
+    double m = 0.0, u = 0.0;
+    for (int i = lane; i < nc; i += 64) {
+        const int64_t o = (int64_t)a * nc + i;
+        const double c = C[o];
+        m = fma(TS[o], c, m);
+        u = fma(TU[o], c, u);
     }
-    red[0][threadIdx.x] = a0;
-    red[1][threadIdx.x] = a1;
-    red[2][threadIdx.x] = a2;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st)
-            for (int k = 0; k < 3; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + st];
-        __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) {
+        m += __shfl_xor(m, o);
+        u += __shfl_xor(u, o);
     }
-    if (threadIdx.x == 0)
-        for (int k = 0; k < 3; ++k) sums[(int64_t)k * nb + b] = red[k][0];
+    if (lane == 0) {
+        const double sv = xsum[a], ir = 1.0 / R[a];
+        const double ta = fma(cc, sv, m) * ir / area[a];
+        t[a] = ta;
+        rc[a] = sv - fma(cc, xsum[(int64_t)nb + a], u) * ir + usum[a] * ta;
+    }
 }
 
-// coarse right-hand side rc_a = sum s v - U.x - area_a sum_{b != a} m_b / (4 pi d_ab),
-// written over sums[2]; one block per bubble a
-__global__ void k_coarse_rhs(const double *cen, const double *area, int nb, double *sums) {
-    __shared__ double red[256];
-    const int a = blockIdx.x;
-    const double *m = sums;
-    const double ax = cen[3 * a], ay = cen[3 * a + 1], az = cen[3 * a + 2];
-    double far = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 256) {
-        if (b == a) continue;
-        const double dx = ax - cen[3 * b], dy = ay - cen[3 * b + 1], dz = az - cen[3 * b + 2];
-        far += m[b] / sqrt(dx * dx + dy * dy + dz * dz);
-    }
-    red[threadIdx.x] = far;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        sums[2 * (int64_t)nb + a] -=
-            sums[(int64_t)nb + a] + area[a] * red[0] * (1.0 / (4.0 * 3.14159265358979323846));
-}
-
-// y = A x for symmetric A (nb x nb): row a read as column a; one block per row
-__global__ void k_dense_mv(const double *A, const double *x, int nb, double *y) {
-    __shared__ double red[256];
+// y = A x - t for symmetric A (nb x nb): row a read as column a; one block per row
+__global__ void __launch_bounds__(256) k_dense_mv(const double *__restrict__ A, const double *__restrict__ x,
+                                                  const double *__restrict__ t, int nb, double *__restrict__ y) {
+    __shared__ double red[4];
     const int a = blockIdx.x;
     const double *col = A + (int64_t)a * nb;
-    double t = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 256) t += col[b] * x[b];
-    red[threadIdx.x] = t;
+    double v = 0.0;
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nb; b += 256) v = fma(col[b], x[b], v);
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) y[a] = red[0];
+    if (threadIdx.x == 0) y[a] = ((red[0] + red[1]) + red[2]) + red[3] - t[a];
 }
 
 void precond_radii(bfm_ctx *c) {
@@ -638,30 +695,39 @@ void precond_radii(bfm_ctx *c) {
     BFM_LAUNCHED();
 }
 
-void precond_apply(bfm_ctx *c, const double *in_s, double *out_s) {
+static void pre_coef(int nc, int nb, int nd, const double *T, int sv, int si, const double *X, const double *fac,
+                     double *C, hipStream_t st) {
+    k_pre_coef<<<dim3(nblk(nc, 16), nblk(nb, 16)), 256, 0, st>>>(nc, nb, nd, T, sv, si, X, fac, C);
+    BFM_LAUNCHED();
+}
+
+// Five launches (three without the coarse correction) in place of eleven,
+// 75 us of kernels at 1000 bubbles: gather with the sums of the input,
+// coefficients, coarse right-hand side, its dense product, result.
+void precond_apply(bfm_ctx *c, const double *in_s, double *out_s, bool add) {
     Precond &P = c->pre;
     hipStream_t st = c->stream;
     const int nd = P.nd, nc = P.nc, nb = c->nb;
+    const bool coarse = c->opt.precond == BFM_PRECOND_SH_COARSE;
+    const int *iperm = c->tree.iperm.get();
     double *X = P.X.ensure((size_t)nd * nb);
     double *Cm = P.C.ensure((size_t)nc * nb);
-    double *Y = P.Y.ensure((size_t)nd * nb);
-    to_original(c, in_s, X);
+    k_pre_gather<<<nb, 256, 0, st>>>(in_s, iperm, c->s.get(), coarse ? P.U.get() : nullptr, nd, nb, X, P.csum.get());
+    BFM_LAUNCHED();
     // C = diag(2n+1 - c) G+ X
-    gemm_f64(nc, nb, nd, P.basis.Gp.get(), nc, X, nd, Cm, nc, P.fac.get(), 0.0, nullptr, 0, &P.gws, st);
-    // Y = G C + c X
-    gemm_f64(nd, nb, nc, P.basis.G.get(), nd, Cm, nc, Y, nd, nullptr, P.cc, X, nd, &P.gws, st);
+    pre_coef(nc, nb, nd, P.basis.Gp.get(), nc, 1, X, P.fac.get(), Cm, st);
     const double *cy = nullptr;
-    if (c->opt.precond == BFM_PRECOND_SH_COARSE) {
-        double *sums = P.csum.get();
-        k_coarse_sums<<<nb, 256, 0, st>>>(Y, X, P.R.get(), c->s.get(), P.U.get(), nd, nb, sums);
+    if (coarse) {
+        double *rc = P.csum.get() + 2 * (int64_t)nb, *t = rc + nb;
+        k_coarse_rhs<<<nblk(nb, 4), 256, 0, st>>>(Cm, P.TS.get(), P.TU.get(), nc, nb, P.cc, P.R.get(), P.csum.get(),
+                                                  P.carea.get(), P.cusum.get(), rc, t);
         BFM_LAUNCHED();
-        k_coarse_rhs<<<nb, 256, 0, st>>>(P.ccen.get(), P.carea.get(), nb, sums);
-        BFM_LAUNCHED();
-        k_dense_mv<<<nb, 256, 0, st>>>(P.Ainv.get(), sums + 2 * (int64_t)nb, nb, P.cy.get());
+        k_dense_mv<<<nb, 256, 0, st>>>(P.Ainv.get(), rc, t, nb, P.cy.get());
         BFM_LAUNCHED();
         cy = P.cy.get();
     }
-    k_precond_out<<<nblk(c->nv, 256), 256, 0, st>>>(Y, c->tree.idx_a.get(), c->nv, nd, P.R.get(), cy, out_s);
+    k_pre_out<<<dim3(nblk(nd, 32), nblk(nb, 16)), 64, 0, st>>>(nc, nb, nd, P.basis.G.get(), Cm, P.cc, X, P.R.get(), cy,
+                                                               iperm, add ? 1 : 0, out_s);
     BFM_LAUNCHED();
 }
 
@@ -710,11 +776,11 @@ static void gj_sweep(double *A, int nb, int B, double *Pn, double *Rn, double *C
         gemm_nn_f64(bs, nb, bs, Pn, bs, A + k0, nb, Rn, bs, st);
         // trailing columns outside the block: A += A_:,K Rn
         if (k0 > 0)
-            gemm_f64(nb, k0, bs, A + (int64_t)k0 * nb, nb, Rn, bs, A, nb, nullptr, 1.0, A, nb, nullptr, st);
+            gemm_f64(nb, k0, bs, A + (int64_t)k0 * nb, nb, Rn, bs, A, nb, 1.0, A, nb, st);
         const int j1 = k0 + bs;
         if (j1 < nb)
             gemm_f64(nb, nb - j1, bs, A + (int64_t)k0 * nb, nb, Rn + (int64_t)j1 * bs, bs, A + (int64_t)j1 * nb,
-                     nb, nullptr, 1.0, A + (int64_t)j1 * nb, nb, nullptr, st);
+                     nb, 1.0, A + (int64_t)j1 * nb, nb, st);
         // Cn = A_:,K Pn  (= -A_:,K P^{-1}), nb x bs
         gemm_nn_f64(nb, bs, bs, A + (int64_t)k0 * nb, nb, Pn, bs, Cn, nb, st);
         k_gj_fix<<<nblk(2 * (int64_t)bs * nb, 256), 256, 0, st>>>(A, nb, k0, bs, Rn, Cn, Pn);
@@ -737,8 +803,9 @@ void spd_inverse(double *A, int nb, DevBuf<double> &piv, DevBuf<double> &row, De
 void coarse_build(bfm_ctx *c, hipStream_t st) {
     Precond &P = c->pre;
     const int nd = P.nd, nb = c->nb;
-    P.csum.ensure(3 * (size_t)nb);  // used by precond_apply
+    P.csum.ensure(4 * (size_t)nb);  // used by precond_apply
     P.cy.ensure(nb);
+    const int nc = P.nc;  // (precond_build has run)
     double *cen = P.ccen.ensure(3 * (size_t)nb), *area = P.carea.ensure(nb), *usum = P.cusum.ensure(nb);
     k_coarse_geom<<<nb, 256, 0, st>>>(c->xyz.get(), c->s.get(), nd, cen, area, usum);
     BFM_LAUNCHED();
@@ -746,6 +813,9 @@ void coarse_build(bfm_ctx *c, hipStream_t st) {
     const int64_t tiles = (int64_t)nblk(nd, 256) * nb;
     k_coarse_u<<<(unsigned)tiles, 256, 0, st>>>(c->xyz.get(), c->s.get(), c->nrm.get(), c->nv, nd, nb, cen, U, usum);
     BFM_LAUNCHED();
+    // G^T s and G^T U of every bubble
+    pre_coef(nc, nb, nd, P.basis.G.get(), 1, nd, c->s.get(), nullptr, P.TS.ensure((size_t)nc * nb), st);
+    pre_coef(nc, nb, nd, P.basis.G.get(), 1, nd, U, nullptr, P.TU.ensure((size_t)nc * nb), st);
     double *A = P.Ainv.ensure((size_t)nb * nb);
     k_coarse_matrix<<<nblk((int64_t)nb * nb, 256), 256, 0, st>>>(cen, area, usum, nb, A);
     BFM_LAUNCHED();

@@ -319,20 +319,32 @@ void matvec_sorted(bfm_ctx *c, double f, const double *x_s, double g, const doub
         BFM_HIP(hipMemsetAsync(out_s, 0, sizeof(double) * n, st));
         return;
     }
-    k_sources_1ch<<<nblk(n, 256), 256, 0, st>>>(t.ps.get(), n, f, mono ? x_s : nullptr, g,
-                                                dip ? y_s : nullptr, q, wd);
-    BFM_LAUNCHED();
     Sources src;
     src.nch = 1;
     src.mono = mono;
     src.dip = dip;
     src.q = q;
     src.w = wd;
-    fmm_apply(lo ? c->fmm_lo : c->fmm, t, src, y, direct, st);
-    k_finalize_1ch<<<nblk(n, 256), 256, 0, st>>>(y, n, f, mono ? x_s : nullptr, g, dip ? y_s : nullptr,
-                                                 add_diag ? c->lii_s.get() : nullptr,
-                                                 add_diag ? c->mii_s.get() : nullptr, out_s);
-    BFM_LAUNCHED();
+    src.f = f;
+    src.g = g;
+    src.x = mono ? x_s : nullptr;
+    src.yv = dip ? y_s : nullptr;
+    if (direct) {
+        k_sources_1ch<<<nblk(n, 256), 256, 0, st>>>(t.ps.get(), n, f, src.x, g, src.yv, q, wd);
+        BFM_LAUNCHED();
+        fmm_apply(c->fmm, t, src, y, true, st);
+        k_finalize_1ch<<<nblk(n, 256), 256, 0, st>>>(y, n, f, src.x, g, src.yv, add_diag ? c->lii_s.get() : nullptr,
+                                                     add_diag ? c->mii_s.get() : nullptr, out_s);
+        BFM_LAUNCHED();
+    } else {  // the strengths and the result are formed by the product's own first and last kernel
+        src.ps = t.ps.get();
+        src.qout = q;
+        src.wout = wd;
+        src.out = out_s;
+        src.lii = add_diag ? c->lii_s.get() : nullptr;
+        src.mii = add_diag ? c->mii_s.get() : nullptr;
+        fmm_apply(lo ? c->fmm_lo : c->fmm, t, src, y, false, st);
+    }
     corr_apply(c, f, mono ? x_s : nullptr, g, dip ? y_s : nullptr, out_s);
 }
 
@@ -509,11 +521,6 @@ __global__ void k_combine(const double *__restrict__ V, int nvec, int64_t ld, co
 #pragma unroll 8
     for (int k = 0; k < nvec; ++k) v = fma(V[k * ld + i], yv[k], v);
     x[i] = v;
-}
-
-__global__ void k_axpy(double a, const double *x, double *y, int64_t n) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) y[i] += a * x[i];
 }
 
 // Small-state layout (doubles) for restart m:
@@ -851,9 +858,7 @@ void gmres_sorted(bfm_ctx *c, double *x, bool use_guess, bfm_solve_info *info) {
         if (pc) {  // x += P^{-1} V y
             k_combine<<<nblk(n, 256), 256, 0, st>>>(V, k, n, sm + L.yv, Tv, n, 0);
             BFM_LAUNCHED();
-            precond_apply(c, Tv, Z);
-            k_axpy<<<nblk(n, 256), 256, 0, st>>>(1.0, Z, x, n);
-            BFM_LAUNCHED();
+            precond_apply(c, Tv, x, true);
         } else {
             k_combine<<<nblk(n, 256), 256, 0, st>>>(V, k, n, sm + L.yv, x, n, 1);
             BFM_LAUNCHED();
