@@ -557,7 +557,7 @@ __device__ inline void givens_column(double *sm, const SmallLayout &L, int j, do
             rot[2 * i + 1] = sn[i];
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (threadIdx.x == 0) {
         double top = col[0];

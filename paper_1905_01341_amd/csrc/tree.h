@@ -12,7 +12,7 @@ namespace bfm {
 
 constexpr int kKeyBits = 15;  // bits per axis of the point keys (levels 0..15)
 constexpr int kP2PChunk = 128;   // receivers per near-field work item (two per lane)
-constexpr int kLeafChunk = 128;  // points per leaf work item of P2M and L2P
+constexpr int kLeafChunk = 256;  // points per leaf work item of P2M and L2P (four per lane)
 constexpr int kP2PPiece = 384;   // near-field sources per work item at most (a leaf's source
                                  // list longer than this is split into balanced pieces)
 // symmetric near field (one channel of monopoles): receivers per chunk (up
