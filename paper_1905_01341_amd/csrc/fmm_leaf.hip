@@ -115,7 +115,15 @@ __device__ inline R swap_add(R a, R b) {
 // same recurrence by forward differentiation:
 //   D Rt_m^m = f_m [D Rt_{m-1}^{m-1} (x+iy) + Rt_{m-1}^{m-1} (n_x+i n_y)]
 //   D Rt_n^m = ae (n_z Rt_{n-1} + z D Rt_{n-1}) - ab (2 v.n Rt_{n-2} + r^2 D Rt_{n-2})
+//
+// In FP32 the buffered columns are the lanes' own values, sixteen columns at a
+// time, and four lanes add up each in a fixed order over groups of 128 points
+// that does not depend on how the work is split: the order of an FP32 sum
+// decides the bits that the split-BF16 translations round next, and a solve's
+// answer at its tolerance moves with them.
 constexpr int kP2MRows = 16;
+template <class R>
+constexpr int kP2MBuf = sizeof(R) == 4 ? 16 * 68 : kP2MRows * 64;  // values a wave; rows of 68: distinct banks
 template <int P_, int NCH, bool MONO, bool DIP, class R, int NW, int PPL>
 __device__ __forceinline__ void p2m_points(int j0, int re, double cx, double cy, double cz, double ih,
                                            const double *__restrict__ px, const double *__restrict__ py,
@@ -157,26 +165,35 @@ __device__ __forceinline__ void p2m_points(int j0, int re, double cx, double cy,
     unsigned desc = 0;
     // buffered columns -> the leaf's expansion; the wave's LDS rows are its own,
     // and a wave's LDS operations complete in order
+    constexpr bool RAW = sizeof(R) == 4;
     auto flush = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        const unsigned dd = (unsigned)__shfl((int)desc, lane >> 2);
-        if (lane < 4 * row) {
-            const R *col = buf + (lane >> 2) * 64 + (lane & 3) * 16;
-            R s0 = 0, s1 = 0;
+        const int cl = RAW ? lane >> 2 : lane;  // column of this lane
+        const unsigned dd = (unsigned)__shfl((int)desc, cl >> 2);
+        R s0 = 0, s1 = 0;
+        if (cl < 4 * row) {
+            const R *col = RAW ? buf + cl * 68 + (lane & 3) : buf + (cl >> 2) * 64 + (cl & 3) * 16;
 #pragma unroll
-            for (int t = 0; t < 16; t += 2) {  // rotated starts: distinct banks
-                s0 += col[(t + lane) & 15];
-                s1 += col[(t + 1 + lane) & 15];
+            for (int t = 0; t < 16; t += 2) {  // reduced rows: rotated starts, distinct banks
+                s0 += col[RAW ? 4 * t : (t + lane) & 15];
+                s1 += col[RAW ? 4 * (t + 1) : (t + 1 + lane) & 15];
             }
-            // 16-lane groups hold a, c, b, d
-            const int isb = (lane >> 1) & 1, isc = lane & 1;
+        }
+        R sum = s0 + s1;
+        if constexpr (RAW) {
+            sum += __shfl_xor(sum, 1);
+            sum += __shfl_xor(sum, 2);
+        }
+        if (cl < 4 * row && (!RAW || (lane & 3) == 0)) {
+            // reduced rows: the 16-lane groups hold a, c, b, d
+            const int isb = RAW ? cl & 1 : (cl >> 1) & 1, isc = RAW ? (cl >> 1) & 1 : cl & 1;
             if ((dd >> (28 + isb + 2 * isc)) & 1) {
                 R *o = mbox + (dd & 0xfff) + (isb ? (dd >> 12) & 0x7f : 0) + (isc ? (dd >> 19) & 0x1ff : 0);
                 if (alone)
-                    *o += s0 + s1;
+                    *o += sum;
                 else
-                    unsafeAtomicAdd(o, s0 + s1);
+                    unsafeAtomicAdd(o, sum);
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -186,10 +203,18 @@ __device__ __forceinline__ void p2m_points(int j0, int re, double cx, double cy,
     static_assert(NCH * PP <= 4096 && 2 * P_ < 128 && PP < 512, "place description");
     // columns a..d at places p, p + sb, p + sc, p + sb + sc (mask: which exist)
     auto push4 = [&](R a, R b, R c, R dd, int place, int sb, int sc, unsigned mask) {
-        buf[row * 64 + lane] = swap_add<false>(swap_add<true>(a, b), swap_add<true>(c, dd));
+        if constexpr (RAW) {
+            R *o = buf + 4 * row * 68 + lane;
+            o[0] = a;
+            o[68] = b;
+            o[2 * 68] = c;
+            o[3 * 68] = dd;
+        } else {
+            buf[row * 64 + lane] = swap_add<false>(swap_add<true>(a, b), swap_add<true>(c, dd));
+        }
         const unsigned d = (unsigned)place | ((unsigned)sb << 12) | ((unsigned)sc << 19) | (mask << 28);
         desc = lane == row ? d : desc;
-        if (++row == kP2MRows) flush();
+        if (++row == (RAW ? 4 : kP2MRows)) flush();
     };
     // a channel's sum over this lane's points (a term is left out where the
     // channel has no monopole, or no dipole)
@@ -198,8 +223,8 @@ __device__ __forceinline__ void p2m_points(int j0, int re, double cx, double cy,
         R t = 0;
 #pragma unroll
         for (int u = 0; u < PPL; ++u) {
-            if (hq) t += sq[u][c] * v[u];
-            if (DIP) t += sw[u][c] * dv[u];
+            const R a = hq && DIP ? sq[u][c] * v[u] + sw[u][c] * dv[u] : hq ? sq[u][c] * v[u] : sw[u][c] * dv[u];
+            t = u ? t + a : a;
         }
         return t;
     };
@@ -303,7 +328,7 @@ __global__ void __launch_bounds__(64 * SP * NW, NCH == 5 ? 3 : 1) k_p2m(const in
                                                          const double *__restrict__ q, const double *__restrict__ w,
                                                          R *__restrict__ mexp) {
     constexpr int NT = P_ * (P_ + 1) / 2;
-    __shared__ R buf[SP * NW][kP2MRows * 64];
+    __shared__ R buf[SP * NW][kP2MBuf<R>];
     __shared__ Pair2<R> rec[NT];
     __shared__ R sect[P_];
     const int wave = threadIdx.x >> 6;
@@ -541,8 +566,10 @@ __global__ void __launch_bounds__(64 * SP * NW) k_l2p(const int2 *__restrict__ i
 // L2P five channels, order 20: 494 items 47 / 50, 2600 items 134 / 119, 4400
 // items 225 / 185; one channel, order 16: 900 items 20 / 22, 2600 items 44 / 38.
 // P2M five channels, order 20: 494 items 113 / 128, 2600 items 274 / 276, 4400
-// items 468 / 409; FP32, order 8: 494 items 9.5 / 11.4, 4400 items 25 / 22. The
-// FP64 P2M of monopoles alone stays with split orders (4400 items 75 / 82).
+// items 468 / 409; FP32, order 8: 494 items 10.7 / 13.3, 4400 items 29.4 / 23.8.
+// The FP64 P2M of monopoles alone stays with split orders (4400 items 75 / 82).
+// The FP32 L2P splits points at every size (order 8, 494 items 9.0, 10.1 with
+// 128 points a wave).
 constexpr int64_t kLeafItemsMany = 1536;
 
 template <int P_, int NCH, bool MONO, bool DIP, class R>
@@ -550,9 +577,10 @@ void launch_p2m(const Tree &t, const Sources &src, R *M, hipStream_t st) {
     if (t.n_leaf_items <= 0) return;
     const int64_t leaf0 = t.lvl_off[t.lmax];
     const double hleaf = t.side / (double)(1 << t.lmax);
+    constexpr int S = sizeof(R) == 4 ? 2 : 1;  // FP32: groups of 128 points in either split
     const bool points = t.n_leaf_items >= kLeafItemsMany && (DIP || sizeof(R) == 4);
-    auto kern = points ? k_p2m<P_, NCH, MONO, DIP, R, 2, 1> : k_p2m<P_, NCH, MONO, DIP, R, 1, 4>;
-    kern<<<(unsigned)t.n_leaf_items, points ? 128 : 256, 0, st>>>(
+    auto kern = points ? k_p2m<P_, NCH, MONO, DIP, R, 2, 1> : k_p2m<P_, NCH, MONO, DIP, R, S, 4>;
+    kern<<<(unsigned)t.n_leaf_items, points ? 128 : 256 * S, 0, st>>>(
         t.leaf_items.get(), leaf0, t.leaf_pt.get(), t.box_centre.get(), hleaf, t.px.get(), t.py.get(), t.pz.get(),
         t.pnx.get(), t.pny.get(), t.pnz.get(), t.n, src.q, src.w, M);
     BFM_LAUNCHED();
@@ -565,9 +593,10 @@ void launch_l2p(const Tree &t, const Sources &src, const R *L, double *y, hipStr
     const double hleaf = t.side / (double)(1 << t.lmax);
     const L2PFinal fin{src.f, src.g, src.x, src.yv, src.lii, src.mii, src.out};
     const bool points = t.n_leaf_items >= kLeafItemsMany;
-    auto kern = points ? k_l2p<P_, NCH, R, false, 4, 1> : k_l2p<P_, NCH, R, false, 1, 4>;
+    constexpr int S = sizeof(R) == 4 ? 4 : 1, W = 4 / S;  // FP32: one wave adds up a point's orders
+    auto kern = points ? k_l2p<P_, NCH, R, false, 4, 1> : k_l2p<P_, NCH, R, false, S, W>;
     if constexpr (NCH == 1)
-        if (src.out) kern = points ? k_l2p<P_, NCH, R, true, 4, 1> : k_l2p<P_, NCH, R, true, 1, 4>;
+        if (src.out) kern = points ? k_l2p<P_, NCH, R, true, 4, 1> : k_l2p<P_, NCH, R, true, S, W>;
     kern<<<(unsigned)t.n_leaf_items, 256, 0, st>>>(t.leaf_items.get(), leaf0, t.leaf_pt.get(),
                                                                t.box_centre.get(), hleaf, t.px.get(), t.py.get(),
                                                                t.pz.get(), t.n, L, y, fin);
