@@ -808,6 +808,29 @@ static void prepare(const Tree &t, const Sources &src, R *M, size_t ncoef, doubl
     BFM_LAUNCHED();
 }
 
+// The near field (writes y) goes to the near-field stream, beside the rest of
+// the far-field chain; the L2P adds into y after both. Where the fork lies:
+// the P2M needs the whole chip and a pair sum beside it costs both more than
+// it hides, while the M2M, M2L and L2L below it leave units idle. In FP64 the
+// near field therefore starts after the P2M (100 bubbles, plain method: 25.1 ms
+// a solve, 27.0 with the fork before the P2M and 26.0 after the M2M; 10
+// bubbles 9.2 / 10.0 / 9.2); in FP32, where it is half as long, after the M2M
+// (200 tori 17.4 ms, 19.4 before the P2M, 18.3 after it; 500 spheres 6.4,
+// 6.5, 6.5). With dipoles the pair sums outlast everything beside them and
+// start first (400 bubbles, both operators: 0.73 ms, 0.75 after the P2M; the
+// diagonal pass of 256,200 vertices 2.93, 2.98). Two events a product cost ~12 us, which a short pair sum does
+// not give back: one bubble of 642 vertices (94 k pairs) 3.18 ms on one
+// stream, 3.55 on two; 3 bubbles (1.2 M pairs) 6.33 on one, 6.05 on two.
+// Kernel timing runs the two one after the other, so that each kernel's
+// events measure it alone.
+static constexpr int64_t kForkPairs = 500000;
+static hipStream_t near_fork(FmmWork &w, const Tree &t, hipStream_t st) {
+    if (!w.near || (w.prof && w.prof->on) || t.npairs_near < kForkPairs) return st;
+    BFM_HIP(hipEventRecord(w.ev_fork, st));
+    BFM_HIP(hipStreamWaitEvent(w.near, w.ev_fork, 0));
+    return w.near;
+}
+
 template <int P_, int NCH, bool MONO, bool DIP>
 static void run_fmm(FmmWork &w, const Tree &tc, const Sources &src, double *y, hipStream_t st) {
     Tree &t = const_cast<Tree &>(tc);
@@ -823,25 +846,23 @@ static void run_fmm(FmmWork &w, const Tree &tc, const Sources &src, double *y, h
         k_zero<double><<<1024, 256, 0, st>>>(L, (int64_t)ncoef);
         BFM_LAUNCHED();
     }
-    // near field (writes y) on the near-field stream when there is one,
-    // beside the far-field chain; the L2P adds into y after it
-    // (kernel timing runs them one after the other, so that each kernel's
-    // events measure it alone)
-    hipStream_t ns = (w.near && !(w.prof && w.prof->on)) ? w.near : st;
-    if (ns != st) {
-        BFM_HIP(hipEventRecord(w.ev_fork, st));
-        BFM_HIP(hipStreamWaitEvent(ns, w.ev_fork, 0));
-    }
-    int pi = prof_begin(w, KC_P2P, ns);
-    if (NCH == 5 && src.packed)
-        launch_p2p_packed(t, src.packed, y, ns);
-    else
-        launch_p2p<NCH, MONO, DIP>(t, src, y, ns);
-    prof_end(w, pi, ns, (double)(t.npairs_near - t.n) * p2p_flops_per_pair(NCH, MONO, DIP));
-    if (ns != st) BFM_HIP(hipEventRecord(w.ev_join, ns));
-    pi = prof_begin(w, KC_P2M, st);
+    auto near = [&] {
+        hipStream_t s = near_fork(w, t, st);
+        const int pi = prof_begin(w, KC_P2P, s);
+        if (NCH == 5 && src.packed)
+            launch_p2p_packed(t, src.packed, y, s);
+        else
+            launch_p2p<NCH, MONO, DIP>(t, src, y, s);
+        prof_end(w, pi, s, (double)(t.npairs_near - t.n) * p2p_flops_per_pair(NCH, MONO, DIP));
+        if (s != st) BFM_HIP(hipEventRecord(w.ev_join, s));
+        return s;
+    };
+    hipStream_t ns = st;
+    if (DIP) ns = near();
+    int pi = prof_begin(w, KC_P2M, st);
     launch_p2m<P_, NCH, MONO, DIP>(t, src, M, st);
     prof_end(w, pi, st, 0.0);
+    if (!DIP) ns = near();
     for (int l = lmax; l >= 3; --l)
         translate64<P_>(w, KC_M2M_L2L, *t.m2m[l], NCH, false, M, M, st);
     translate64<P_>(w, KC_M2L, t.m2l, NCH, false, M, L, st);
@@ -868,27 +889,25 @@ static void run_fmm_lo(FmmWork &w, const Tree &tc, const Sources &src, double *y
         k_zero<float><<<1024, 256, 0, st>>>(L, (int64_t)ncoef);
         BFM_LAUNCHED();
     }
-    hipStream_t ns = (w.near && !(w.prof && w.prof->on)) ? w.near : st;
-    if (ns != st) {
-        BFM_HIP(hipEventRecord(w.ev_fork, st));
-        BFM_HIP(hipStreamWaitEvent(ns, w.ev_fork, 0));
+    int pi = prof_begin(w, KC_P2M, st);
+    launch_p2m<P_, 1, MONO, DIP, float>(t, src, M, st);
+    prof_end(w, pi, st, 0.0);
+    for (int l = lmax; l >= 3; --l) {
+        if (w.prec == BFM_PREC_FP32)
+            translate<P_, float>(w, KC_M2M_L2L, *t.m2m[l], 1, false, w.opf_m2m.get(), M, M, st);
+        else
+            translate_bf3<P_>(w, KC_M2M_L2L, *t.m2m[l], false, w.opb_m2m[0].get(), w.opb_m2m[1].get(), M, M, st);
     }
-    int pi = prof_begin(w, KC_P2P, ns);
+    hipStream_t ns = near_fork(w, t, st);
+    pi = prof_begin(w, KC_P2P, ns);
     launch_p2p32<MONO, DIP>(t, src, y, ns);
     prof_end(w, pi, ns, (double)(t.npairs_near - t.n) * p2p_flops_per_pair(1, MONO, DIP));
     if (ns != st) BFM_HIP(hipEventRecord(w.ev_join, ns));
-    pi = prof_begin(w, KC_P2M, st);
-    launch_p2m<P_, 1, MONO, DIP, float>(t, src, M, st);
-    prof_end(w, pi, st, 0.0);
     if (w.prec == BFM_PREC_FP32) {
-        for (int l = lmax; l >= 3; --l)
-            translate<P_, float>(w, KC_M2M_L2L, *t.m2m[l], 1, false, w.opf_m2m.get(), M, M, st);
         translate<P_, float>(w, KC_M2L, t.m2l, 1, false, w.opf_m2l.get(), M, L, st);
         for (int l = 3; l <= lmax; ++l)
             translate<P_, float>(w, KC_M2M_L2L, *t.m2m[l], 1, true, w.opf_l2l.get(), L, L, st);
     } else {
-        for (int l = lmax; l >= 3; --l)
-            translate_bf3<P_>(w, KC_M2M_L2L, *t.m2m[l], false, w.opb_m2m[0].get(), w.opb_m2m[1].get(), M, M, st);
         translate_bf3<P_>(w, KC_M2L, t.m2l, false, w.opb_m2l[0].get(), w.opb_m2l[1].get(), M, L, st);
         for (int l = 3; l <= lmax; ++l)
             translate_bf3<P_>(w, KC_M2M_L2L, *t.m2m[l], true, w.opb_l2l[0].get(), w.opb_l2l[1].get(), L, L, st);

@@ -223,8 +223,8 @@ __device__ __forceinline__ void p2m_points(int j0, int re, double cx, double cy,
         R t = 0;
 #pragma unroll
         for (int u = 0; u < PPL; ++u) {
-            const R a = hq && DIP ? sq[u][c] * v[u] + sw[u][c] * dv[u] : hq ? sq[u][c] * v[u] : sw[u][c] * dv[u];
-            t = u ? t + a : a;
+            if (hq) t += sq[u][c] * v[u];
+            if (DIP) t += sw[u][c] * dv[u];
         }
         return t;
     };
