@@ -35,7 +35,7 @@ struct Precond {
     DevBuf<double> U;                  // own-bubble column sums of s^T L, caller order [nv]
     DevBuf<double> ccen, carea;        // area-weighted centroids [nb][3], areas [nb]
     DevBuf<double> cusum;              // bubble sums of U [nb] (the coarse matrix's diagonal)
-    DevBuf<double> Ainv, gj_row, gj_col, gj_piv;  // inverse coarse matrix [nb x nb] and Gauss-Jordan work
+    DevBuf<double> Ainv, sweep_p, sweep_v, sweep_w;  // inverse coarse matrix [nb x nb] and the sweep's work
     DevBuf<double> csum, cy;           // per-bubble sums of the input [2][nb], coarse right-hand side and
                                        // monopole strengths [2][nb]; coarse correction [nb]
 };
@@ -187,15 +187,13 @@ void coarse_launch(bfm_ctx *c);
 void coarse_join(bfm_ctx *c);
 // stop the handle's coarse-build thread (after the build it queued)
 void coarse_worker_free(bfm_ctx *c);
-// in-place inverse of an SPD n x n column-major device matrix (blocked Gauss-Jordan)
+// in-place inverse of an SPD n x n column-major device matrix (blocked symmetric
+// sweep; the lower triangle is read)
 void spd_inverse(double *A, int n, DevBuf<double> &piv, DevBuf<double> &row, DevBuf<double> &col,
                  hipStream_t st);
 // C = A B, column-major FP64 (precond.hip)
 void gemm_nn_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc,
                  hipStream_t st);
-// C = A B + beta D (D may be null; C may alias D)
-void gemm_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc, double beta,
-              const double *D, int ldd, hipStream_t st);
 
 // the solve of bfm_solve_dev: tree, diagonals and b, optional guess, GMRES
 // (guess: BFM_GUESS_*); throws BFM_ENOCONV when GMRES stops at gmres_maxit

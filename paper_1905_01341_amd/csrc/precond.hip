@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cmath>
 #include <complex>
+#include <type_traits>
 #include <vector>
 
 #include <condition_variable>
@@ -217,12 +218,11 @@ __global__ void k_bubble_radius(const double *s, int nd, double *R) {
     if (threadIdx.x == 0) R[b] = sqrt(red[0] / (4.0 * 3.14159265358979323846));
 }
 
-// C = A B + beta D, column-major FP64 on MFMA
+// C = A B, column-major FP64 on MFMA
 // (v_mfma_f64_16x16x4f64). A workgroup of 4 waves owns a 64 x 64 tile of C
 // (each wave a 32 x 32 quarter, 2 x 2 MFMA blocks); K advances in chunks of
 // 32 staged through LDS, the next chunk's elements loaded into registers
-// while the current one is multiplied. D may be null. C may alias D (each
-// element is read and written by the same lane) but not A or B.
+// while the current one is multiplied. C aliases neither A nor B.
 // MFMA operand layout: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]
 // of a 16 x 4 by 4 x 16 product; element r of the result holds row
 // l / 16 + 4 r, column l % 16.
@@ -231,8 +231,7 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 constexpr int kGemmKC = 32;  // K chunk
 
 __global__ void __launch_bounds__(256) k_gemm_nn(int M, int N, int K, const double *A, int lda,
-                                                 const double *B, int ldb, double *C, int ldc, double beta,
-                                                 const double *D, int ldd) {
+                                                 const double *B, int ldb, double *C, int ldc) {
     // A and B chunks ([k][row], [k][col]); after the products the same LDS
     // holds the 64 x 64 result tile ([col][row]) for coalesced stores
     __shared__ double sbuf[2 * kGemmKC * (64 + 1)];
@@ -301,25 +300,15 @@ __global__ void __launch_bounds__(256) k_gemm_nn(int M, int N, int K, const doub
 #pragma unroll 4
     for (int cc = wave; cc < 64; cc += 4) {
         const int gj = j0 + cc;
-        if (gi < M && gj < N) {
-            double val = Cs[cc][lane];
-            if (D) val += beta * D[(int64_t)gj * ldd + gi];
-            C[(int64_t)gj * ldc + gi] = val;
-        }
+        if (gi < M && gj < N) C[(int64_t)gj * ldc + gi] = Cs[cc][lane];
     }
 }
 
-void gemm_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc, double beta,
-              const double *D, int ldd, hipStream_t st) {
-    if (M <= 0 || N <= 0) return;
-    k_gemm_nn<<<dim3((M + 63) / 64, (N + 63) / 64), 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, beta, D, ldd);
-    BFM_LAUNCHED();
-}
-
-// C = A B, all column-major (the plain product of k_gemm_nn)
 void gemm_nn_f64(int M, int N, int K, const double *A, int lda, const double *B, int ldb, double *C, int ldc,
                  hipStream_t st) {
-    gemm_f64(M, N, K, A, lda, B, ldb, C, ldc, 0.0, nullptr, 0, st);
+    if (M <= 0 || N <= 0) return;
+    k_gemm_nn<<<dim3((M + 63) / 64, (N + 63) / 64), 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc);
+    BFM_LAUNCHED();
 }
 
 // X[b][v] = in_s at vertex v of bubble b (caller order), with the bubble's sums
@@ -573,70 +562,263 @@ __global__ void k_coarse_matrix(const double *cen, const double *area, const dou
     A[e] = area[a] * area[b] / (4.0 * 3.14159265358979323846 * sqrt(dx * dx + dy * dy + dz * dz));
 }
 
-// Gauss-Jordan inverse (no pivoting: the coarse matrix is symmetric positive
-// definite) of the bs x bs diagonal block at (k0, k0) of A (column-major,
-// leading dimension n); writes -inverse to P (column-major bs x bs).
-// Thread t owns column t % 64 and rows 16 (t / 64) .. +15 in registers; each
-// step publishes the pivot row and column through LDS.
-constexpr int kGjBlock = 64;
-constexpr int kGjThreads = 1024;
-constexpr int kGjRows = kGjBlock * kGjBlock / kGjThreads;  // rows per thread
-__global__ void __launch_bounds__(kGjThreads) k_gj_block(const double *A, int n, int k0, int bs, double *P) {
-    // The block lives in LDS, twice: step k reads buffer k % 2 and writes the
-    // other, so one barrier per step suffices. Thread (j, i0) updates column
-    // j, rows i0..i0+3: sixteen waves share the step, which is bound by the
-    // latency of its reads and writes rather than by their number.
-    __shared__ double a[2][kGjBlock][kGjBlock + 1];  // [buffer][row][column]
-    const int tid = threadIdx.x;
-    const int j = tid % kGjBlock, i0 = kGjRows * (tid / kGjBlock);
-    for (int e = tid; e < kGjBlock * kGjBlock; e += kGjThreads) {
-        const int i = e % kGjBlock, c = e / kGjBlock;
-        // identity outside the bs x bs block keeps the padded steps inert
-        a[0][i][c] = (i < bs && c < bs) ? A[(int64_t)(k0 + c) * n + k0 + i] : (i == c ? 1.0 : 0.0);
-    }
-    __syncthreads();
-    for (int k = 0; k < kGjBlock; ++k) {
-        const double(*src)[kGjBlock + 1] = a[k & 1];
-        double(*dst)[kGjBlock + 1] = a[(k & 1) ^ 1];
+// Inverse of a symmetric positive definite matrix by the symmetric sweep
+// operator in blocks of 128 pivots (no pivoting needed). Sweeping block K maps
+//   A_KK -> -P, P = A_KK^{-1};  A_iK -> W_i = A_iK P;  A_ij -> A_ij - W_i A_jK^T
+// for every i, j outside K, and all blocks swept give -A^{-1}. The matrix stays
+// symmetric throughout, so only its lower triangle (column-major, row >= column)
+// is kept and updated: n^3 flops, half of a Gauss-Jordan sweep's, and half its
+// traffic. Three launches a block: the pivot block (one workgroup: a serial
+// chain of 128 pivots), the panel, the rest of the triangle. Alone, n = 1000:
+// 0.76 ms, 8 x (67 + 17 + 10) us, bound by the pivot chain; n = 5000: 6.5 ms,
+// 40 x (66 + 19 + 76), the update at 41 Tflop/s. In the solve of 5000 bubbles,
+// where it runs beside the octree and the diagonal pass, 55.3 -> 46.0 ms against
+// a Gauss-Jordan sweep over the whole matrix in blocks of 64 and 256.
+constexpr int kSweep = 128;      // pivots a block
+constexpr int kSweepTile = 64;   // tile of the update
+static_assert(kSweep == 2 * kSweepTile, "a pivot block is two tiles");
+
+// P (kSweep x kSweep, identity outside bs x bs) = inverse of the diagonal block
+// at (k0, k0); the block itself becomes -P. One pivot a step: its row, which by
+// symmetry is also its column, goes through LDS (two buffers, one barrier a
+// step), and every thread updates its 8 x 8 elements in registers: rows
+// 32 q + 2 ty + e and columns 32 q + 2 tx + e, so that the reads of a wave
+// touch each bank once.
+__global__ void __launch_bounds__(256) k_sweep_pivot(double *__restrict__ A, int n, int k0, int bs,
+                                                     double *__restrict__ P) {
+    __shared__ __align__(16) double row[2][kSweep];
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    double a[8][8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int i = 32 * (r >> 1) + 2 * ty + (r & 1), j = 32 * (c >> 1) + 2 * tx + (c & 1);
+            const int hi = max(i, j), lo = min(i, j);
+            a[r][c] = hi < bs ? A[(int64_t)(k0 + lo) * n + k0 + hi] : (i == j ? 1.0 : 0.0);
+        }
+    // one pivot: row 2 t + e of quarter q, in register row R = 2 q + e
+    auto pivot = [&](auto RC, int t) {
+        constexpr int R = decltype(RC)::value;
+        double *buf = row[R & 1];
+        if (ty == t) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<double2 *>(buf + 32 * q + 2 * tx) = make_double2(a[R][2 * q], a[R][2 * q + 1]);
+        }
+        __syncthreads();
         // 1 / pivot: hardware reciprocal and two Newton steps
-        const double piv = src[k][k];
+        const double piv = buf[32 * (R >> 1) + 2 * t + (R & 1)];
         double p = __builtin_amdgcn_rcp(piv);
         p = fma(p, fma(-piv, p, 1.0), p);
         p = fma(p, fma(-piv, p, 1.0), p);
-        const double rk = (j == k) ? p : src[k][j] * p;  // new row k, column j
+        double ci[8], cj[8];
 #pragma unroll
-        for (int r = 0; r < kGjRows; ++r) {
-            const int i = i0 + r;
-            const double f = src[i][k], old = src[i][j];
-            const double upd = (j == k) ? -f * p : old - f * rk;
-            dst[i][j] = (i == k) ? rk : upd;
+        for (int q = 0; q < 4; ++q) {
+            const double2 u = *reinterpret_cast<const double2 *>(buf + 32 * q + 2 * ty);
+            const double2 v = *reinterpret_cast<const double2 *>(buf + 32 * q + 2 * tx);
+            ci[2 * q] = u.x;
+            ci[2 * q + 1] = u.y;
+            cj[2 * q] = v.x * p;
+            cj[2 * q + 1] = v.y * p;
         }
-        __syncthreads();
+        const bool mine = ty == t, col = tx == t;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                a[r][c] = fma(-ci[r], cj[c], a[r][c]);
+                if (r == R) a[r][c] = mine ? cj[c] : a[r][c];
+                if (c == R) a[r][c] = col ? (r == R && mine ? -p : ci[r] * p) : a[r][c];
+            }
+    };
+    auto quarter = [&](auto QC) {
+        constexpr int Q = decltype(QC)::value;
+#pragma unroll 1
+        for (int t = 0; t < 16 && 32 * Q + 2 * t < bs; ++t) {  // identity pivots beyond bs change nothing
+            pivot(std::integral_constant<int, 2 * Q>{}, t);
+            pivot(std::integral_constant<int, 2 * Q + 1>{}, t);
+        }
+    };
+    quarter(std::integral_constant<int, 0>{});
+    quarter(std::integral_constant<int, 1>{});
+    quarter(std::integral_constant<int, 2>{});
+    quarter(std::integral_constant<int, 3>{});
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int i = 32 * (r >> 1) + 2 * ty + (r & 1), j = 32 * (c >> 1) + 2 * tx + (c & 1);
+            P[j * kSweep + i] = -a[r][c];
+            if (i >= j && i < bs) A[(int64_t)(k0 + j) * n + k0 + i] = a[r][c];
+        }
+}
+
+// Panel: V_i = A_iK (kept for the update), W_i = V_i P, which replaces A_iK; 32
+// rows a workgroup, wave w the columns 32 w .. of W. V and W are column-major
+// n x kSweep (columns beyond bs zero). Rows above the block are held transposed,
+// as A_Ki.
+constexpr int kPanelRows = 32;
+__global__ void __launch_bounds__(256) k_sweep_panel(double *__restrict__ A, int n, int k0, int bs,
+                                                     const double *__restrict__ P, double *__restrict__ V,
+                                                     double *__restrict__ W) {
+    __shared__ double Vs[kSweep][kPanelRows + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // the grid counts the rows outside the block; k0 is a multiple of the tile
+    int i0 = blockIdx.x * kPanelRows;
+    const bool below = i0 >= k0;
+    if (below) i0 += bs;
+    const int rows = below ? min(kPanelRows, n - i0) : kPanelRows;
+#pragma unroll 4
+    for (int u = 0; u < kSweep * kPanelRows / 256; ++u) {
+        const int e = tid + 256 * u;
+        const int i = below ? e % kPanelRows : e / kSweep, k = below ? e / kPanelRows : e % kSweep;
+        const int ic = min(i, rows - 1), kc = min(k, bs - 1);
+        const double v = below ? A[(int64_t)(k0 + kc) * n + i0 + ic] : A[(int64_t)(i0 + ic) * n + k0 + kc];
+        Vs[k][i] = k < bs ? v : 0.0;
     }
-    for (int e = tid; e < kGjBlock * kGjBlock; e += kGjThreads) {
-        const int i = e % kGjBlock, c = e / kGjBlock;
-        if (i < bs && c < bs) P[(int64_t)c * bs + i] = -a[kGjBlock & 1][i][c];
+    __syncthreads();
+#pragma unroll 4
+    for (int u = 0; u < kSweep * kPanelRows / 256; ++u) {
+        const int e = tid + 256 * u, i = e % kPanelRows, k = e / kPanelRows;
+        if (i < rows) V[(int64_t)k * n + i0 + i] = Vs[k][i];
+    }
+    // 32 x 32 of W^T a wave: result rows are columns of W, its columns rows
+    dbl4 acc[2][2];
+    for (int a = 0; a < 2; ++a)
+        for (int b = 0; b < 2; ++b) acc[a][b] = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int k4 = 0; k4 < kSweep / 4; ++k4) {
+        const int k = 4 * k4 + lane / 16;
+        double pf[2], vf[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) pf[a] = P[k * kSweep + 32 * wave + 16 * a + lane % 16];  // P is symmetric
+#pragma unroll
+        for (int b = 0; b < 2; ++b) vf[b] = Vs[k][16 * b + lane % 16];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(pf[a], vf[b], acc[a][b], 0, 0, 0);
+    }
+    __syncthreads();  // V has been read
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Vs[32 * wave + 16 * a + lane / 16 + 4 * r][16 * b + lane % 16] = acc[a][b][r];
+    __syncthreads();
+#pragma unroll 4
+    for (int u = 0; u < kSweep * kPanelRows / 256; ++u) {
+        const int e = tid + 256 * u, i = e % kPanelRows, k = e / kPanelRows;
+        if (i >= rows) continue;
+        W[(int64_t)k * n + i0 + i] = Vs[k][i];
+        if (below && k < bs) A[(int64_t)(k0 + k) * n + i0 + i] = Vs[k][i];
+    }
+    if (!below) {
+#pragma unroll 4
+        for (int u = 0; u < kSweep * kPanelRows / 256; ++u) {
+            const int e = tid + 256 * u, i = e / kSweep, k = e % kSweep;
+            if (k < bs) A[(int64_t)(i0 + i) * n + k0 + k] = Vs[k][i];
+        }
     }
 }
 
-// row block k0..k0+bs of A := -Rn (Rn = -P^{-1} A_K,:) outside the block
-// columns; column block := Cn (= -A_:,K P^{-1}) outside the block rows, and
-// the diagonal block := P^{-1} = -Pn.
-__global__ void k_gj_fix(double *A, int n, int k0, int bs, const double *Rn, const double *Cn, const double *Pn) {
-    int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t nrow = (int64_t)bs * n;
-    if (e < nrow) {  // row block, all columns j (block columns get -Pn below)
-        const int r = (int)(e % bs), j = (int)(e / bs);
-        if (j < k0 || j >= k0 + bs) A[(int64_t)j * n + k0 + r] = -Rn[(int64_t)j * bs + r];
-        return;
+// Update of the lower triangle's tiles outside block K: A_ij -= W_i V_j^T, K =
+// 128 in four chunks of 32 through LDS, the next chunk's loads in flight during
+// the products. A wave owns a 32 x 32 quarter and computes its transpose, whose
+// result lanes run down the columns of A, so the tile is read into the
+// accumulators and stored from them in 128-byte pieces. The stash's odd rows
+// are held with their halves of 32 columns' 16s exchanged: both rows that a
+// half-wave reads fall on different banks.
+__global__ void __launch_bounds__(256, 4) k_sweep_update(double *__restrict__ A, int n, int k0, int bs,
+                                                         const double *__restrict__ V, const double *__restrict__ W) {
+    constexpr int KC = 32, T = kSweepTile;
+    __shared__ double Ws[KC][T], Vs[KC][T];
+    int ti = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);  // tile row: ti (ti + 1) / 2 <= block
+    while ((int64_t)(ti + 1) * (ti + 2) / 2 <= (int64_t)blockIdx.x) ++ti;
+    while ((int64_t)ti * (ti + 1) / 2 > (int64_t)blockIdx.x) --ti;
+    const int tj = (int)((int64_t)blockIdx.x - (int64_t)ti * (ti + 1) / 2);
+    const int i0 = T * ti, j0 = T * tj;
+    if ((i0 >= k0 && i0 < k0 + bs) || (j0 >= k0 && j0 < k0 + bs)) return;  // the panel's
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
+    // rows of W and V that this lane loads (the last row again beyond n)
+    const int ri = min(i0 + lane, n - 1), rj = min(j0 + lane, n - 1);
+    double rw[KC / 4], rv[KC / 4];
+    auto load = [&](int c) {
+#pragma unroll
+        for (int u = 0; u < KC / 4; ++u) {
+            const int64_t k = (int64_t)(KC * c + wave + 4 * u) * n;
+            rw[u] = W[k + ri];
+            rv[u] = V[k + rj];
+        }
+    };
+    load(0);
+    dbl4 acc[2][2];  // [column block][row block]
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = min(i0 + wi + 16 * b + lane % 16, n - 1), j = min(j0 + wj + 16 * a + lane / 16 + 4 * r, n - 1);
+                acc[a][b][r] = A[(int64_t)j * n + i];
+            }
+#pragma unroll 1
+    for (int c = 0; c < kSweep / KC; ++c) {
+#pragma unroll
+        for (int u = 0; u < KC / 4; ++u) {
+            const int k = wave + 4 * u, x = lane ^ (16 * (k & 1));
+            Ws[k][x] = -rw[u];
+            Vs[k][x] = rv[u];
+        }
+        __syncthreads();
+        if (c + 1 < kSweep / KC) load(c + 1);
+#pragma unroll
+        for (int k4 = 0; k4 < KC / 4; ++k4) {
+            const int k = 4 * k4 + lane / 16, sw = 16 * (k & 1);
+            double vf[2], wf[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) vf[a] = Vs[k][(wj + 16 * a + lane % 16) ^ sw];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) wf[b] = Ws[k][(wi + 16 * b + lane % 16) ^ sw];
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(vf[a], wf[b], acc[a][b], 0, 0, 0);
+        }
+        __syncthreads();
     }
-    e -= nrow;
-    if (e >= nrow) return;
-    const int i = (int)(e % n), c = (int)(e / n);  // column block, all rows i
-    if (i < k0 || i >= k0 + bs)
-        A[(int64_t)(k0 + c) * n + i] = Cn[(int64_t)c * n + i];
-    else
-        A[(int64_t)(k0 + c) * n + i] = -Pn[(int64_t)c * bs + (i - k0)];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = i0 + wi + 16 * b + lane % 16, j = j0 + wj + 16 * a + lane / 16 + 4 * r;
+                if (i < n && j < n) A[(int64_t)j * n + i] = acc[a][b][r];
+            }
+}
+
+// A := -A on the lower triangle, mirrored to the upper one.
+__global__ void __launch_bounds__(256) k_sweep_mirror(double *__restrict__ A, int n) {
+    constexpr int T = 32;
+    if (blockIdx.x < blockIdx.y) return;
+    __shared__ double t[T][T + 1];
+    const int i0 = T * blockIdx.x, j0 = T * blockIdx.y, x = threadIdx.x & 31;
+    for (int y = threadIdx.x >> 5; y < T; y += 8) {
+        const int i = i0 + x, j = j0 + y;
+        if (i < n && j < n) t[y][x] = -A[(int64_t)j * n + i];
+    }
+    __syncthreads();
+    for (int y = threadIdx.x >> 5; y < T; y += 8) {
+        const int i = i0 + x, j = j0 + y;
+        if (i < n && j < n && i >= j) A[(int64_t)j * n + i] = t[y][x];
+        const int i2 = j0 + x, j2 = i0 + y;  // the transposed place
+        if (i2 < n && j2 < n && i2 < j2) A[(int64_t)j2 * n + i2] = t[x][y];
+    }
 }
 
 // Coarse right-hand side of the residual v - L x, x = (G C + cc v) / R on each
@@ -731,73 +913,25 @@ void precond_apply(bfm_ctx *c, const double *in_s, double *out_s, bool add) {
     BFM_LAUNCHED();
 }
 
-// S = the bs x bs diagonal block at (k0, k0) of A (leading dimension n), packed
-__global__ void k_gj_copy_block(const double *A, int n, int k0, int bs, double *S) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= (int64_t)bs * bs) return;
-    const int i = (int)(e % bs), c = (int)(e / bs);
-    S[e] = A[(int64_t)(k0 + c) * n + k0 + i];
-}
-
-__global__ void k_gj_negate(const double *S, int64_t m, double *P) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e < m) P[e] = -S[e];
-}
-
-// Column blocks of the sweep: 64 (each diagonal block inverted in LDS by
-// k_gj_block), or 256 on large matrices, whose diagonal blocks are inverted
-// by a 64-block sweep over a packed copy. A rank-256 trailing update reads
-// and writes the matrix once for 256 columns instead of 64, and the sweep
-// is bound by that traffic (with 64-column blocks, 79 passes over a 200 MB
-// matrix at 5000 bubbles).
-constexpr int kGjOuter = 256;
-constexpr int kGjOuterMin = 2048;  // matrix size from which the sweep takes 256-column blocks
-
-// One blocked Gauss-Jordan sweep with B-column blocks (B = 64 or 256):
-// per diagonal block K, P = A_KK^{-1}; A_Kj <- P A_Kj, A_ij <- A_ij - A_iK P A_Kj,
-// A_iK <- -A_iK P, A_KK <- P (j, i outside K). Work: Pn (B x B), Rn (B x n),
-// Cn (n x B); for B = 256 also `inner` (B^2 + 64^2 + 2 * 64 B doubles).
-static void gj_sweep(double *A, int nb, int B, double *Pn, double *Rn, double *Cn, double *inner, hipStream_t st) {
-    for (int k0 = 0; k0 < nb; k0 += B) {
-        const int bs = std::min(B, nb - k0);
-        if (B == kGjBlock) {
-            k_gj_block<<<1, kGjThreads, 0, st>>>(A, nb, k0, bs, Pn);
-            BFM_LAUNCHED();
-        } else {
-            double *S = inner, *w = inner + (size_t)B * B;
-            k_gj_copy_block<<<nblk((int64_t)bs * bs, 256), 256, 0, st>>>(A, nb, k0, bs, S);
-            BFM_LAUNCHED();
-            gj_sweep(S, bs, kGjBlock, w, w + kGjBlock * kGjBlock, w + kGjBlock * kGjBlock + (size_t)kGjBlock * B,
-                     nullptr, st);  // S = A_KK^{-1}
-            k_gj_negate<<<nblk((int64_t)bs * bs, 256), 256, 0, st>>>(S, (int64_t)bs * bs, Pn);
-            BFM_LAUNCHED();
-        }
-        // Rn = Pn A_K,:  (= -P^{-1} A_K,:), bs x nb
-        gemm_nn_f64(bs, nb, bs, Pn, bs, A + k0, nb, Rn, bs, st);
-        // trailing columns outside the block: A += A_:,K Rn
-        if (k0 > 0)
-            gemm_f64(nb, k0, bs, A + (int64_t)k0 * nb, nb, Rn, bs, A, nb, 1.0, A, nb, st);
-        const int j1 = k0 + bs;
-        if (j1 < nb)
-            gemm_f64(nb, nb - j1, bs, A + (int64_t)k0 * nb, nb, Rn + (int64_t)j1 * bs, bs, A + (int64_t)j1 * nb,
-                     nb, 1.0, A + (int64_t)j1 * nb, nb, st);
-        // Cn = A_:,K Pn  (= -A_:,K P^{-1}), nb x bs
-        gemm_nn_f64(nb, bs, bs, A + (int64_t)k0 * nb, nb, Pn, bs, Cn, nb, st);
-        k_gj_fix<<<nblk(2 * (int64_t)bs * nb, 256), 256, 0, st>>>(A, nb, k0, bs, Rn, Cn, Pn);
+// In-place inverse of a symmetric positive definite n x n matrix (column-major;
+// its lower triangle is read) by the blocked symmetric sweep.
+void spd_inverse(double *A, int n, DevBuf<double> &piv, DevBuf<double> &row, DevBuf<double> &col, hipStream_t st) {
+    double *P = piv.ensure((size_t)kSweep * kSweep);
+    double *V = row.ensure((size_t)kSweep * n), *W = col.ensure((size_t)kSweep * n);
+    const int64_t tiles = nblk(n, kSweepTile);
+    for (int k0 = 0; k0 < n; k0 += kSweep) {
+        const int bs = std::min(kSweep, n - k0);
+        k_sweep_pivot<<<1, 256, 0, st>>>(A, n, k0, bs, P);
+        BFM_LAUNCHED();
+        if (bs == n) break;
+        k_sweep_panel<<<nblk(n - bs, kPanelRows), 256, 0, st>>>(A, n, k0, bs, P, V, W);
+        BFM_LAUNCHED();
+        k_sweep_update<<<(unsigned)(tiles * (tiles + 1) / 2), 256, 0, st>>>(A, n, k0, bs, V, W);
         BFM_LAUNCHED();
     }
-}
-
-// In-place inverse of a symmetric positive definite n x n matrix
-// (column-major) by blocked Gauss-Jordan elimination without pivoting.
-void spd_inverse(double *A, int nb, DevBuf<double> &piv, DevBuf<double> &row, DevBuf<double> &col,
-                 hipStream_t st) {
-    const int B = nb >= kGjOuterMin ? kGjOuter : kGjBlock;
-    const size_t inner = B == kGjBlock ? 0 : (size_t)B * B + kGjBlock * kGjBlock + 2 * (size_t)kGjBlock * B;
-    double *Pn = piv.ensure((size_t)B * B + inner);
-    double *Rn = row.ensure((size_t)B * nb);
-    double *Cn = col.ensure((size_t)nb * B);
-    gj_sweep(A, nb, B, Pn, Rn, Cn, inner ? Pn + (size_t)B * B : nullptr, st);
+    const unsigned m = (unsigned)nblk(n, 32);
+    k_sweep_mirror<<<dim3(m, m), 256, 0, st>>>(A, n);
+    BFM_LAUNCHED();
 }
 
 void coarse_build(bfm_ctx *c, hipStream_t st) {
@@ -819,7 +953,7 @@ void coarse_build(bfm_ctx *c, hipStream_t st) {
     double *A = P.Ainv.ensure((size_t)nb * nb);
     k_coarse_matrix<<<nblk((int64_t)nb * nb, 256), 256, 0, st>>>(cen, area, usum, nb, A);
     BFM_LAUNCHED();
-    spd_inverse(A, nb, P.gj_piv, P.gj_row, P.gj_col, st);
+    spd_inverse(A, nb, P.sweep_p, P.sweep_v, P.sweep_w, st);
 }
 
 static void coarse_worker_wait(CoarseWorker *w);
