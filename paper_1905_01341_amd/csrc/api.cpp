@@ -466,19 +466,18 @@ int bfm_diagonals(bfm_ctx *c, const double *phi, double *Mii, double *Lii, doubl
         DeviceScope ds(c->device);
         const int64_t n = c->nv;
         BFM_CHECK(n > 0, BFM_EINVAL, "no mesh set");
-        DevBuf<double> dphi, tmp;
-        dphi.ensure(n);
-        tmp.ensure(n);
-        BFM_HIP(hipMemcpyAsync(dphi.get(), phi, sizeof(double) * n, hipMemcpyHostToDevice, c->stream));
-        diagonal_pass(c, dphi.get());
+        double *io = c->io.ensure((size_t)4 * n);  // phi and the three results
+        BFM_HIP(hipMemcpyAsync(io, phi, sizeof(double) * n, hipMemcpyHostToDevice, c->stream));
+        diagonal_pass(c, io);
         double *outs[3] = {Mii, Lii, b};
         const double *srcs[3] = {c->mii_s.get(), c->lii_s.get(), c->b_s.get()};
-        for (int k = 0; k < 3; ++k) {
-            if (!outs[k]) continue;
-            to_original(c, srcs[k], tmp.get());
-            BFM_HIP(hipMemcpyAsync(outs[k], tmp.get(), sizeof(double) * n, hipMemcpyDeviceToHost, c->stream));
-            BFM_HIP(hipStreamSynchronize(c->stream));
-        }
+        for (int k = 0; k < 3; ++k)
+            if (outs[k]) to_original(c, srcs[k], io + (k + 1) * n);
+        for (int k = 0; k < 3; ++k)
+            if (outs[k])
+                BFM_HIP(hipMemcpyAsync(outs[k], io + (k + 1) * n, sizeof(double) * n, hipMemcpyDeviceToHost,
+                                       c->stream));
+        BFM_HIP(hipStreamSynchronize(c->stream));
     });
 }
 
@@ -492,23 +491,21 @@ int bfm_matvec(bfm_ctx *c, double f, const double *x, double g, const double *y,
         const int64_t n = c->nv;
         BFM_CHECK(n > 0, BFM_EINVAL, "no mesh set");
         ensure_tree(c);
-        DevBuf<double> dx, dy, ds_, dout;
         hipStream_t st = c->stream;
+        // [x or the product, y or the result, sorted x, sorted y]
+        double *io = c->io.ensure((size_t)4 * n);
         double *xs = nullptr, *ys = nullptr;
         if (f != 0.0) {
-            dx.ensure(n);
-            xs = ds_.ensure(2 * n);
-            BFM_HIP(hipMemcpyAsync(dx.get(), x, sizeof(double) * n, hipMemcpyHostToDevice, st));
-            to_sorted(c, dx.get(), xs);
+            xs = io + 2 * n;
+            BFM_HIP(hipMemcpyAsync(io, x, sizeof(double) * n, hipMemcpyHostToDevice, st));
+            to_sorted(c, io, xs);
         }
         if (g != 0.0) {
-            dy.ensure(n);
-            if (!ds_.get()) ds_.ensure(2 * n);
-            ys = ds_.get() + n;
-            BFM_HIP(hipMemcpyAsync(dy.get(), y, sizeof(double) * n, hipMemcpyHostToDevice, st));
-            to_sorted(c, dy.get(), ys);
+            ys = io + 3 * n;
+            BFM_HIP(hipMemcpyAsync(io + n, y, sizeof(double) * n, hipMemcpyHostToDevice, st));
+            to_sorted(c, io + n, ys);
         }
-        double *os = dout.ensure(2 * n);
+        double *os = io;
         matvec_sorted(c, f, xs, g, ys, os, add_diag != 0, precision, direct != 0);
         to_original(c, os, os + n);
         BFM_HIP(hipMemcpyAsync(out, os + n, sizeof(double) * n, hipMemcpyDeviceToHost, st));
@@ -533,20 +530,19 @@ int bfm_solve(bfm_ctx *c, const double *phi, double *q, int use_guess, bfm_solve
         BFM_CHECK(c->nv > 0, BFM_EINVAL, "no mesh set");
         DeviceScope ds(c->device);
         const int64_t n = c->nv;
-        DevBuf<double> buf;
-        buf.ensure(2 * n);
+        double *buf = c->io.ensure((size_t)2 * n);
         hipStream_t st = c->stream;
-        BFM_HIP(hipMemcpyAsync(buf.get(), phi, sizeof(double) * n, hipMemcpyHostToDevice, st));
+        BFM_HIP(hipMemcpyAsync(buf, phi, sizeof(double) * n, hipMemcpyHostToDevice, st));
         if (use_guess == BFM_GUESS_GIVEN)
-            BFM_HIP(hipMemcpyAsync(buf.get() + n, q, sizeof(double) * n, hipMemcpyHostToDevice, st));
+            BFM_HIP(hipMemcpyAsync(buf + n, q, sizeof(double) * n, hipMemcpyHostToDevice, st));
         try {
-            solve_impl(c, buf.get(), buf.get() + n, use_guess, info);
+            solve_impl(c, buf, buf + n, use_guess, info);
         } catch (const Error &e) {
             if (e.code != BFM_ENOCONV) throw;
             g_last_error = e.msg;
             rc_solve = e.code;
         }
-        BFM_HIP(hipMemcpyAsync(q, buf.get() + n, sizeof(double) * n, hipMemcpyDeviceToHost, st));
+        BFM_HIP(hipMemcpyAsync(q, buf + n, sizeof(double) * n, hipMemcpyDeviceToHost, st));
         BFM_HIP(hipStreamSynchronize(st));
     });
     return rc != BFM_OK ? rc : rc_solve;

@@ -458,12 +458,11 @@ void step_state_set(bfm_ctx *c, const double *xyz_h, const double *phi_h, double
     hipStream_t st = c->stream;
     const int nd = c->pre.nd, nb = c->nb;
     const int64_t nv = c->nv;
-    DevBuf<double> tmp;
-    tmp.ensure(4 * (size_t)nv);
-    BFM_HIP(hipMemcpyAsync(tmp.get(), xyz_h, sizeof(double) * 3 * nv, hipMemcpyHostToDevice, st));
-    BFM_HIP(hipMemcpyAsync(tmp.get() + 3 * nv, phi_h, sizeof(double) * nv, hipMemcpyHostToDevice, st));
+    double *tmp = c->io.ensure(4 * (size_t)nv);
+    BFM_HIP(hipMemcpyAsync(tmp, xyz_h, sizeof(double) * 3 * nv, hipMemcpyHostToDevice, st));
+    BFM_HIP(hipMemcpyAsync(tmp + 3 * nv, phi_h, sizeof(double) * nv, hipMemcpyHostToDevice, st));
     double *Sv = S.S.ensure(4 * (size_t)nv);
-    k_pack<<<nblk(nv, 256), 256, 0, st>>>(tmp.get(), tmp.get() + 3 * nv, nd, nv, Sv);
+    k_pack<<<nblk(nv, 256), 256, 0, st>>>(tmp, tmp + 3 * nv, nd, nv, Sv);
     BFM_LAUNCHED();
     // gas: volumes of the filtered initial shape
     set_surface(c, S, Sv);
@@ -483,14 +482,13 @@ void step_state_get(bfm_ctx *c, double *xyz_h, double *phi_h, double *t) {
     Stepper &S = stepper(c);
     BFM_CHECK(S.state_set, BFM_EINVAL, "no state set (bfm_state_set)");
     const int64_t nv = c->nv;
-    DevBuf<double> tmp;
-    tmp.ensure(4 * (size_t)nv);
-    k_unpack<<<nblk(nv, 256), 256, 0, c->stream>>>(S.S.get(), c->pre.nd, nv, tmp.get(), tmp.get() + 3 * nv);
+    double *tmp = c->io.ensure(4 * (size_t)nv);
+    k_unpack<<<nblk(nv, 256), 256, 0, c->stream>>>(S.S.get(), c->pre.nd, nv, tmp, tmp + 3 * nv);
     BFM_LAUNCHED();
     if (xyz_h)
-        BFM_HIP(hipMemcpyAsync(xyz_h, tmp.get(), sizeof(double) * 3 * nv, hipMemcpyDeviceToHost, c->stream));
+        BFM_HIP(hipMemcpyAsync(xyz_h, tmp, sizeof(double) * 3 * nv, hipMemcpyDeviceToHost, c->stream));
     if (phi_h)
-        BFM_HIP(hipMemcpyAsync(phi_h, tmp.get() + 3 * nv, sizeof(double) * nv, hipMemcpyDeviceToHost, c->stream));
+        BFM_HIP(hipMemcpyAsync(phi_h, tmp + 3 * nv, sizeof(double) * nv, hipMemcpyDeviceToHost, c->stream));
     BFM_HIP(hipStreamSynchronize(c->stream));
     if (t) *t = S.t;
 }
