@@ -849,7 +849,7 @@ static void run_fmm(FmmWork &w, const Tree &tc, const Sources &src, double *y, h
     auto near = [&] {
         hipStream_t s = near_fork(w, t, st);
         const int pi = prof_begin(w, KC_P2P, s);
-        if (NCH == 5 && src.packed)
+        if constexpr (NCH == 5)
             launch_p2p_packed(t, src.packed, y, s);
         else
             launch_p2p<NCH, MONO, DIP>(t, src, y, s);

@@ -99,92 +99,127 @@ __device__ inline void p2p_range(int j0, int j1, const double *__restrict__ px,
     }
 }
 
-// Receivers rc + lane + 64 k (k < R) of the leaf whose points are [l0, r1)
-// against sources s0..s1-1 of the leaf's source list (its near ranges in
-// order). ATOMIC: several items share these receivers, so the sums are added
-// into the (cleared) output; otherwise they are stored.
-template <int NCH, bool MONO, bool DIP, int R, bool ATOMIC>
-__device__ inline void p2p_pass(int rc, int l0, int r1, int s0, int s1, int nr, const int2 *__restrict__ rng,
-                                const double *__restrict__ px, const double *__restrict__ py,
-                                const double *__restrict__ pz, const double *__restrict__ pnx,
-                                const double *__restrict__ pny, const double *__restrict__ pnz,
-                                int64_t n, const double *__restrict__ q, const double *__restrict__ w,
-                                double *__restrict__ y) {
+// One tile of 64 sources (records in LDS, read at wave-uniform addresses)
+// against R receivers per lane. SELF: the tile holds points of the receivers'
+// own leaf, where a pair may coincide (excluded).
+template <bool MONO, int R, bool SELF>
+__device__ inline void p2p_dip_tile(const double2 (*rec)[kP2PThreads], int cnt, const double *xi, const double *yi,
+                                    const double *zi, double *acc) {
+#pragma unroll 2
+    for (int t = 0; t < cnt; ++t) {
+        const double2 xy = rec[0][t], zq = rec[1][t], nxy = rec[2][t], nzw = rec[3][t];
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const double dx = xi[k] - xy.x, dy = yi[k] - xy.y, dz = zi[k] - zq.x;
+            const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+            double inv = rsqrt_m2_f64(r2);
+            if (SELF) inv = r2 > 0.0 ? inv : 0.0;
+            if (MONO) acc[k] = fma(zq.y, inv, acc[k]);
+            const double nd = fma(nxy.x, dx, fma(nxy.y, dy, nzw.x * dz));
+            acc[k] = fma(nzw.y * nd, inv * inv * inv, acc[k]);
+        }
+    }
+}
+
+// Receivers rc + lane + 64 k (k < R) of a leaf [l0, l1) against sources
+// s0..s1-1 of its source list (its near ranges in order). ATOMIC: several items
+// share these receivers, so the sums are added into the (cleared) output;
+// otherwise they are stored.
+template <bool MONO, int R, bool ATOMIC>
+__device__ inline void p2p_dip_item(int rc, int l0, int l1, int s0, int s1, int nr, const int2 *__restrict__ rng,
+                                    const double *__restrict__ px, const double *__restrict__ py,
+                                    const double *__restrict__ pz, const double *__restrict__ pnx,
+                                    const double *__restrict__ pny, const double *__restrict__ pnz,
+                                    const double *__restrict__ q, const double *__restrict__ w,
+                                    double *__restrict__ y, double2 (*rec)[kP2PThreads]) {
     const int lane = threadIdx.x;
-    double xi[R], yi[R], zi[R], acc[R][NCH];
+    double xi[R], yi[R], zi[R], acc[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int i = rc + lane + k * kP2PThreads;
-        const bool ok = i < r1;
+        const bool ok = i < l1;
         // idle lanes sit far away: their sums are never stored
         xi[k] = ok ? px[i] : 1e100;
         yi[k] = ok ? py[i] : 0.0;
         zi[k] = ok ? pz[i] : 0.0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) acc[k][c] = 0.0;
+        acc[k] = 0.0;
     }
-    // walk the ranges, keeping the part that falls in [s0, s1); only the
-    // leaf's own points [l0, r1) can coincide with a receiver, so that part
-    // runs with the test and the rest without
-    int cum = 0;
-    for (int g = 0; g < nr && cum < s1; ++g) {
-        const int2 r = rng[g];
-        const int len = r.y - r.x;
-        const int a = r.x + max(0, s0 - cum), b = r.x + min(len, s1 - cum);
-        cum += len;
-        if (a >= b) continue;
-        if (a < r1 && l0 < b) {
-            const int m0 = max(a, l0), m1 = min(b, r1);
-            p2p_range<NCH, MONO, DIP, R, false>(a, m0, px, py, pz, pnx, pny, pnz, n, q, w, xi, yi, zi, acc);
-            p2p_range<NCH, MONO, DIP, R, true>(m0, m1, px, py, pz, pnx, pny, pnz, n, q, w, xi, yi, zi, acc);
-            p2p_range<NCH, MONO, DIP, R, false>(m1, b, px, py, pz, pnx, pny, pnz, n, q, w, xi, yi, zi, acc);
-        } else {
-            p2p_range<NCH, MONO, DIP, R, false>(a, b, px, py, pz, pnx, pny, pnz, n, q, w, xi, yi, zi, acc);
+    for (int base = s0; base < s1; base += kP2PThreads) {
+        // this lane's source: position base + lane of the list
+        const int p = base + lane;
+        int j = -1, cum = 0;
+        for (int g = 0; g < nr; ++g) {
+            const int2 r = rng[g];
+            const int len = r.y - r.x;
+            if (p >= cum && p < cum + len) j = r.x + (p - cum);
+            cum += len;
         }
+        const bool ok = p < s1 && j >= 0;
+        __syncthreads();  // the previous tile has been read
+        if (ok) {
+            rec[0][lane] = make_double2(px[j], py[j]);
+            rec[1][lane] = make_double2(pz[j], MONO ? -0.5 * q[j] : 0.0);
+            rec[2][lane] = make_double2(pnx[j], pny[j]);
+            rec[3][lane] = make_double2(pnz[j], -0.125 * w[j]);
+        }
+        __syncthreads();
+        const int cnt = min(kP2PThreads, s1 - base);
+        if (__any(ok && j >= l0 && j < l1))
+            p2p_dip_tile<MONO, R, true>(rec, cnt, xi, yi, zi, acc);
+        else
+            p2p_dip_tile<MONO, R, false>(rec, cnt, xi, yi, zi, acc);
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int i = rc + lane + k * kP2PThreads;
-        if (i < r1)
-            for (int c = 0; c < NCH; ++c) {
-                if (ATOMIC)
-                    unsafeAtomicAdd(y + (int64_t)c * n + i, acc[k][c]);
-                else
-                    y[(int64_t)c * n + i] = acc[k][c];
-            }
+        if (i < l1) {
+            if (ATOMIC)
+                unsafeAtomicAdd(y + i, acc[k]);
+            else
+                y[i] = acc[k];
+        }
     }
 }
 
-// One wave per near-field work item (a leaf chunk of up to kP2PChunk
-// receivers, two per lane, and a piece of the leaf's source list). A leaf's
-// sources are its merged near-field ranges (the points of up to 27
-// neighbour leaves); lists longer than kP2PPiece are split into balanced
-// pieces, so that no wave carries much more work than the average and there
-// are more waves than slots, which lets the dispatcher balance the tail.
-template <int NCH, bool MONO, bool DIP, bool ATOMIC>
-__global__ void __launch_bounds__(kP2PThreads) k_p2p(const int4 *__restrict__ items,
-                                                     const int *__restrict__ leaf_pt,
-                                                     const int2 *__restrict__ near_rng,
-                                                     const int *__restrict__ near_cnt,
-                                                     const double *__restrict__ px,
-                                                     const double *__restrict__ py,
-                                                     const double *__restrict__ pz,
-                                                     const double *__restrict__ pnx,
-                                                     const double *__restrict__ pny,
-                                                     const double *__restrict__ pnz, int64_t n,
-                                                     const double *__restrict__ q,
-                                                     const double *__restrict__ w, double *__restrict__ y) {
-    constexpr int R = kP2PChunk / kP2PThreads;
-    static_assert(kP2PChunk == R * kP2PThreads, "whole receivers per lane");
+// Near field with dipoles, one channel: one wave per work item (a leaf chunk of
+// up to kP2PChunk receivers, two per lane, one where the chunk has at most 64,
+// and a piece of the leaf's source list). A leaf's sources are its merged
+// near-field ranges (the points of up to 27 neighbour leaves); lists longer than
+// kP2PPiece are split into balanced pieces, so that no wave carries much more
+// work than the average and there are more waves than slots, which lets the
+// dispatcher balance the tail. Bound by FP64 VALU, 16 operations and the 1/sqrt
+// estimate a pair with both layers; the weights take in the powers of -2 of the
+// reciprocal. Each source tile passes through LDS once for the item's receivers: 218
+// M pairs in leaves of 156 points, both layers, 277 us with scalar source loads
+// and two receivers a lane throughout, 249 so.
+template <bool MONO, bool ATOMIC>
+__global__ void __launch_bounds__(kP2PThreads) k_p2p_dip(const int4 *__restrict__ items,
+                                                         const int *__restrict__ leaf_pt,
+                                                         const int2 *__restrict__ near_rng,
+                                                         const int *__restrict__ near_cnt,
+                                                         const double *__restrict__ px, const double *__restrict__ py,
+                                                         const double *__restrict__ pz,
+                                                         const double *__restrict__ pnx,
+                                                         const double *__restrict__ pny,
+                                                         const double *__restrict__ pnz,
+                                                         const double *__restrict__ q, const double *__restrict__ w,
+                                                         double *__restrict__ y) {
+    static_assert(kP2PChunk == 2 * kP2PThreads, "one or two receivers per lane");
+    __shared__ double2 rec[4][kP2PThreads];
     // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs, so XCD
     // x takes a contiguous run of items (neighbouring leaves, which share
     // their sources) and keeps those sources in its own L2
     const int nblock = gridDim.x, per = nblock / kXcdCount, rem = nblock % kXcdCount;
     const int xcd = blockIdx.x % kXcdCount, idx = blockIdx.x / kXcdCount;
     const int4 it = items[xcd * per + (xcd < rem ? xcd : rem) + idx];
-    const int leaf = it.x;
-    p2p_pass<NCH, MONO, DIP, R, ATOMIC>(it.y, leaf_pt[leaf], leaf_pt[leaf + 1], it.z, it.w, near_cnt[leaf],
-                                        near_rng + 27 * (int64_t)leaf, px, py, pz, pnx, pny, pnz, n, q, w, y);
+    const int leaf = it.x, l0 = leaf_pt[leaf], l1 = leaf_pt[leaf + 1];
+    const int2 *rng = near_rng + 27 * (int64_t)leaf;
+    if (l1 - it.y <= kP2PThreads)
+        p2p_dip_item<MONO, 1, ATOMIC>(it.y, l0, l1, it.z, it.w, near_cnt[leaf], rng, px, py, pz, pnx, pny, pnz, q, w,
+                                      y, rec);
+    else
+        p2p_dip_item<MONO, 2, ATOMIC>(it.y, l0, l1, it.z, it.w, near_cnt[leaf], rng, px, py, pz, pnx, pny, pnz, q, w,
+                                      y, rec);
 }
 
 // Near field of the five-channel pass from packed source records (one
@@ -280,7 +315,7 @@ __device__ inline void p2p_diag_item(int leaf, int rc, int s0, int s1, const int
     }
 }
 
-// The five-channel counterpart of k_p2p (same items, pieces and order); a
+// The five-channel counterpart of k_p2p_dip (same items, pieces and order); a
 // chunk of at most 64 receivers runs with one receiver per lane.
 template <bool ATOMIC>
 __global__ void __launch_bounds__(kP2PThreads) k_p2p_diag(const int4 *__restrict__ items,
@@ -606,7 +641,7 @@ __global__ void __launch_bounds__(kP2PThreads) k_p2p_sym32(const int4 *__restric
     }
 }
 
-// One-sided FP32 form (any channel content; k_p2p's items and pieces):
+// One-sided FP32 form (any channel content; k_p2p_dip's items and pieces):
 // receivers rc + lane + 64 k of the leaf against sources s0..s1-1 of its list,
 // read at wave-uniform addresses and shifted to the leaf centre per lane.
 template <bool MONO, bool DIP, bool SELF>
@@ -733,8 +768,9 @@ static unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 template <int NCH, bool MONO, bool DIP>
 void launch_p2p(const Tree &t, const Sources &src, double *y, hipStream_t st) {
     if (t.n_near_items <= 0) return;
-    if constexpr (NCH == 1 && MONO && !DIP) {
-        // one channel of monopoles: each pair once, added to both points
+    static_assert(NCH == 1, "five channels: launch_p2p_packed");
+    if constexpr (MONO && !DIP) {
+        // monopoles: each pair once, added to both points
         BFM_CHECK(t.n_sym_items > 0, BFM_EINVAL, "symmetric near-field items missing");
         k_p2p_sym<<<(unsigned)t.n_sym_items, kP2PThreads, 0, st>>>(t.sym_items.get(), t.leaf_pt.get(),
                                                                    t.near_rng.get(), t.near_cnt.get(), t.px.get(),
@@ -743,14 +779,14 @@ void launch_p2p(const Tree &t, const Sources &src, double *y, hipStream_t st) {
         BFM_LAUNCHED();
         return;
     }
-    auto kern = t.near_split ? k_p2p<NCH, MONO, DIP, true> : k_p2p<NCH, MONO, DIP, false>;
-    kern<<<(unsigned)t.n_near_items, kP2PThreads, 0, st>>>(t.near_items.get(), t.leaf_pt.get(), t.near_rng.get(),
-                                                           t.near_cnt.get(), t.px.get(), t.py.get(), t.pz.get(),
-                                                           t.pnx.get(), t.pny.get(), t.pnz.get(), t.n, src.q, src.w,
-                                                           y);
-    BFM_LAUNCHED();
+    if constexpr (DIP) {
+        auto kern = t.near_split ? k_p2p_dip<MONO, true> : k_p2p_dip<MONO, false>;
+        kern<<<(unsigned)t.n_near_items, kP2PThreads, 0, st>>>(t.near_items.get(), t.leaf_pt.get(), t.near_rng.get(),
+                                                               t.near_cnt.get(), t.px.get(), t.py.get(), t.pz.get(),
+                                                               t.pnx.get(), t.pny.get(), t.pnz.get(), src.q, src.w, y);
+        BFM_LAUNCHED();
+    }
 }
-
 void launch_p2p_packed(const Tree &t, const double *packed, double *y, hipStream_t st) {
     if (t.n_near_items <= 0) return;
     auto kern = t.near_split ? k_p2p_diag<true> : k_p2p_diag<false>;
@@ -794,8 +830,11 @@ template void launch_p2p32<true, false>(const Tree &, const Sources &, double *,
 template void launch_p2p32<false, true>(const Tree &, const Sources &, double *, hipStream_t);
 template void launch_p2p32<true, true>(const Tree &, const Sources &, double *, hipStream_t);
 
+template void launch_p2p<1, true, false>(const Tree &, const Sources &, double *, hipStream_t);
+template void launch_p2p<1, false, true>(const Tree &, const Sources &, double *, hipStream_t);
+template void launch_p2p<1, true, true>(const Tree &, const Sources &, double *, hipStream_t);
+
 #define BFM_NEAR_INST(NCH, MONO, DIP)                                                                    \
-    template void launch_p2p<NCH, MONO, DIP>(const Tree &, const Sources &, double *, hipStream_t); \
     template void launch_direct<NCH, MONO, DIP>(const Tree &, const Sources &, double *, hipStream_t);
 BFM_NEAR_INST(1, true, false)
 BFM_NEAR_INST(1, false, true)
