@@ -215,15 +215,19 @@ __device__ inline void split8(const float *v, bool ok, bf16x8 &hi, bf16x8 &lo) {
 
 // STORE: the result of every task is stored (out = [task][LD]) for a
 // reduction per target box instead of added atomically into the target.
-// LD, PP, op0, g0 as for k_translate (the operators hold LD rows and
+// LD, PP as for k_translate (the operators hold LD rows and
 // round-up(LD, 32) / 32 chunks; K beyond PP is masked through the input).
+// Small launches are a chain of dependent loads, each of them a miss of a cold
+// L2 (about 1 us): the tile's record, the boxes of its columns (sources and
+// targets together) and their coefficients are three; searching the prefix
+// and the group first made it six at eight operators and twelve at 316.
 template <int PP, int ROWS, int KIND, bool STORE, int LD = PP>
-__global__ void __launch_bounds__(64 * kBfWaves) k_translate_bf3(int op0, int nops, const int *tile_off, int g0,
-                                                                 int ntiles,
-                                                                 const int *op_off, const int *tsrc,
-                                                                 const int *tdst, int nch, int swap,
-                                                                 const uint4 *Thi, const uint4 *Tlo,
-                                                                 const float *in, float *out) {
+__global__ void __launch_bounds__(64 * kBfWaves) k_translate_bf3(const int4 *__restrict__ tiles, int ntiles,
+                                                                 const int *__restrict__ tsrc,
+                                                                 const int *__restrict__ tdst, int nch, int swap,
+                                                                 const uint4 *__restrict__ Thi,
+                                                                 const uint4 *__restrict__ Tlo, const float *in,
+                                                                 float *out) {
     static_assert(PP % ROWS == 0 && ROWS % 16 == 0 && PP <= LD, "row slab");
     constexpr int KP = (PP + 31) / 32 * 32, NC = KP / 32, NSLAB = PP / ROWS, RB = ROWS / 16;
     constexpr int NCF = (LD + 31) / 32;  // chunks of the stored operators
@@ -235,20 +239,11 @@ __global__ void __launch_bounds__(64 * kBfWaves) k_translate_bf3(int op0, int no
     const int xcd = blockIdx.x % kXcds, idx = blockIdx.x / kXcds;
     const int logical = xcd * per + (xcd < rem ? xcd : rem) + idx;
     if (logical / NSLAB >= ntiles) return;
-    const int g = g0 + logical / NSLAB, slab = logical % NSLAB;
+    const int4 tile = tiles[logical / NSLAB];
+    const int slab = logical % NSLAB;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    int lo = op0, hi = op0 + nops;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (tile_off[mid] <= g)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    const int op = lo;
-    const int t0 = op_off[op];
-    const int ncols = (op_off[op + 1] - t0) * nch;
-    const int colbase = (g - tile_off[op]) * kBfTile + wave * (kBfCb * 16);
+    const int op = tile.x, t0 = tile.y, ncols = tile.z;
+    const int colbase = tile.w + wave * (kBfCb * 16);
     const int kq = lane >> 4, rl = lane & 15;
     const float *acol[kBfCb];
     bool aok[kBfCb];
@@ -260,6 +255,16 @@ __global__ void __launch_bounds__(64 * kBfWaves) k_translate_bf3(int op0, int no
         const int ch = aok[cb] ? col % nch : 0;
         const int sb = aok[cb] ? (swap ? tdst[task] : tsrc[task]) : 0;
         acol[cb] = in + ((int64_t)sb * nch + ch) * LD;
+    }
+    int db[kBfCb][4];  // target boxes of this lane's result columns
+    if (!STORE) {
+#pragma unroll
+        for (int cb = 0; cb < kBfCb; ++cb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int task = t0 + min(colbase + cb * 16 + 4 * kq + r, ncols - 1) / nch;
+                db[cb][r] = swap ? tsrc[task] : tdst[task];
+            }
     }
     // chunk c of this slab: 16-byte unit u (row u / 4, k group u % 4)
     const uint4 *sh = Thi + ((int64_t)op * NCF * LD + slab * ROWS) * 4;
@@ -351,14 +356,13 @@ __global__ void __launch_bounds__(64 * kBfWaves) k_translate_bf3(int op0, int no
         for (int r = 0; r < 4; ++r) {
             const int col = colbase + cb * 16 + 4 * kq + r;
             if (col >= ncols) continue;
-            const int task = t0 + col / nch, ch = col % nch;
+            const int ch = col % nch;
             if (STORE) {
                 float *dcol = out + ((int64_t)(t0 * nch + col)) * LD + slab * ROWS + rl;
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) dcol[rb * 16] = acc[cb][rb][r];
             } else {
-                const int db = swap ? tsrc[task] : tdst[task];
-                float *dcol = out + ((int64_t)db * nch + ch) * LD + slab * ROWS + rl;
+                float *dcol = out + ((int64_t)db[cb][r] * nch + ch) * LD + slab * ROWS + rl;
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) unsafeAtomicAdd(dcol + rb * 16, acc[cb][rb][r]);
             }
@@ -739,13 +743,14 @@ static void translate(FmmWork &w, int cls, TaskList &tl, int nch, bool swap, con
 // at p = 20 (accumulator registers and LDS bound the slab).
 constexpr int bf_rows(int PP) { return PP <= 144 ? PP : (PP == 256 ? 128 : 80); }
 
+// tiles g0 .. g0 + ntiles - 1
 template <int PPo, int LD, bool STORE>
-static void launch_bf3(int op0, int nops, int g0, int ntiles, const int *to, const TaskList &tl, bool swap,
-                       const uint16_t *Thi, const uint16_t *Tlo, const float *in, float *out, hipStream_t st) {
+static void launch_bf3(int g0, int ntiles, const TaskList &tl, bool swap, const uint16_t *Thi, const uint16_t *Tlo,
+                       const float *in, float *out, hipStream_t st) {
     if (ntiles <= 0) return;
     constexpr int RM = bf_rows(PPo);
     k_translate_bf3<PPo, RM, STORE ? 0 : 1, STORE, LD><<<(unsigned)(ntiles * (PPo / RM)), 64 * kBfWaves, 0, st>>>(
-        op0, nops, to, g0, ntiles, tl.op_off.get(), tl.src.get(), tl.dst.get(), 1, swap ? 1 : 0,
+        tl.tiles_for(1, kBfTile) + g0, ntiles, tl.src.get(), tl.dst.get(), 1, swap ? 1 : 0,
         reinterpret_cast<const uint4 *>(Thi), reinterpret_cast<const uint4 *>(Tlo), in, out);
     BFM_LAUNCHED();
 }
@@ -762,7 +767,6 @@ static void translate_bf3(FmmWork &w, int cls, TaskList &tl, bool swap, const ui
     if (cls == KC_M2L) w.m2l_shape_used = 1;
     if (nt <= 0) return;
     const int pi = prof_begin(w, cls, st);
-    const int *to = tl.tile_for(1, kBfTile);
     double flops = 2.0 * (double)PP * PP * (double)tl.ntasks;
     if (cls == KC_M2L) {
         float *part = w.part32.ensure((size_t)tl.ntasks * PP);
@@ -778,16 +782,16 @@ static void translate_bf3(FmmWork &w, int cls, TaskList &tl, bool swap, const ui
                 const int g0 = tiles_before(tl, 1, kBfTile, o0), g1 = tiles_before(tl, 1, kBfTile, o1);
                 flops += 2.0 * (double)po * po * po * po * (double)(tl.op_off_h[o1] - tl.op_off_h[o0]);
                 if (po == P_)
-                    launch_bf3<PP, PP, true>(o0, o1 - o0, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
+                    launch_bf3<PP, PP, true>(g0, g1 - g0, tl, swap, Thi, Tlo, in, part, st);
                 else if (po == P1)
-                    launch_bf3<P1 * P1, PP, true>(o0, o1 - o0, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
+                    launch_bf3<P1 * P1, PP, true>(g0, g1 - g0, tl, swap, Thi, Tlo, in, part, st);
                 else
-                    launch_bf3<P2 * P2, PP, true>(o0, o1 - o0, g0, g1 - g0, to, tl, swap, Thi, Tlo, in, part, st);
+                    launch_bf3<P2 * P2, PP, true>(g0, g1 - g0, tl, swap, Thi, Tlo, in, part, st);
             }
             cut1 = tl.op_off_h[first[1]];
             cut2 = tl.op_off_h[first[2]];
         } else {
-            launch_bf3<PP, PP, true>(0, tl.nops, 0, nt, to, tl, swap, Thi, Tlo, in, part, st);
+            launch_bf3<PP, PP, true>(0, nt, tl, swap, Thi, Tlo, in, part, st);
         }
         if (tl.dst_nbox > 0) {
             k_m2l_reduce<PP><<<(unsigned)tl.dst_nbox, 64, 0, st>>>(tl.dst_off.get(), tl.pos_of.get(), tl.dst_box0,
@@ -795,7 +799,7 @@ static void translate_bf3(FmmWork &w, int cls, TaskList &tl, bool swap, const ui
             BFM_LAUNCHED();
         }
     } else {
-        launch_bf3<PP, PP, false>(0, tl.nops, 0, nt, to, tl, swap, Thi, Tlo, in, out, st);
+        launch_bf3<PP, PP, false>(0, nt, tl, swap, Thi, Tlo, in, out, st);
     }
     prof_end(w, pi, st, flops);
 }

@@ -74,17 +74,19 @@ __device__ __forceinline__ void az_static_for(F &&f) {
     }
 }
 
+constexpr int kAzAhead = 2;  // chunks in flight in the single-wave shape
+
 // The chunk loop and the result of one slab: NCB cosine and NSB sine row
 // blocks starting at row block rb0.
 template <int P, int PB, int WAVES, int NCB, int NSB, int KIND>
 __device__ __forceinline__ void az_slab(int rb0, const double *__restrict__ Top, const double *__restrict__ bcol,
                                double (*As)[PB * 512], const double2 *Fs, const int *Os, int colbase, int ncols,
-                               int t0, int nch, const int *__restrict__ dbox, int64_t ld, int task0,
+                               int t0, int nch, const int *tbox, int64_t ld, int task0,
                                double *__restrict__ out) {
     using S = Az<P>;
     constexpr bool DIRECT = WAVES == 1;  // operator straight to registers
-    constexpr int NT = 64 * WAVES;
-    constexpr int PER = az_cdiv(NCB * 256, NT);
+    [[maybe_unused]] constexpr int NT = 64 * WAVES;
+    [[maybe_unused]] constexpr int PER = az_cdiv(NCB * 256, NT);
     const int tid = threadIdx.x, lane = tid & 63;
     const int kq = lane >> 4, rl = lane & 15;
     az_dbl4 ac[NCB], as[NSB > 0 ? NSB : 1];
@@ -92,91 +94,114 @@ __device__ __forceinline__ void az_slab(int rb0, const double *__restrict__ Top,
     for (int b = 0; b < NCB; ++b) ac[b] = az_dbl4{0, 0, 0, 0};
 #pragma unroll
     for (int b = 0; b < NSB; ++b) as[b] = az_dbl4{0, 0, 0, 0};
-    double2 pre[DIRECT ? 1 : PER];
-    double dc[DIRECT ? 4 * NCB : 1], ds[DIRECT && NSB > 0 ? 4 * NSB : 1];
-    AzPair raw[4];
-    auto fetch = [&](int c) {
-        const double *src = Top + ((int64_t)c * S::CC + rb0) * 512;
-        if (DIRECT) {
+    if constexpr (DIRECT) {
+        // the operator and the expansions of kAzAhead chunks in flight, in
+        // registers: a wave with one chunk ahead waited for memory at every
+        // chunk
+        constexpr int D = S::CC < kAzAhead ? S::CC : kAzAhead;
+        AzPair raw[D][4];
+        double dc[D][4 * NCB], ds[D][NSB > 0 ? 4 * NSB : 1];
+        auto fetch = [&](int c, AzPair(&rw)[4], double(&oc)[4 * NCB], double(&os)[NSB > 0 ? 4 * NSB : 1]) {
+            const double *src = Top + ((int64_t)c * S::CC + rb0) * 512 + lane;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                rw[kk] = *reinterpret_cast<const AzPair *>(bcol + Os[16 * c + 4 * kk + kq]);
+#pragma unroll
+                for (int b = 0; b < NCB; ++b) oc[kk * NCB + b] = src[b * 512 + kk * 64];
+#pragma unroll
+                for (int b = 0; b < NSB; ++b) os[kk * NSB + b] = src[b * 512 + 256 + kk * 64];
+            }
+        };
+        az_static_for<0, D>([&](auto ci) {
+            constexpr int C = decltype(ci)::value;
+            fetch(C, raw[C], dc[C], ds[C]);
+        });
+        az_static_for<0, S::CC>([&](auto ci) {
+            constexpr int C = decltype(ci)::value, U = C % D;
+            // MFMA steps of the chunk's cosine and sine part
+            constexpr int KC = az_cdiv(S::NC - 16 * C, 4), KS = S::NS > 16 * C ? az_cdiv(S::NS - 16 * C, 4) : 0;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const double2 f = Fs[16 * C + 4 * kk + kq];
+                const double bc = f.x * raw[U][kk].x - f.y * raw[U][kk].y;
+                const double bs = f.y * raw[U][kk].x + f.x * raw[U][kk].y;
+#pragma unroll
+                for (int b = 0; b < NCB; ++b)
+                    if (kk < KC) ac[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(bc, dc[U][kk * NCB + b], ac[b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < NSB; ++b)
+                    if (kk < KS) as[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(bs, ds[U][kk * NSB + b], as[b], 0, 0, 0);
+            }
+            if constexpr (C + D < S::CC) {
+                fetch(C + D, raw[U], dc[U], ds[U]);
+                __builtin_amdgcn_sched_barrier(0);  // issued here, not where they are used
+            }
+        });
+    } else {
+        double2 pre[PER];
+        AzPair raw[4];
+        auto fetch = [&](int c) {
+            const double2 *s2 = reinterpret_cast<const double2 *>(Top + ((int64_t)c * S::CC + rb0) * 512);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) pre[u] = s2[min(tid + u * NT, NCB * 256 - 1)];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+                raw[kk] = *reinterpret_cast<const AzPair *>(bcol + Os[16 * c + 4 * kk + kq]);
+        };
+        auto stash = [&](int buf) {
+            double2 *d2 = reinterpret_cast<double2 *>(As[buf]);
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (PER * NT == NCB * 256 || tid + u * NT < NCB * 256) d2[tid + u * NT] = pre[u];
+        };
+        fetch(0);
+        stash(0);
+        __syncthreads();
+        // chunk c: rotate its pairs into the two B operands, start the next
+        // chunk's loads, multiply; NKC, NKS: MFMA steps of the cosine and the
+        // sine part
+        auto step = [&](int c, auto nkc, auto nks, auto last) {
+            constexpr int NKC = decltype(nkc)::value, NKS = decltype(nks)::value;
+            constexpr bool LAST = decltype(last)::value;
+            double bc[4], bs[4];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const double2 f = Fs[16 * c + 4 * kk + kq];
+                bc[kk] = f.x * raw[kk].x - f.y * raw[kk].y;
+                bs[kk] = f.y * raw[kk].x + f.x * raw[kk].y;
+            }
+            if (!LAST) fetch(c + 1);
+            const double *Ab = As[c & 1] + lane;
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
 #pragma unroll
-                for (int b = 0; b < NCB; ++b) dc[kk * NCB + b] = src[b * 512 + kk * 64 + lane];
+                for (int b = 0; b < NCB; ++b)
+                    if (kk < NKC)
+                        ac[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(bc[kk], Ab[b * 512 + kk * 64], ac[b], 0, 0, 0);
 #pragma unroll
-                for (int b = 0; b < NSB; ++b) ds[kk * NSB + b] = src[b * 512 + 256 + kk * 64 + lane];
+                for (int b = 0; b < NSB; ++b)
+                    if (kk < NKS)
+                        as[b] =
+                            __builtin_amdgcn_mfma_f64_16x16x4f64(bs[kk], Ab[b * 512 + 256 + kk * 64], as[b], 0, 0, 0);
             }
-        } else {
-            const double2 *s2 = reinterpret_cast<const double2 *>(src);
-#pragma unroll
-            for (int u = 0; u < PER; ++u)
-                pre[u] = s2[min(tid + u * NT, NCB * 256 - 1)];
-        }
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-            raw[kk] = *reinterpret_cast<const AzPair *>(bcol + Os[16 * c + 4 * kk + kq]);
-    };
-    auto stash = [&](int buf) {
-        if (DIRECT) return;
-        double2 *d2 = reinterpret_cast<double2 *>(As[buf]);
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (PER * NT == NCB * 256 || tid + u * NT < NCB * 256) d2[tid + u * NT] = pre[u];
-    };
-    fetch(0);
-    stash(0);
-    if (!DIRECT) __syncthreads();
-    // chunk c: rotate its pairs into the two B operands, start the next
-    // chunk's loads, multiply; NKC, NKS: MFMA steps of the cosine and the
-    // sine part
-    auto step = [&](int c, auto nkc, auto nks, auto last) {
-        constexpr int NKC = decltype(nkc)::value, NKS = decltype(nks)::value;
-        constexpr bool LAST = decltype(last)::value;
-        double bc[4], bs[4];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const double2 f = Fs[16 * c + 4 * kk + kq];
-            bc[kk] = f.x * raw[kk].x - f.y * raw[kk].y;
-            bs[kk] = f.y * raw[kk].x + f.x * raw[kk].y;
-        }
-        double oc[DIRECT ? 4 * NCB : 1], os[DIRECT && NSB > 0 ? 4 * NSB : 1];
-        if (DIRECT) {
-#pragma unroll
-            for (int e = 0; e < 4 * NCB; ++e) oc[e] = dc[e];
-#pragma unroll
-            for (int e = 0; e < 4 * NSB; ++e) os[e] = ds[e];
-        }
-        if (!LAST) fetch(c + 1);
-        const double *Ab = As[DIRECT ? 0 : c & 1] + lane;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-#pragma unroll
-            for (int b = 0; b < NCB; ++b)
-                if (kk < NKC)
-                    ac[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        bc[kk], DIRECT ? oc[kk * NCB + b] : Ab[b * 512 + kk * 64], ac[b], 0, 0, 0);
-#pragma unroll
-            for (int b = 0; b < NSB; ++b)
-                if (kk < NKS)
-                    as[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        bs[kk], DIRECT ? os[kk * NSB + b] : Ab[b * 512 + 256 + kk * 64], as[b], 0, 0, 0);
-        }
-        if (!DIRECT && !LAST) {
-            // the stores wait for the loads: keep them behind the products
-            __builtin_amdgcn_sched_barrier(0);
-            stash((c + 1) & 1);
-            __syncthreads();
-        }
-    };
-    // chunks full in both parts, then the tail's partial ones
-    constexpr int CF = S::NS / 16;
-    static_assert(CF < S::CC, "a tail chunk");
+            if (!LAST) {
+                // the stores wait for the loads: keep them behind the products
+                __builtin_amdgcn_sched_barrier(0);
+                stash((c + 1) & 1);
+                __syncthreads();
+            }
+        };
+        // chunks full in both parts, then the tail's partial ones
+        constexpr int CF = S::NS / 16;
+        static_assert(CF < S::CC, "a tail chunk");
 #pragma unroll 1
-    for (int c = 0; c < CF; ++c) step(c, az_int<4>{}, az_int<4>{}, az_int<0>{});
-    az_static_for<CF, S::CC>([&](auto ci) {
-        constexpr int C = decltype(ci)::value;
-        constexpr int KC = az_cdiv(S::NC - 16 * C, 4), KS = S::NS > 16 * C ? az_cdiv(S::NS - 16 * C, 4) : 0;
-        step(C, az_int<(KC < 4 ? KC : 4)>{}, az_int<(KS < 4 ? KS : 4)>{}, az_int<(C + 1 == S::CC)>{});
-    });
+        for (int c = 0; c < CF; ++c) step(c, az_int<4>{}, az_int<4>{}, az_int<0>{});
+        az_static_for<CF, S::CC>([&](auto ci) {
+            constexpr int C = decltype(ci)::value;
+            constexpr int KC = az_cdiv(S::NC - 16 * C, 4), KS = S::NS > 16 * C ? az_cdiv(S::NS - 16 * C, 4) : 0;
+            step(C, az_int<(KC < 4 ? KC : 4)>{}, az_int<(KS < 4 ? KS : 4)>{}, az_int<(C + 1 == S::CC)>{});
+        });
+    }
     // lane l, element r: column l/16 + 4r, row l%16 of each block
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -184,7 +209,7 @@ __device__ __forceinline__ void az_slab(int rb0, const double *__restrict__ Top,
         if (col >= ncols) continue;
         // M2L: the column's row of results, cosine values then sine values
         double *dcol = KIND == 0 ? out + ((int64_t)(t0 - task0) * nch + col) * (P * P)
-                             : out + ((int64_t)dbox[t0 + col / nch] * nch + col % nch) * ld;
+                             : out + ((int64_t)tbox[kq + 4 * r] * nch + col % nch) * ld;
 #pragma unroll
         for (int b = 0; b < NCB; ++b) {
             const int i = (rb0 + b) * 16 + rl;
@@ -212,18 +237,18 @@ __device__ __forceinline__ void az_slab(int rb0, const double *__restrict__ Top,
 }
 
 // P: the order applied; LDP: the order the expansions are stored at (degrees
-// P and above are left alone). Offsets op0 .. op0 + nops - 1, whose tiles are
-// g0 .. g0 + ntiles - 1 of the prefix tile_off; canon[o] = operator of offset
-// o in T, fac / off = rotation factors (per offset) and packed positions of
-// the table entries. KIND: 0 M2L, 1 M2M (added to the parent atomically), 2
+// P and above are left alone). tiles: records of the launch's ntiles tiles (one
+// load instead of a search of the offsets, each step of which missed a cold L2:
+// a small launch is a chain of such misses); canon[o] = operator of offset o in
+// T, fac / off = rotation factors (per offset) and packed positions of the table
+// entries. KIND: 0 M2L, 1 M2M (added to the parent atomically), 2
 // L2L. The M2L results of task t go to row t - task0 of out ([nch][P^2],
 // cosine values, then sine values) for k_az_reduce instead of being added to
 // the target's expansion: FP64 atomic adds ran at 75 to 97 G adds/s whatever
 // the kernel around them did (59,112 tasks at order 16: 190 us with half the
 // products as with all of them, 137 us stored and summed).
 template <int P, int LDP, int PB, int WAVES, int KIND>
-__global__ void __launch_bounds__(64 * WAVES, WAVES == 1 ? 4 : (P == 12 ? 2 : (P == 20 ? 3 : 4))) k_translate_az(int op0, int nops, const int *__restrict__ tile_off,
-                                                             int g0, int ntiles, const int *__restrict__ op_off,
+__global__ void __launch_bounds__(64 * WAVES, WAVES == 1 ? 4 : (P == 12 ? 2 : (P == 20 ? 3 : 4))) k_translate_az(const int4 *__restrict__ tiles, int ntiles,
                                                              const int *__restrict__ tsrc,
                                                              const int *__restrict__ tdst, int nch,
                                                              const int *__restrict__ canon,
@@ -243,23 +268,25 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 1 ? 4 : (P == 12 ? 2 : (P
     __shared__ __align__(16) double As[WAVES == 1 ? 1 : 2][PB * 512];
     __shared__ double2 Fs[S::CC * 16];
     __shared__ int Os[S::CC * 16];
+    __shared__ int Bs[KIND == 0 ? 1 : 16 * WAVES];  // target boxes of the tile's columns
     // XCD-aware order: XCD x takes a contiguous run of logical blocks (the
     // tiles of a few offsets), whose operators then stay in its own L2
     const int nblock = gridDim.x, per = nblock / kAzXcds, rem = nblock % kAzXcds;
     const int xcd = blockIdx.x % kAzXcds, idx = blockIdx.x / kAzXcds;
     const int logical = xcd * per + (xcd < rem ? xcd : rem) + idx;
     if (logical / NSLAB >= ntiles) return;
-    const int g = g0 + logical / NSLAB, slab = logical % NSLAB;
+    const int4 tile = tiles[logical / NSLAB];
+    const int slab = logical % NSLAB;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    int lo = op0, hi = op0 + nops;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (tile_off[mid] <= g)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    const int op = lo;
+    const int op = tile.x, t0 = tile.y, ncols = tile.z;
+    const int colbase = tile.w + wave * 16;
+    const int bcolid = colbase + (lane & 15);
+    const bool bok = bcolid < ncols;
+    // idle columns read the first one (valid memory) and are never stored
+    const int bt = bok ? bcolid : 0;
+    const int sbox = tsrc[t0 + bt / nch];
+    const double *Top = T + (int64_t)canon[op] * S::OPW;
+    if (KIND != 0 && tid < 16 * WAVES) Bs[tid] = tdst[t0 + min(tile.w + tid, ncols - 1) / nch];
     for (int e = tid; e < S::CC * 16; e += 64 * WAVES) {
         const int t = e < S::NS ? e : (e < S::NC ? kAzPairs + e - S::NS : -1);
         // rows past the order: zero factors and a valid position
@@ -267,20 +294,12 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == 1 ? 4 : (P == 12 ? 2 : (P
         Os[e] = t >= 0 ? off[t] : 0;
     }
     __syncthreads();
-    const int t0 = op_off[op];
-    const int ncols = (op_off[op + 1] - t0) * nch;
-    const int colbase = (g - tile_off[op]) * (16 * WAVES) + wave * 16;
-    const int bcolid = colbase + (lane & 15);
-    const bool bok = bcolid < ncols;
-    // idle columns read the first one (valid memory) and are never stored
-    const int bt = bok ? bcolid : 0;
-    const double *bcol = in + ((int64_t)tsrc[t0 + bt / nch] * nch + bt % nch) * (LDP * LDP);
-    const double *Top = T + (int64_t)canon[op] * S::OPW;
+    const double *bcol = in + ((int64_t)sbox * nch + bt % nch) * (LDP * LDP);
     if (slab < FULL)
-        az_slab<P, PB, WAVES, PB, PB, KIND>(slab * PB, Top, bcol, As, Fs, Os, colbase, ncols, t0, nch, tdst, LDP * LDP,
+        az_slab<P, PB, WAVES, PB, PB, KIND>(slab * PB, Top, bcol, As, Fs, Os, colbase, ncols, t0, nch, Bs + 16 * wave, LDP * LDP,
                                                task0, out);
     else
-        az_slab<P, PB, WAVES, LCB, LSB, KIND>(slab * PB, Top, bcol, As, Fs, Os, colbase, ncols, t0, nch, tdst, LDP * LDP,
+        az_slab<P, PB, WAVES, LCB, LSB, KIND>(slab * PB, Top, bcol, As, Fs, Os, colbase, ncols, t0, nch, Bs + 16 * wave, LDP * LDP,
                                                  task0, out);
 }
 
@@ -353,7 +372,7 @@ constexpr int az_pb() {
 }
 
 template <int P, int LDP, int KIND>
-static void launch_az(int shape, int op0, int nops, int g0, int ntiles, const int *to, const TaskList &tl, bool swap,
+static void launch_az(int shape, const int4 *tiles, int ntiles, const TaskList &tl, bool swap,
                       int nch, const int *canon, const double *T, const double2 *fac, const int *off, int task0,
                       const double *in, double *out, hipStream_t st) {
     if (ntiles <= 0) return;
@@ -361,13 +380,13 @@ static void launch_az(int shape, int op0, int nops, int g0, int ntiles, const in
     const int *src = swap ? tl.dst.get() : tl.src.get(), *dst = swap ? tl.src.get() : tl.dst.get();
     if (shape == 0)
         k_translate_az<P, LDP, PB, 8, KIND><<<(unsigned)(ntiles * az_cdiv(CC, PB)), 512, 0, st>>>(
-            op0, nops, to, g0, ntiles, tl.op_off.get(), src, dst, nch, canon, T, fac, off, task0, in, out);
+            tiles, ntiles, src, dst, nch, canon, T, fac, off, task0, in, out);
     else if (shape == 1)
         k_translate_az<P, LDP, PB, 4, KIND><<<(unsigned)(ntiles * az_cdiv(CC, PB)), 256, 0, st>>>(
-            op0, nops, to, g0, ntiles, tl.op_off.get(), src, dst, nch, canon, T, fac, off, task0, in, out);
+            tiles, ntiles, src, dst, nch, canon, T, fac, off, task0, in, out);
     else
         k_translate_az<P, LDP, 1, 1, KIND><<<(unsigned)(ntiles * CC), 64, 0, st>>>(
-            op0, nops, to, g0, ntiles, tl.op_off.get(), src, dst, nch, canon, T, fac, off, task0, in, out);
+            tiles, ntiles, src, dst, nch, canon, T, fac, off, task0, in, out);
     BFM_LAUNCHED();
 }
 
@@ -577,7 +596,7 @@ static void az_one(const AzLaunch &a, int shape, int op0, int nops, const double
     const int width = shape == 0 ? 128 : (shape == 1 ? 64 : 16);
     const int g0 = az_tiles_before(tl, a.nch, width, op0), g1 = az_tiles_before(tl, a.nch, width, op0 + nops);
     const int base = KIND ? kNumM2LOps : 0;
-    launch_az<P, LDP, KIND>(shape, op0, nops, g0, g1 - g0, tl.tile_for(a.nch, width), tl, a.swap, a.nch,
+    launch_az<P, LDP, KIND>(shape, tl.tiles_for(a.nch, width) + g0, g1 - g0, tl, a.swap, a.nch,
                             a.w->az_canon.get() + base, T, a.w->az_fac.get() + (int64_t)base * kAzTab,
                             a.w->az_off.get(), tl.op_off_h[op0], a.in, out, a.st);
 }

@@ -41,6 +41,9 @@ struct TaskList {
     // workgroup-tile prefix per (channel count, tile width 64, 128 or 16),
     // built lazily: slot = nch * 3 + (0, 1, 2 by width)
     DevBuf<int> tile_off[24];
+    // per tile: operator, first task of its group, columns of the group, first
+    // column of the tile (one load instead of a search of the prefix)
+    DevBuf<int4> tiles[24];
     int ntiles[24] = {0};
     bool tiles_ready[24] = {false};
     // M2L lists only: the tasks of each target box, for a reduction of
@@ -53,6 +56,7 @@ struct TaskList {
     static int slot(int nch, int width) { return nch * 3 + (width == 128 ? 1 : (width == 16 ? 2 : 0)); }
     int ntiles_for(int nch, int width) const { return ntiles[slot(nch, width)]; }
     const int *tile_for(int nch, int width) const { return tile_off[slot(nch, width)].get(); }
+    const int4 *tiles_for(int nch, int width) const { return tiles[slot(nch, width)].get(); }
 };
 
 struct Tree {

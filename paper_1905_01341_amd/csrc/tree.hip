@@ -805,12 +805,15 @@ static void group_tasks(TaskList &tl, int nops, const int *tsrc, const int *tdst
     BFM_CHECK(!keep_positions || n == 0 || nops > 16, BFM_EINVAL, "task positions kept only for the sorted grouping");
 }
 
-// Workgroup-tile prefix of one (channel count, tile width) shape:
+// Workgroup tiles of one (channel count, tile width) shape: the prefix
 // tile_off[o] = sum over o' < o of ceil(cols(o') / width), cols(o) = tasks of
-// operator o times nch. One workgroup scans the operators 256 at a time.
-__global__ void __launch_bounds__(256) k_tile_off(const int *op_off, int nops, int nch, int width,
-                                                  int *tile_off) {
-    __shared__ int s[256];
+// operator o times nch, and every tile's record. Every workgroup scans the
+// operators, 256 at a time, and fills the records of the 256 tiles of its own;
+// the first also writes the prefix.
+constexpr int kTileOps = 512;
+__global__ void __launch_bounds__(256) k_tile_off(const int *op_off, int nops, int nch, int width, int ntiles,
+                                                  int *tile_off, int4 *tiles) {
+    __shared__ int s[256], pre[kTileOps + 1];
     const int tid = threadIdx.x;
     int carry = 0;
     for (int base = 0; base < nops; base += 256) {
@@ -824,11 +827,26 @@ __global__ void __launch_bounds__(256) k_tile_off(const int *op_off, int nops, i
             s[tid] += t;
             __syncthreads();
         }
-        if (o < nops) tile_off[o] = carry + s[tid] - v;
+        if (o < nops) pre[o] = carry + s[tid] - v;
         carry += s[255];
         __syncthreads();
     }
-    if (tid == 0) tile_off[nops] = carry;
+    if (tid == 0) pre[nops] = carry;
+    __syncthreads();
+    if (blockIdx.x == 0)
+        for (int o = tid; o <= nops; o += 256) tile_off[o] = pre[o];
+    const int g = blockIdx.x * 256 + tid;
+    if (g >= ntiles) return;
+    int lo = 0, hi = nops;  // the last operator whose tiles start at or before g
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (pre[mid] <= g)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    const int t0 = op_off[lo];
+    tiles[g] = make_int4(lo, t0, (op_off[lo + 1] - t0) * nch, (g - pre[lo]) * width);
 }
 
 void prepare_tiles(TaskList &tl, int nch, int width, hipStream_t st) {
@@ -845,7 +863,10 @@ void prepare_tiles(TaskList &tl, int nch, int width, hipStream_t st) {
         run += (cols + width - 1) / width;
     }
     tl.tile_off[sl].ensure(tl.nops + 1);
-    k_tile_off<<<1, 256, 0, st>>>(tl.op_off.get(), tl.nops, nch, width, tl.tile_off[sl].get());
+    tl.tiles[sl].ensure(std::max(run, 1));
+    BFM_CHECK(tl.nops <= kTileOps, BFM_EINVAL, "too many operators for the tile table");
+    k_tile_off<<<std::max(1, (int)nblk(run, 256)), 256, 0, st>>>(tl.op_off.get(), tl.nops, nch, width, run,
+                                                                 tl.tile_off[sl].get(), tl.tiles[sl].get());
     BFM_LAUNCHED();
     tl.ntiles[sl] = run;
     tl.tiles_ready[sl] = true;
