@@ -344,95 +344,154 @@ __global__ void __launch_bounds__(256) k_pre_gather(const double *__restrict__ i
     }
 }
 
+// Two doubles at any double's address, one load
+struct __attribute__((packed, aligned(8))) PrePair {
+    double x, y;
+};
+
+// A lane's B values of a row of K for B MFMA steps from position s on: the lane
+// takes positions s + B (lane / 16) + 0 .. B - 1 (which k of a step a lane holds
+// is free as long as both operands agree), so a row is read in runs of 8 B bytes
+// by 16-byte loads. Near the row's end the run is moved back to stay inside
+// (len >= B); v0 is its first position, and positions the lane does not own
+// (below its first, or from `end` on) come as zeros.
+template <int B>
+__device__ inline void pre_run(const double *row, int s, int len, int end, double (&x)[B], int &v0) {
+    const int first = s + B * (((int)threadIdx.x & 63) >> 4);
+    v0 = min(first, len - B);
+    if constexpr (B % 2 == 0) {
+#pragma unroll
+        for (int u = 0; u < B; u += 2) {
+            const PrePair q = *reinterpret_cast<const PrePair *>(row + v0 + u);
+            x[u] = q.x;
+            x[u + 1] = q.y;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < B; ++u) x[u] = row[v0 + u];
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) x[u] = v0 + u >= first && v0 + u < end ? x[u] : 0.0;
+}
+
 // C[i][b] = fac[i] sum_v T(i, v) X[b][v] (fac null: 1), T(i, v) = T[v * sv + i * si],
-// C column-major [nc x nb]. One 16 x 16 tile (coefficients x bubbles) per
-// workgroup, the sum over v split over its four waves: a product of this size
-// (169 x 642 x 1000) is bound by the latency of a wave's chain of loads, and 16
-// x 16 tiles with four waves each give it 2772 short chains. 64 x 64 tiles
-// with a split sum and its own reduction launch took 14 + 4 us at 1000 bubbles.
+// C column-major [nc x nb]. One tile of 16 NI coefficients x 16 NJ bubbles per
+// workgroup, the sum over v split over its four waves. A product of this size
+// (169 x 642 x 1000) is bound by the latency of a wave's chain of loads: 16 x 16
+// tiles with four waves each give it 2772 short chains, of B steps' loads at a
+// time. With many bubbles it is bound by reading the operands from L2 once per
+// tile, and the tiles are wider (kCoefWide).
+template <int NI, int NJ, int B>
 __global__ void __launch_bounds__(256) k_pre_coef(int nc, int nb, int nd, const double *__restrict__ T, int sv, int si,
                                                   const double *__restrict__ X, const double *__restrict__ fac,
                                                   double *__restrict__ C) {
-    constexpr int B = 8;  // MFMA steps whose loads are in flight together
-    __shared__ double red[3][4][64];
+    __shared__ double red[3][NI * NJ * 4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4, rl = lane & 15;
-    const int i0 = blockIdx.x * 16, b0 = blockIdx.y * 16;
-    const double *xb = X + (int64_t)min(b0 + rl, nb - 1) * nd;
-    const double *tb = T + (int64_t)min(i0 + rl, nc - 1) * si;
-    const int steps = (nd + 3) / 4, s0 = steps * wave / 4, s1 = steps * (wave + 1) / 4;
-    dbl4 acc = dbl4{0.0, 0.0, 0.0, 0.0};
-    for (int s = s0; s < s1; s += B) {
-        double x[B], t[B];
+    const int i0 = blockIdx.x * 16 * NI, b0 = blockIdx.y * 16 * NJ;
+    const int steps = (nd + 3) / 4, s0 = 4 * (steps * wave / 4), s1 = min(nd, 4 * (steps * (wave + 1) / 4));
+    dbl4 acc[NJ][NI];
 #pragma unroll
-        for (int u = 0; u < B; ++u) {
-            const int v = 4 * (s + u) + kq;
-            const int vc = min(v, nd - 1);
-            const bool ok = s + u < s1 && v < nd;
-            const double xv = xb[vc];
-            x[u] = ok ? xv : 0.0;
-            t[u] = tb[(int64_t)vc * sv];
-        }
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int u = 0; u < B; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u], t[u], acc, 0, 0, 0);
+        for (int i = 0; i < NI; ++i) acc[j][i] = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int s = s0; s < s1; s += 4 * B) {
+        double x[NJ][B], t[NI][B];
+        int v0 = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            pre_run<B>(X + (int64_t)min(b0 + 16 * j + rl, nb - 1) * nd, s, nd, s1, x[j], v0);
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                t[i][u] = T[(int64_t)(v0 + u) * sv + (int64_t)min(i0 + 16 * i + rl, nc - 1) * si];
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+                    acc[j][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[j][u], t[i][u], acc[j][i], 0, 0, 0);
     }
     if (wave > 0)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave - 1][r][lane] = acc[r];
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[wave - 1][(j * NI + i) * 4 + r][lane] = acc[j][i][r];
     __syncthreads();
     if (wave > 0) return;
-    const int i = i0 + rl;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {  // bubble b0 + kq + 4 r, coefficient i0 + rl
-        const int b = b0 + kq + 4 * r;
-        const double v = ((acc[r] + red[0][r][lane]) + red[1][r][lane]) + red[2][r][lane];
-        if (b < nb && i < nc) C[(int64_t)b * nc + i] = fac ? fac[i] * v : v;
-    }
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {  // bubble kq + 4 r, coefficient rl of the block
+                const int e = (j * NI + i) * 4 + r, b = b0 + 16 * j + kq + 4 * r, ic = i0 + 16 * i + rl;
+                const double v = ((acc[j][i][r] + red[0][e][lane]) + red[1][e][lane]) + red[2][e][lane];
+                if (b < nb && ic < nc) C[(int64_t)b * nc + ic] = fac ? fac[ic] * v : v;
+            }
 }
 
 // out_s at vertex v of bubble b (+)= ((G C + cc X)[v][b]) / R[b] (+ cy[b]); G
-// column-major [nd x nc]. One wave per 32 vertices x 16 bubbles.
+// column-major [nd x nc]. One wave per 32 vertices x 16 NJ bubbles, B steps'
+// loads in flight, the result's places loaded ahead of them. Bound by the
+// scattered result: wider tiles, which read less, change little (kOutWide).
+template <int NJ, int B>
 __global__ void __launch_bounds__(64) k_pre_out(int nc, int nb, int nd, const double *__restrict__ G,
                                                 const double *__restrict__ C, double cc,
                                                 const double *__restrict__ X, const double *__restrict__ R,
                                                 const double *__restrict__ cy, const int *__restrict__ iperm, int add,
                                                 double *__restrict__ out) {
-    constexpr int B = 8;
     const int lane = threadIdx.x, kq = lane >> 4, rl = lane & 15;
-    const int v0 = blockIdx.x * 32, b0 = blockIdx.y * 16;
-    const double *cb = C + (int64_t)min(b0 + rl, nb - 1) * nc;
+    const int v0 = blockIdx.x * 32, b0 = blockIdx.y * 16 * NJ;
     const int va = min(v0 + rl, nd - 1), vb = min(v0 + 16 + rl, nd - 1);
-    const int steps = (nc + 3) / 4;
-    dbl4 acc[2] = {dbl4{0.0, 0.0, 0.0, 0.0}, dbl4{0.0, 0.0, 0.0, 0.0}};
-    for (int s = 0; s < steps; s += B) {
-        double c[B], ga[B], gb[B];
+    int at[NJ][2][4];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                at[j][h][r] = iperm[(int64_t)min(b0 + 16 * j + kq + 4 * r, nb - 1) * nd + (h ? vb : va)];
+    dbl4 acc[NJ][2];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[j][0] = acc[j][1] = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int s = 0; s < nc; s += 4 * B) {
+        double c[NJ][B], ga[B], gb[B];
+        int c0 = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            pre_run<B>(C + (int64_t)min(b0 + 16 * j + rl, nb - 1) * nc, s, nc, nc, c[j], c0);
 #pragma unroll
         for (int u = 0; u < B; ++u) {
-            const int i = 4 * (s + u) + kq, ic = min(i, nc - 1);
-            const double cv = cb[ic];
-            c[u] = i < nc ? cv : 0.0;
-            ga[u] = G[(int64_t)ic * nd + va];
-            gb[u] = G[(int64_t)ic * nd + vb];
+            ga[u] = G[(int64_t)(c0 + u) * nd + va];
+            gb[u] = G[(int64_t)(c0 + u) * nd + vb];
         }
 #pragma unroll
-        for (int u = 0; u < B; ++u) {
-            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[u], ga[u], acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[u], gb[u], acc[1], 0, 0, 0);
-        }
+        for (int u = 0; u < B; ++u)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                acc[j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[j][u], ga[u], acc[j][0], 0, 0, 0);
+                acc[j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[j][u], gb[u], acc[j][1], 0, 0, 0);
+            }
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int v = v0 + 16 * h + rl;
-        if (v >= nd) continue;
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int b = b0 + kq + 4 * r;
-            if (b >= nb) continue;
-            const int64_t o = (int64_t)b * nd + v;
-            const double y = fma(cc, X[o], acc[h][r]) / R[b] + (cy ? cy[b] : 0.0);
-            double *d = out + iperm[o];
-            *d = add ? *d + y : y;
+        for (int h = 0; h < 2; ++h) {
+            const int v = v0 + 16 * h + rl;
+            if (v >= nd) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int b = b0 + 16 * j + kq + 4 * r;
+                if (b >= nb) continue;
+                const double y = fma(cc, X[(int64_t)b * nd + v], acc[j][h][r]) / R[b] + (cy ? cy[b] : 0.0);
+                double *d = out + at[j][h][r];
+                *d = add ? *d + y : y;
+            }
         }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -877,9 +936,20 @@ void precond_radii(bfm_ctx *c) {
     BFM_LAUNCHED();
 }
 
+// Bubbles from which the coefficients take tiles of 48 x 16 (least time of 16 x 16
+// and 48 x 16 tiles: 12 bubbles 6.3 and 10.1 us, 1000 bubbles 17.4 and 11.6, 5000
+// bubbles 69 and 39; 32 x 32, 64 x 32 and 48 x 64 lie above 48 x 16 at 1000) and
+// from which the result takes 32 bubbles a wave (16 and 32: 1000 bubbles 17 and
+// 20 us, 5000 bubbles 65 and 58).
+constexpr int kCoefWide = 512, kOutWide = 2048;
 static void pre_coef(int nc, int nb, int nd, const double *T, int sv, int si, const double *X, const double *fac,
                      double *C, hipStream_t st) {
-    k_pre_coef<<<dim3(nblk(nc, 16), nblk(nb, 16)), 256, 0, st>>>(nc, nb, nd, T, sv, si, X, fac, C);
+    if (nd < 14)  // no run of a lane fits the row
+        k_pre_coef<1, 1, 1><<<dim3(nblk(nc, 16), nblk(nb, 16)), 256, 0, st>>>(nc, nb, nd, T, sv, si, X, fac, C);
+    else if (nb < kCoefWide)
+        k_pre_coef<1, 1, 14><<<dim3(nblk(nc, 16), nblk(nb, 16)), 256, 0, st>>>(nc, nb, nd, T, sv, si, X, fac, C);
+    else
+        k_pre_coef<3, 1, 8><<<dim3(nblk(nc, 48), nblk(nb, 16)), 256, 0, st>>>(nc, nb, nd, T, sv, si, X, fac, C);
     BFM_LAUNCHED();
 }
 
@@ -908,8 +978,10 @@ void precond_apply(bfm_ctx *c, const double *in_s, double *out_s, bool add) {
         BFM_LAUNCHED();
         cy = P.cy.get();
     }
-    k_pre_out<<<dim3(nblk(nd, 32), nblk(nb, 16)), 64, 0, st>>>(nc, nb, nd, P.basis.G.get(), Cm, P.cc, X, P.R.get(), cy,
-                                                               iperm, add ? 1 : 0, out_s);
+    auto out = nc < 12 ? k_pre_out<1, 1> : (nb < kOutWide ? k_pre_out<1, 12> : k_pre_out<2, 4>);
+    const int wide = nc >= 12 && nb >= kOutWide ? 32 : 16;
+    out<<<dim3(nblk(nd, 32), nblk(nb, wide)), 64, 0, st>>>(nc, nb, nd, P.basis.G.get(), Cm, P.cc, X, P.R.get(), cy,
+                                                           iperm, add ? 1 : 0, out_s);
     BFM_LAUNCHED();
 }
 
