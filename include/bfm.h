@@ -133,7 +133,8 @@ typedef struct bfm_options {
     int p2p_shape;     /* work items of the symmetric one-channel near field (receivers per
                           chunk, sources per piece of the chunk's own block, per piece of the
                           rest): -1 or 0 = (256, 128, 192), 1 = (128, 128, 128), 2 = (256, 128,
-                          384); set by bfm_autotune */
+                          384); set by bfm_autotune; meshes of fewer than 524,288 points take
+                          (128, 64, 64) with each of them */
     int near_corr;     /* != 0: add near-field correction matrices to every product, the
                           singular diagonals and b (Section 3.9): for each collocation point
                           i the triangles touching i or its mesh neighbours are integrated

@@ -27,6 +27,15 @@ struct SymShape {
 };
 constexpr int kSymShapeCount = 3;
 constexpr SymShape kSymShapes[kSymShapeCount] = {{256, 128, 192}, {128, 128, 128}, {256, 128, 384}};
+// Meshes of fewer than kSymSmall points have too few pairs for such items to fill
+// the device (100 bubbles, 41.6 M pairs: 2587 waves on 1024 SIMDs) and take the
+// smallest, one tile of 64 sources, whatever the shape. Near field alone, FP64 /
+// FP32: 7704 points 23 / 22 us with (128, 128, 128), 15 / 14 so; 64,200 points 43
+// (60 with shape 0) and 35 us; 642,000 points 256 / 136 and 253 / 132. The solve
+// of 642,000 points takes 9.00 ms with shape 1, 9.02 so, that of 1.28 M 17.6
+// (shape 0) and 17.8; of 160,500 points 3.64 and 3.60.
+constexpr SymShape kSymShapeSmall = {128, 64, 64};
+constexpr int64_t kSymSmall = (int64_t)1 << 19;
 
 // Translation tasks grouped by operator: tasks op_off[o]..op_off[o+1] use
 // operator o; task t moves expansion src[t] into expansion dst[t] (global

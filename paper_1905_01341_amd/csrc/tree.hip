@@ -932,7 +932,7 @@ void build_tree(Tree &t, const double *xyz, int64_t n, int lmax_req, int leaf_ta
     BFM_CHECK(sym_shape >= 0 && sym_shape < kSymShapeCount, BFM_EINVAL, "near-field item shape out of range");
     t.valid = false;
     t.n = n;
-    const SymShape sh = kSymShapes[sym_shape];
+    const SymShape sh = n < kSymSmall ? kSymShapeSmall : kSymShapes[sym_shape];
     static_assert(kSymShapes[0].dpiece % 64 == 0 && kSymShapes[1].dpiece % 64 == 0 && kSymShapes[2].dpiece % 64 == 0,
                   "pieces of a chunk's own block start at receiver-group bounds");
     static_assert(kSymShapes[0].chunk <= kSymChunk && kSymShapes[1].chunk <= kSymChunk &&
