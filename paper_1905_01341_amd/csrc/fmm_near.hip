@@ -191,7 +191,8 @@ __device__ inline void p2p_dip_item(int rc, int l0, int l1, int s0, int s1, int 
 // estimate a pair with both layers; the weights take in the powers of -2 of the
 // reciprocal. Each source tile passes through LDS once for the item's receivers: 218
 // M pairs in leaves of 156 points, both layers, 277 us with scalar source loads
-// and two receivers a lane throughout, 249 so.
+// and two receivers a lane throughout and pieces of 384, 249 so, 216 with pieces
+// of 128.
 template <bool MONO, bool ATOMIC>
 __global__ void __launch_bounds__(kP2PThreads) k_p2p_dip(const int4 *__restrict__ items,
                                                          const int *__restrict__ leaf_pt,

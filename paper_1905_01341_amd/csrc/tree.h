@@ -13,8 +13,13 @@ namespace bfm {
 constexpr int kKeyBits = 15;  // bits per axis of the point keys (levels 0..15)
 constexpr int kP2PChunk = 128;   // receivers per near-field work item (two per lane)
 constexpr int kLeafChunk = 256;  // points per leaf work item of P2M and L2P (four per lane)
-constexpr int kP2PPiece = 384;   // near-field sources per work item at most (a leaf's source
-                                 // list longer than this is split into balanced pieces)
+// one-sided near-field sources per work item at most (a leaf's source list longer
+// than this is split into balanced pieces). Five-channel sums, pieces of 384 /
+// 192 / 128 / 64: 7704 points 110 / 63 / 46 / 29 us, 64,200 points 132 / 101 / 93 /
+// 80, 642,000 points 875 / 838 / 837 / 856, 3.2 M points 3612 / 3608 / 3641 / 3812:
+// shorter items fill the device on small meshes and even out its tail, until
+// the sums' atomics cost more.
+constexpr int kP2PPiece = 128;
 // symmetric near field (one channel of monopoles): receivers per chunk (up
 // to four per lane), and the positions per work item at most in the chunk's
 // diagonal block and in the two-sided rest of its list
