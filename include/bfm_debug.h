@@ -41,8 +41,8 @@ int bfm_debug_operator(int p, int kind, int index, double *out, int *d_out);
  * Device dense kernels on host data, for tests (need a GPU):
  * bfm_debug_dgemm: C = A B with the library's FP64 MFMA GEMM; A [M x K],
  * B [K x N], C [M x N], all column-major host arrays.
- * bfm_debug_spd_inverse: the library's in-place blocked Gauss-Jordan inverse
- * (no pivoting) of a symmetric positive definite n x n column-major matrix,
+ * bfm_debug_spd_inverse: the library's in-place inverse (a blocked symmetric sweep
+ * without pivoting; the lower triangle is read) of a symmetric positive definite n x n column-major matrix,
  * as used for the coarse correction of BFM_PRECOND_SH_COARSE.
  * Return BFM_OK or a BFM_E* code (message in bfm_last_error()).
  */

@@ -281,7 +281,7 @@ def debug_dgemm(A, B, device=0):
 
 
 def debug_spd_inverse(A, device=0):
-    """The library's blocked Gauss-Jordan inverse of an SPD matrix (test hook)."""
+    """The library's blocked-sweep inverse of an SPD matrix (test hook)."""
     A = np.asfortranarray(A, dtype=np.float64)
     n = A.shape[0]
     out = np.empty((n, n), dtype=np.float64, order="F")

@@ -218,9 +218,10 @@ __device__ inline void split8(const float *v, bool ok, bf16x8 &hi, bf16x8 &lo) {
 // LD, PP as for k_translate (the operators hold LD rows and
 // round-up(LD, 32) / 32 chunks; K beyond PP is masked through the input).
 // Small launches are a chain of dependent loads, each of them a miss of a cold
-// L2 (about 1 us): the tile's record, the boxes of its columns (sources and
-// targets together) and their coefficients are three; searching the prefix
-// and the group first made it six at eight operators and twelve at 316.
+// L2: the tile's record, the boxes of its columns (sources and targets
+// together) and their coefficients are three; searching the prefix and the
+// group first made it six at eight operators (M2M and L2L of 642,000 points
+// 12.1 -> 9.6 us) and twelve at 316 (M2L 51.7 -> 50.2 us).
 template <int PP, int ROWS, int KIND, bool STORE, int LD = PP>
 __global__ void __launch_bounds__(64 * kBfWaves) k_translate_bf3(const int4 *__restrict__ tiles, int ntiles,
                                                                  const int *__restrict__ tsrc,
