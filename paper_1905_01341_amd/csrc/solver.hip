@@ -596,7 +596,8 @@ __global__ void __launch_bounds__(kRedThreads) k_gs_finish(double *sm, SmallLayo
 }
 
 // Start of a cycle: beta = ||r|| from its partials to res (pinned host memory),
-// g = [beta, 0, ...], v_0 = r / beta
+// g = [beta, 0, ...], v_0 = r / beta. A residual that is not a number goes to res
+// as one (fmax alone would make it 0, which the host takes for convergence).
 __global__ void __launch_bounds__(kRedThreads) k_cycle_start(double *sm, SmallLayout L, const double *__restrict__ part,
                                                              double *__restrict__ r, int64_t n, double *res) {
     __shared__ double nrm[1];
@@ -607,7 +608,7 @@ __global__ void __launch_bounds__(kRedThreads) k_cycle_start(double *sm, SmallLa
         r[i] *= inv;
     if (blockIdx.x == 0) {
         for (int i = threadIdx.x; i <= L.m; i += kRedThreads) sm[L.g + i] = i == 0 ? beta : 0.0;
-        if (threadIdx.x == 0) *res = beta;
+        if (threadIdx.x == 0) *res = sqrt(nrm[0]);
     }
 }
 
