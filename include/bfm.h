@@ -132,9 +132,9 @@ typedef struct bfm_options {
                           ones' accuracy at lower order. Applies to every product */
     int p2p_shape;     /* work items of the symmetric one-channel near field (receivers per
                           chunk, sources per piece of the chunk's own block, per piece of the
-                          rest): -1 or 0 = (256, 128, 192), 1 = (128, 128, 128), 2 = (256, 128,
-                          384); set by bfm_autotune; meshes of fewer than 524,288 points take
-                          (128, 64, 64) with each of them */
+                          rest): 0 = (256, 128, 192), 1 = (128, 128, 128), 2 = (256, 128,
+                          384), -1 = by size: (128, 64, 64) on meshes of fewer than 524,288
+                          points, else as 0; set by bfm_autotune */
     int near_corr;     /* != 0: add near-field correction matrices to every product, the
                           singular diagonals and b (Section 3.9): for each collocation point
                           i the triangles touching i or its mesh neighbours are integrated
@@ -319,7 +319,8 @@ int bfm_direct_dev_noalloc(int64_t n, const double *xyz, const double *s, const 
  * products of a typical solve (ten FP64 products, or two FP64 and eight
  * low-precision ones), and the M2L launch shape (dense shapes 0..2 and the
  * rotation-factored 3) with the fastest product at that depth, and the
- * near-field work item shape (p2p_shape 0..2) with the fastest near field
+ * near-field work item shape (when p2p_shape is -1: 0..2, or -1 where the rule
+ * by size has items of its own) with the fastest near field
  * of the products GMRES runs most (the low-precision ones under
  * refinement), timed with HIP events after a warm-up. The choice is stored
  * in the handle's options (p, p_lo, p_diag, lmax, m2l_shape, p2p_shape).

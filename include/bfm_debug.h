@@ -10,6 +10,8 @@
 #ifndef BFM_DEBUG_H
 #define BFM_DEBUG_H
 
+#include <stdint.h>
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -63,6 +65,13 @@ int bfm_debug_spd_inverse(int device, int n, const double *A, double *Ainv);
  * not 0..5, iters not in [1, 2^16]) / BFM_EDEVICE.
  */
 int bfm_debug_probe(int device, int kind, int iters, double *ms, double *ops);
+
+/*
+ * Work items of the symmetric near field on a mesh of `points` points with the
+ * option p2p_shape: out receives receivers per chunk, sources per piece of the
+ * chunk's own block and per piece of the rest. Returns BFM_OK or BFM_EINVAL.
+ */
+int bfm_debug_near_shape(int64_t points, int p2p_shape, int *out);
 
 #ifdef __cplusplus
 }

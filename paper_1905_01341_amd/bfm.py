@@ -174,6 +174,7 @@ def load(path: str = LIB_PATH):
         "bfm_debug_dgemm": ([I, I, I, I, P, P, P], I),
         "bfm_debug_spd_inverse": ([I, I, P, P], I),
         "bfm_debug_probe": ([I, I, I, P, P], I),
+        "bfm_debug_near_shape": ([ctypes.c_int64, I, P], I),
         "bfm_profile": ([P, I], I),
         "bfm_profile_read": ([P, I, P, P, P], I),
         "bfm_autotune": ([P, D, ctypes.POINTER(TuneResult)], I),
@@ -266,6 +267,13 @@ def debug_probe(kind: int, iters: int, device: int = 0):
     ms, ops = ctypes.c_double(), ctypes.c_double()
     _check(load().bfm_debug_probe(device, kind, iters, ctypes.byref(ms), ctypes.byref(ops)))
     return ms.value, ops.value
+
+
+def debug_near_shape(points: int, p2p_shape: int):
+    """(chunk, own piece, piece) of the symmetric near field (include/bfm_debug.h)."""
+    out = np.zeros(3, dtype=np.int32)
+    _check(load().bfm_debug_near_shape(int(points), int(p2p_shape), _ptr(out)))
+    return tuple(int(v) for v in out)
 
 
 def debug_dgemm(A, B, device=0):

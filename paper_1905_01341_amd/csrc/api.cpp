@@ -844,6 +844,17 @@ int bfm_debug_probe(int device, int kind, int iters, double *ms, double *ops) {
     });
 }
 
+int bfm_debug_near_shape(int64_t points, int p2p_shape, int *out) {
+    return guarded([&] {
+        BFM_CHECK(out && points >= 1 && p2p_shape >= -1 && p2p_shape < kSymShapeCount, BFM_EINVAL,
+                  "near-field shape query");
+        const SymShape s = sym_shape_of(points, p2p_shape);
+        out[0] = s.chunk;
+        out[1] = s.dpiece;
+        out[2] = s.piece;
+    });
+}
+
 // ---------------------------------------------------------------------------
 // Time-step harness (include/bfm_step.h)
 

@@ -34,13 +34,18 @@ constexpr int kSymShapeCount = 3;
 constexpr SymShape kSymShapes[kSymShapeCount] = {{256, 128, 192}, {128, 128, 128}, {256, 128, 384}};
 // Meshes of fewer than kSymSmall points have too few pairs for such items to fill
 // the device (100 bubbles, 41.6 M pairs: 2587 waves on 1024 SIMDs) and take the
-// smallest, one tile of 64 sources, whatever the shape. Near field alone, FP64 /
-// FP32: 7704 points 23 / 22 us with (128, 128, 128), 15 / 14 so; 64,200 points 43
-// (60 with shape 0) and 35 us; 642,000 points 256 / 136 and 253 / 132. The solve
-// of 642,000 points takes 9.00 ms with shape 1, 9.02 so, that of 1.28 M 17.6
-// (shape 0) and 17.8; of 160,500 points 3.64 and 3.60.
+// smallest, one tile of 64 sources, unless the caller asks for a shape. Near field
+// alone, FP64 / FP32: 7704 points 23 / 22 us with (128, 128, 128), 15 / 14 so;
+// 64,200 points 43 (60 with shape 0) and 35 us; 642,000 points 256 / 136 with
+// shape 0 and 253 / 132. The solve of 160,500 points takes 3.64 ms with shape 1 and
+// 3.60 so, that of 642,000 9.00 and 9.02: about there the choice stops mattering;
+// that of 1.28 M 17.6 with shape 0 and 17.8.
 constexpr SymShape kSymShapeSmall = {128, 64, 64};
 constexpr int64_t kSymSmall = (int64_t)1 << 19;
+// Shape of a mesh of n points: the option's (0..2), or by size (-1).
+constexpr SymShape sym_shape_of(int64_t n, int option) {
+    return option >= 0 ? kSymShapes[option] : (n < kSymSmall ? kSymShapeSmall : kSymShapes[0]);
+}
 
 // Translation tasks grouped by operator: tasks op_off[o]..op_off[o+1] use
 // operator o; task t moves expansion src[t] into expansion dst[t] (global
@@ -118,7 +123,7 @@ struct Tree {
     // clipped to start at r0 (the chunk itself first), in leaf order
     DevBuf<int4> sym_items;
     int64_t n_sym_items = 0;
-    int sym_shape = 0, sym_chunk = kSymChunk;  // shape the items were built with
+    int sym_chunk = kSymChunk;  // receivers per chunk the items were built with
 
     // sorted point data (per tree): positions, weights, normals
     DevBuf<double> px, py, pz;  // [n]
@@ -146,7 +151,7 @@ struct Tree {
 
 // Build (or rebuild) the tree for the points xyz (device, [n][3] AoS).
 // lmax_req > 0 fixes the depth; otherwise the deepest level whose mean leaf
-// occupancy is >= leaf_target is used (at least 2).
+// occupancy is >= leaf_target is used (at least 2). sym_shape: -1 or 0..2 (sym_shape_of).
 void build_tree(Tree &t, const double *xyz, int64_t n, int lmax_req, int leaf_target, int sym_shape,
                 hipStream_t st);
 

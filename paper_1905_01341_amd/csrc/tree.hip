@@ -929,16 +929,17 @@ static HostSizes *host_sizes(Tree::Scratch &scr) {
 void build_tree(Tree &t, const double *xyz, int64_t n, int lmax_req, int leaf_target, int sym_shape,
                 hipStream_t st) {
     BFM_CHECK(n >= 1, BFM_EINVAL, "tree of no points");
-    BFM_CHECK(sym_shape >= 0 && sym_shape < kSymShapeCount, BFM_EINVAL, "near-field item shape out of range");
+    BFM_CHECK(sym_shape >= -1 && sym_shape < kSymShapeCount, BFM_EINVAL, "near-field item shape out of range");
     t.valid = false;
     t.n = n;
-    const SymShape sh = n < kSymSmall ? kSymShapeSmall : kSymShapes[sym_shape];
-    static_assert(kSymShapes[0].dpiece % 64 == 0 && kSymShapes[1].dpiece % 64 == 0 && kSymShapes[2].dpiece % 64 == 0,
+    const SymShape sh = sym_shape_of(n, sym_shape);
+    static_assert(kSymShapes[0].dpiece % 64 == 0 && kSymShapes[1].dpiece % 64 == 0 && kSymShapes[2].dpiece % 64 == 0 &&
+                      kSymShapeSmall.dpiece % 64 == 0,
                   "pieces of a chunk's own block start at receiver-group bounds");
     static_assert(kSymShapes[0].chunk <= kSymChunk && kSymShapes[1].chunk <= kSymChunk &&
-                      kSymShapes[2].chunk <= kSymChunk && kSymShapes[1].chunk % 64 == 0,
+                      kSymShapes[2].chunk <= kSymChunk && kSymShapeSmall.chunk <= kSymChunk &&
+                      kSymShapes[1].chunk % 64 == 0 && kSymShapeSmall.chunk % 64 == 0,
                   "at most four receivers per lane");
-    t.sym_shape = sym_shape;
     t.sym_chunk = sh.chunk;
     Tree::Scratch &scr = t.scratch;
     HostSizes *hs = host_sizes(scr);

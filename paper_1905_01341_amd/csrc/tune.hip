@@ -314,10 +314,13 @@ void autotune(bfm_ctx *c, double mvp_tol, bfm_tune_result *out) {
         // 3. near-field work item shape: the symmetric near field of the
         // products GMRES runs most (the low-precision ones under refinement),
         // timed alone with the library's kernel timing (which runs the near
-        // field in line) at the chosen depth and M2L shape
+        // field in line) at the chosen depth and M2L shape. On small meshes the
+        // rule by size (-1) has items of its own and is a candidate too; on
+        // larger ones it is shape 0
         int best_ps = saved.p2p_shape;
         if (saved.p2p_shape < 0) {
-            best_ps = 0;
+            const int first = n < kSymSmall ? -1 : 0;
+            best_ps = first;
             if (!c->prof.on) {
                 c->opt.p = best_p;
                 c->opt.lmax = best_l;
@@ -325,7 +328,7 @@ void autotune(bfm_ctx *c, double mvp_tol, bfm_tune_result *out) {
                 const int prec = ir ? saved.precision : BFM_PREC_FP64;
                 const int cls = (ir ? kLoBase : 0) + KC_P2P;
                 double best_near = 1e300;
-                for (int ps = 0; ps < kSymShapeCount; ++ps) {
+                for (int ps = first; ps < kSymShapeCount; ++ps) {
                     c->opt.p2p_shape = ps;
                     c->tree_valid = false;
                     ensure_tree(c);
