@@ -166,7 +166,9 @@ typedef struct bfm_ctx bfm_ctx;
 int bfm_default_options(bfm_options *opt);
 
 /* Create a handle on opt->device. The handle owns every device buffer
- * (mesh, octree, expansions, translation operators, Krylov basis). */
+ * (mesh, octree, expansions, translation operators, Krylov basis, at most
+ * 1 GiB of per-translation results of the FP64 products) and keeps it, grown to
+ * the largest call, until bfm_destroy. */
 int bfm_create(const bfm_options *opt, bfm_ctx **out);
 int bfm_destroy(bfm_ctx *ctx);
 

@@ -73,6 +73,15 @@ int bfm_debug_probe(int device, int kind, int iters, double *ms, double *ops);
  */
 int bfm_debug_near_shape(int64_t points, int p2p_shape, int *out);
 
+/*
+ * Batches of an FP64 M2L list whose offset o owns tasks op_off[o] ..
+ * op_off[o + 1] - 1 (nops + 1 entries), with nch channels, tiles of `width`
+ * columns and at most `most` >= width tasks a batch: out receives, per batch, (end
+ * task, offset and tile of that offset where it ends), up to `cap` batches; the
+ * number of batches goes to *count. Returns BFM_OK or BFM_EINVAL.
+ */
+int bfm_debug_m2l_batches(int nops, const int *op_off, int nch, int width, int64_t most, int cap, int *out, int *count);
+
 #ifdef __cplusplus
 }
 #endif

@@ -175,6 +175,7 @@ def load(path: str = LIB_PATH):
         "bfm_debug_spd_inverse": ([I, I, P, P], I),
         "bfm_debug_probe": ([I, I, I, P, P], I),
         "bfm_debug_near_shape": ([ctypes.c_int64, I, P], I),
+        "bfm_debug_m2l_batches": ([I, P, I, I, ctypes.c_int64, I, P, P], I),
         "bfm_profile": ([P, I], I),
         "bfm_profile_read": ([P, I, P, P, P], I),
         "bfm_autotune": ([P, D, ctypes.POINTER(TuneResult)], I),
@@ -274,6 +275,17 @@ def debug_near_shape(points: int, p2p_shape: int):
     out = np.zeros(3, dtype=np.int32)
     _check(load().bfm_debug_near_shape(int(points), int(p2p_shape), _ptr(out)))
     return tuple(int(v) for v in out)
+
+
+def debug_m2l_batches(op_off, nch: int, width: int, most: int):
+    """[(end task, offset, tile)] of an M2L list's batches (include/bfm_debug.h)."""
+    off = np.ascontiguousarray(op_off, dtype=np.int32)
+    cap = int(off[-1] - off[0]) // width + off.size + 1
+    out = np.zeros((cap, 3), dtype=np.int32)
+    count = ctypes.c_int(0)
+    _check(load().bfm_debug_m2l_batches(off.size - 1, _ptr(off), int(nch), int(width), int(most), cap, _ptr(out),
+                                        ctypes.byref(count)))
+    return [tuple(int(v) for v in b) for b in out[:count.value]]
 
 
 def debug_dgemm(A, B, device=0):

@@ -12,6 +12,7 @@
 #include "../../include/bfm_step.h"
 #include "ctx.h"
 #include "direct.h"
+#include "fmm_kernels.h"
 #include "learn.h"
 #include "ops.h"
 
@@ -208,6 +209,8 @@ int bfm_create(const bfm_options *opt, bfm_ctx **out) {
         DeviceScope ds(opt->device);
         auto *c = new bfm_ctx();
         c->fmm.prof = &c->prof;
+        c->fmm.az_part = &c->az_part;
+        c->fmm_diag.az_part = &c->az_part;
         c->fmm_diag.prof = &c->prof;  // the diagonal pass's kernels in their own classes
         c->fmm_diag.prof_base = kDiagBase;
         c->fmm_lo.prof = &c->prof;
@@ -852,6 +855,24 @@ int bfm_debug_near_shape(int64_t points, int p2p_shape, int *out) {
         out[0] = s.chunk;
         out[1] = s.dpiece;
         out[2] = s.piece;
+    });
+}
+
+int bfm_debug_m2l_batches(int nops, const int *op_off, int nch, int width, int64_t most, int cap, int *out,
+                          int *count) {
+    return guarded([&] {
+        BFM_CHECK(op_off && out && count && nops >= 1 && nch >= 1 && width >= 1 && most >= width, BFM_EINVAL,
+                  "M2L batch query");
+        int op = 0, lo = op_off[0], n = 0;
+        do {
+            int h[3];
+            az_batch(op_off, op, nops, nch, width, most, lo, h, h + 1, h + 2);
+            if (n < cap) std::copy(h, h + 3, out + 3 * n);
+            ++n;
+            lo = h[0];
+            op = h[1];
+        } while (lo < op_off[nops]);
+        *count = n;
     });
 }
 

@@ -100,6 +100,7 @@ struct bfm_ctx {
     bfm::FmmWork fmm;       // FP64 products inside GMRES (order p)
     bfm::FmmWork fmm_diag;  // diagonal + right-hand-side pass (order p_diag)
     bfm::FmmWork fmm_lo;    // low-precision products (order p_lo; iterative refinement)
+    bfm::DevBuf<double> az_part;  // per-task M2L results of the FP64 products (all on `stream`)
 
     // sorted-order solve data
     bfm::DevBuf<double> src_q, src_w;  // channel monopole strengths, dipole weights

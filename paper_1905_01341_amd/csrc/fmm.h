@@ -49,7 +49,7 @@ struct FmmWork {
     // each), the operator and the rotation factors of every offset (316, then
     // the 8 octants), packed positions of the factors' entries
     DevBuf<double> az_m2m, az_l2l, az_m2l;
-    DevBuf<double> az_part;  // per-task M2L results of one batch
+    DevBuf<double> *az_part = nullptr;  // per-task M2L results of one batch (the handle's)
     DevBuf<int> az_canon, az_off;
     DevBuf<double2> az_fac;
     size_t az_goff[3] = {0, 0, 0};

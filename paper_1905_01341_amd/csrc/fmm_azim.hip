@@ -593,41 +593,73 @@ static int az_shape(const TaskList &tl, int nch, int nslab) {
     return ((cols + 63) / 64) * nslab >= 512 ? 1 : 2;
 }
 
+// Tiles g0 .. g1 - 1 of the list; task0: the task whose results start `out` (M2L).
 template <int P, int LDP, int KIND>
-static void az_one(const AzLaunch &a, int shape, int op0, int nops, const double *T, const TaskList &tl,
+static void az_one(const AzLaunch &a, int shape, int g0, int g1, int task0, const double *T, const TaskList &tl,
                    double *out) {
     const int width = shape == 0 ? 128 : (shape == 1 ? 64 : 16);
-    const int g0 = az_tiles_before(tl, a.nch, width, op0), g1 = az_tiles_before(tl, a.nch, width, op0 + nops);
     const int base = KIND ? kNumM2LOps : 0;
     launch_az<P, LDP, KIND>(shape, tl.tiles_for(a.nch, width) + g0, g1 - g0, tl, a.swap, a.nch,
                             a.w->az_canon.get() + base, T, a.w->az_fac.get() + (int64_t)base * kAzTab,
-                            a.w->az_off.get(), tl.op_off_h[op0], a.in, out, a.st);
+                            a.w->az_off.get(), task0, a.in, out, a.st);
 }
 
-// Doubles of per-task M2L results held at once (4 GiB): longer lists run in
-// batches of offsets, each summed into the targets before the next.
-constexpr size_t kAzPart = (size_t)1 << 29;
+// The batch of an M2L list that starts at task lo, a cut of offset op or its first
+// task (op_off: first task of each offset, op_off[op1]: the end): the most
+// tasks up to `most` that end at the end or at a cut. Cuts lie every `width` tasks
+// of an offset, where one of its tiles of `width` columns (nch a task) ends.
+// most >= width, so a batch is never empty. hop, htile: offset and tile of the
+// end (tile 0: the offset's first).
+void az_batch(const int *op_off, int op, int op1, int nch, int width, int64_t most, int lo, int *hi, int *hop,
+              int *htile) {
+    const int64_t want = lo + most;
+    if (want >= op_off[op1]) {
+        *hi = op_off[op1];
+        *hop = op1;
+        *htile = 0;
+        return;
+    }
+    while (op_off[op + 1] <= want) ++op;
+    const int cut = (int)((want - op_off[op]) / width);
+    *hi = op_off[op] + cut * width;
+    *hop = op;
+    *htile = cut * nch;
+}
+
+// Doubles of per-task M2L results held at once (1 GiB, one workspace of the handle
+// for both FP64 product groups, which run on one stream): longer lists run in
+// batches, each summed into the targets before the next, which costs about 60 us a
+// batch on 3.2 M points (reads and writes of the targets, short last waves). A solve
+// of that size with up to 4 GiB / 1 GiB / 512 / 256 / 128 / 64 MiB: 44.8 / 45.8 /
+// 47.1 / 49.7 / 53.0 / 58.1 ms; 642,000 points 9.03 / 9.03 / 9.05 / 9.14 / 9.31 /
+// 9.69.
+constexpr int64_t kAzPart = (int64_t)1024 << 17;
 
 // M2L of offsets op0 .. op1 - 1 at order P, added to (first: written over)
 // the target expansions.
 template <int P, int LDP>
 static void az_m2l(const AzLaunch &a, int shape, int op0, int op1, const double *T, TaskList &tl, bool first) {
-    const size_t row = (size_t)a.nch * P * P;
-    for (int b0 = op0; b0 < op1;) {
-        int b1 = b0 + 1;
-        while (b1 < op1 && (size_t)(tl.op_off_h[b1 + 1] - tl.op_off_h[b0]) * row <= kAzPart) ++b1;
-        const int lo = tl.op_off_h[b0], hi = tl.op_off_h[b1];
-        double *part = a.w->az_part.ensure(std::max((size_t)(hi - lo) * row, (size_t)1));
-        az_one<P, LDP, 0>(a, shape, b0, b1 - b0, T, tl, part);
-        const int64_t waves = tl.dst_nbox * (int64_t)((row + 127) / 128);
+    const int width = shape == 0 ? 128 : (shape == 1 ? 64 : 16);
+    const int64_t row = (int64_t)a.nch * P * P, most = std::max<int64_t>(kAzPart / row, width);
+    const int *off = tl.op_off_h.data();
+    const int64_t waves = tl.dst_nbox * ((row + 127) / 128);
+    int op = op0, lo = off[op0], g0 = az_tiles_before(tl, a.nch, width, op0);
+    do {  // (a list without tasks writes its targets all the same)
+        int hi, hop, htile;
+        az_batch(off, op, op1, a.nch, width, most, lo, &hi, &hop, &htile);
+        const int g1 = az_tiles_before(tl, a.nch, width, hop) + htile;
+        double *part = a.w->az_part->ensure((size_t)std::max<int64_t>((hi - lo) * row, 1));
+        az_one<P, LDP, 0>(a, shape, g0, g1, lo, T, tl, part);
         auto kern = first ? k_az_reduce<P, true> : k_az_reduce<P, false>;
         kern<<<(unsigned)((waves + 3) / 4), 256, 0, a.st>>>(tl.dst_off.get(), tl.pos_of.get(), tl.dst_box0,
                                                             tl.dst_nbox, lo, hi, a.nch, LDP * LDP, part,
                                                             a.w->az_off.get(), a.out);
         BFM_LAUNCHED();
         first = false;
-        b0 = b1;
-    }
+        op = hop;
+        lo = hi;
+        g0 = g1;
+    } while (lo < off[op1]);
 }
 
 template <int P>
@@ -645,10 +677,11 @@ int launch_translate_az(const AzLaunch &a, TaskList &tl, bool m2l, int shape, do
     FmmWork &w = *a.w;
     if (!m2l) {
         *flops = col_flops(P) * (double)tl.ntasks * a.nch;
+        const int nt = tl.ntiles_for(a.nch, width);
         if (a.swap)
-            az_one<P, P, 2>(a, shape, 0, tl.nops, w.az_l2l.get(), tl, a.out);
+            az_one<P, P, 2>(a, shape, 0, nt, 0, w.az_l2l.get(), tl, a.out);
         else
-            az_one<P, P, 1>(a, shape, 0, tl.nops, w.az_m2m.get(), tl, a.out);
+            az_one<P, P, 1>(a, shape, 0, nt, 0, w.az_m2m.get(), tl, a.out);
         return shape;
     }
     constexpr int P1 = m2l_class_order(P, 1), P2 = m2l_class_order(P, 2);

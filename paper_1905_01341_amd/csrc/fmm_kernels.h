@@ -64,6 +64,9 @@ struct AzLaunch {
     hipStream_t st;
 };
 void az_ops_upload(FmmWork &w, int p, hipStream_t st);
+// One batch of an M2L list (fmm_azim.hip).
+void az_batch(const int *op_off, int op, int op1, int nch, int width, int64_t most, int lo, int *hi, int *hop,
+              int *htile);
 template <int P>
 int launch_translate_az(const AzLaunch &a, TaskList &tl, bool m2l, int shape, double *flops);
 
