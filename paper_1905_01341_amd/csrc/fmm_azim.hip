@@ -332,6 +332,9 @@ __global__ void __launch_bounds__(256) k_az_reduce(const int *__restrict__ dst_o
         if (ok) list[wave][n + __popcll(m & ((1ull << lane) - 1))] = p - lo;
         n += __popcll(m);
     }
+    // lanes read positions that other lanes of the wave wrote
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     if (!FIRST && n == 0) return;
     const int e0 = (int)(w % nchunk) * 128 + 2 * lane;
     if (e0 >= row) return;
