@@ -19,6 +19,7 @@
 namespace bfm {
 
 constexpr int kDirThreads = 64;
+constexpr int64_t kDirGroups = 1024;  // workgroups that fill the device
 constexpr double kInv4PiD = 0.079577471545947667884441881686257;
 
 // Scratch of the allocation-free entry point (kDirectScratch doubles,
@@ -154,16 +155,26 @@ __global__ void __launch_bounds__(256) k_direct_sum(const double *__restrict__ p
     out[k] = kInv4PiD * v;
 }
 
-// Receivers per lane: enough to share each source read, without idle lanes
-// on short row lists.
-int direct_recv(int64_t nr) { return nr <= kDirThreads ? 1 : (nr <= 2 * kDirThreads ? 2 : 4); }
+// Receivers per lane: enough to share each source read, without idle lanes on
+// short row lists, and fewer where the workgroups would not fill the device even
+// with one tile of sources each: the call is then one chain of pair steps a wave,
+// four times as long with four receivers (both layers, four and one, a call: 500
+// points x 500 rows 51.6 and 35.3 us, of which the call's host side is 34; 2500 x
+// 2500 52.4 and 44.5; 5000 x 5000 57.5 and 53.4; with one receiver and scalar source
+// loads they took 42, 49 and 83).
+int direct_recv(int64_t n, int64_t nr) {
+    int r = nr <= kDirThreads ? 1 : (nr <= 2 * kDirThreads ? 2 : 4);
+    const int64_t splits = std::max<int64_t>(1, n / (4 * kDirThreads));
+    while (r > 1 && (nr + r * kDirThreads - 1) / (r * kDirThreads) * splits < kDirGroups) r /= 2;
+    return r;
+}
 
-// Source splits: about 1024 workgroups (four waves each), at least one tile
+// Source splits: about kDirGroups workgroups (four waves each), at least one tile
 // of sources a split, the partials within the fixed scratch array.
 int direct_splits(int64_t n, int64_t nr) {
-    const int64_t per = (int64_t)direct_recv(nr) * kDirThreads;
+    const int64_t per = (int64_t)direct_recv(n, nr) * kDirThreads;
     const int64_t blocks = (nr + per - 1) / per;
-    int64_t sp = (1024 + blocks - 1) / blocks;
+    int64_t sp = (kDirGroups + blocks - 1) / blocks;
     sp = std::min<int64_t>(sp, n / (4 * kDirThreads));
     sp = std::min<int64_t>(sp, kDirectScratch / nr);
     return (int)std::max<int64_t>(sp, 1);
@@ -180,7 +191,7 @@ void direct_check(const DirectArgs &a) {
 
 template <bool MONO, bool DIP>
 static void direct_part(const DirectArgs &a, double *part, int nsplit, hipStream_t st) {
-    const int r = direct_recv(a.nr);
+    const int r = direct_recv(a.n, a.nr);
     const int64_t per = (int64_t)r * kDirThreads;
     const dim3 grid((unsigned)((a.nr + per - 1) / per), (unsigned)nsplit);
     auto kern = r == 1 ? k_direct_part<MONO, DIP, 1> : (r == 2 ? k_direct_part<MONO, DIP, 2> : k_direct_part<MONO, DIP, 4>);
