@@ -3,9 +3,10 @@
  *
  * The fast multipole translations of the paper's FMM (Section 3.9:
  * multipole and local expansions of degrees 0..p_fmm-1, translated between
- * boxes of the octree) are stored by libbfm as dense real p^2 x p^2
- * matrices in a normalised, box-scaled basis. This call exposes one of them
- * so that tests can check it against independent expansions on the CPU.
+ * boxes of the octree) are built by libbfm as dense real p^2 x p^2
+ * matrices in a normalised, box-scaled basis, from which the forms that its
+ * kernels read are derived. This call exposes one of them so that tests can
+ * check it against independent expansions on the CPU.
  */
 #ifndef BFM_DEBUG_H
 #define BFM_DEBUG_H
@@ -44,8 +45,9 @@ int bfm_debug_operator(int p, int kind, int index, double *out, int *d_out);
  * bfm_debug_dgemm: C = A B with the library's FP64 MFMA GEMM; A [M x K],
  * B [K x N], C [M x N], all column-major host arrays.
  * bfm_debug_spd_inverse: the library's in-place inverse (a blocked symmetric sweep
- * without pivoting; the lower triangle is read) of a symmetric positive definite n x n column-major matrix,
- * as used for the coarse correction of BFM_PRECOND_SH_COARSE.
+ * without pivoting; the lower triangle is read) of a symmetric positive definite
+ * n x n column-major matrix, as used for the coarse correction of
+ * BFM_PRECOND_SH_COARSE.
  * Return BFM_OK or a BFM_E* code (message in bfm_last_error()).
  */
 int bfm_debug_dgemm(int device, int M, int N, int K, const double *A, const double *B, double *C);

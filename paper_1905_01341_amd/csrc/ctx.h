@@ -129,7 +129,7 @@ struct bfm_ctx {
     bfm::DevBuf<double> gin, gout;
 
     // GMRES workspace (sorted order)
-    bfm::DevBuf<double> V, work, x_s, part, small, zbuf, tbuf;
+    bfm::DevBuf<double> V, x_s, part, small, zbuf, tbuf;
     double *host_small = nullptr;       // pinned
     // device copies of a call's host vectors, kept: allocating and freeing them
     // cost a product of 256,200 vertices 85 of its 720 us

@@ -53,7 +53,7 @@ struct Mma<float> {
 // input coefficients and shared by all waves; each wave multiplies it by its
 // 16 gathered expansion columns. The operands are passed transposed
 // (D = in^T T^T), so lane l, element r of a result block holds column
-// l/16 + 4r and row l%16: each quarter-wave adds 16 contiguous coefficients
+// 4 (l/16) + r and row l%16: each quarter-wave adds 16 contiguous coefficients
 // of one target expansion. Wide tiles (many waves, all rows) cut operator
 // re-reads when groups are large; row slabs give parallelism when groups are
 // small (coarse octree levels). KIND only separates the kernel symbols of
@@ -203,10 +203,10 @@ __global__ void __launch_bounds__(64 * WAVES) k_translate(int op0, int nops, con
 constexpr int kBfWaves = 4, kBfCb = 2, kBfTile = kBfWaves * kBfCb * 16;  // 128 columns
 constexpr int kBfRs = 5;  // LDS row stride in 16-byte units (4 used, 1 pad: conflict-free reads)
 
-__device__ inline void split8(const float *v, bool ok, bf16x8 &hi, bf16x8 &lo) {
+__device__ inline void split8(const float *v, bf16x8 &hi, bf16x8 &lo) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const float a = ok ? v[e] : 0.f;
+        const float a = v[e];
         const __bf16 h = (__bf16)a;
         hi[e] = h;
         lo[e] = (__bf16)(a - (float)h);
@@ -327,7 +327,7 @@ __global__ void __launch_bounds__(64 * kBfWaves) k_translate_bf3(const int4 *__r
         const int buf = c & 1;
         bf16x8 ah[kBfCb], al[kBfCb];
 #pragma unroll
-        for (int cb = 0; cb < kBfCb; ++cb) split8(av[cb], true, ah[cb], al[cb]);
+        for (int cb = 0; cb < kBfCb; ++cb) split8(av[cb], ah[cb], al[cb]);
         if (c + 1 < NC) {  // next chunk's loads overlap this chunk's products
             fetch_op(c + 1);
             fetch_in(c + 1);

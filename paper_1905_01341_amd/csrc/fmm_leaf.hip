@@ -120,7 +120,9 @@ __device__ inline R swap_add(R a, R b) {
 // time, and four lanes add up each in a fixed order over groups of 128 points
 // that does not depend on how the work is split: the order of an FP32 sum
 // decides the bits that the split-BF16 translations round next, and a solve's
-// answer at its tolerance moves with them.
+// answer at its tolerance moves with them. The groups of a leaf are added
+// atomically: leaves of up to 256 points (two groups) come out the same on every
+// run, larger ones up to the order in which their groups arrive.
 constexpr int kP2MRows = 16;
 template <class R>
 constexpr int kP2MBuf = sizeof(R) == 4 ? 16 * 68 : kP2MRows * 64;  // values a wave; rows of 68: distinct banks

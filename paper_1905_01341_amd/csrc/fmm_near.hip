@@ -26,11 +26,8 @@ __device__ inline double rsqrt_m2_f64(double x) {
 constexpr int kP2PThreads = 64;
 constexpr int kXcdCount = 8;  // accelerator complex dies of an MI355X
 
-// Receivers xi..zi (R per lane) against sources [j0, j1): every lane reads
-// the same source at the same time, so the loads are wave-uniform (scalar
-// loads of read-only data) and no LDS staging is needed.
-// SELF: the sources may include the receiver itself (r = 0, excluded);
-// otherwise every pair is at a positive distance and needs no test.
+// One source against the all-pairs sum's receivers xi..zi (R per lane).
+// SELF: the source may be the receiver itself (r = 0, excluded).
 template <int NCH, bool MONO, bool DIP, int R, bool SELF>
 __device__ inline void p2p_pair(double sx, double sy, double sz, const double *sq, const double *sw,
                                 double nx, double ny, double nz, const double *xi, const double *yi,
@@ -788,6 +785,7 @@ void launch_p2p(const Tree &t, const Sources &src, double *y, hipStream_t st) {
         BFM_LAUNCHED();
     }
 }
+
 void launch_p2p_packed(const Tree &t, const double *packed, double *y, hipStream_t st) {
     if (t.n_near_items <= 0) return;
     auto kern = t.near_split ? k_p2p_diag<true> : k_p2p_diag<false>;
@@ -816,8 +814,6 @@ void launch_p2p32(const Tree &t, const Sources &src, double *y, hipStream_t st) 
             t.px.get(), t.py.get(), t.pz.get(), src.q, t.sym_chunk, y);
         BFM_LAUNCHED();
         return;
-    }
-    if (t.near_split) {
     }
     auto kern = t.near_split ? k_p2p32<MONO, DIP, true> : k_p2p32<MONO, DIP, false>;
     kern<<<(unsigned)t.n_near_items, kP2PThreads, 0, st>>>(t.near_items.get(), t.leaf_pt.get(), t.near_rng.get(),

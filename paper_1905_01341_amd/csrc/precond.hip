@@ -1048,9 +1048,9 @@ void coarse_mark(bfm_ctx *c) {
     c->coarse_marked = true;
 }
 
-// The coarse build is about a hundred small launches. Queued by the solving
-// thread they would hold it, and so the octree build that runs beside them on
-// the main stream, for a millisecond or more; a worker thread of the handle
+// The coarse build is 3 ceil(nb / 128) + 6 launches, most of them small (30 at
+// 1000 bubbles). Queued by the solving thread they would hold it, and so the octree
+// build that runs beside them on the main stream; a worker thread of the handle
 // queues them instead. coarse_launch hands the build over and returns;
 // coarse_join waits until the worker has queued the build and its completion
 // event (not for the device), then orders the main stream after that event.
