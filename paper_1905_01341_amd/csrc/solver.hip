@@ -359,13 +359,13 @@ void matvec_sorted(bfm_ctx *c, double f, const double *x_s, double g, const doub
 // sums the pass before it left (every block does, which costs less than a
 // launch) and ends with the partial sums of the next: dots of w; update and
 // dots again (the basis is read once for both); update and norm; rotation
-// and scaling. Up to kSmallGs points one workgroup does the whole step.
+// and scaling. On small meshes one workgroup does the whole step (gs_in_one).
 // Measured: see gs_step.
 
 constexpr int kRedBlocks = 512;
 constexpr int kRedThreads = 256;
 constexpr int kGsFuse = 32;          // basis vectors a fused pass holds in registers
-constexpr int64_t kSmallGs = 4096;   // points up to which one workgroup runs the step
+constexpr int64_t kSmallGs = 4096;   // points one workgroup holds
 constexpr int kMaxRestart = 128;
 
 // two points a thread at least: every block adds up all blocks' partials
@@ -695,8 +695,18 @@ __global__ void __launch_bounds__(kMaxRestart) k_trisolve(double *sm, SmallLayou
     }
 }
 
+// Whether one workgroup takes the step (four launches else). Its time grows with
+// the basis it reads, about 7 + 0.0007 n nvec us, that of the four launches is about
+// 14.4 + 0.52 nvec whatever n <= kSmallGs: they meet at (n - 743) nvec = 10571.
+// Means over a cycle of 30 / of 10, one and four launches: 642 points 14.2 and 20.4
+// / 9.9 and 16.7 us, 1284 points 21.7 and 22.7 / 12.4 and 17.0, 2562 points 32.0
+// and 22.7 / 17.5 and 17.4, 3852 points 44.9 and 22.8 / 22.9 and 17.7.
+static bool gs_in_one(int64_t n, int nvec) {
+    return n <= kSmallGs && nvec <= kGsFuse && (n - 743) * nvec <= 10571;
+}
+
 // Orthogonalisation of Arnoldi step j: w = V[j + 1] against V[0..j]: one launch
-// up to kSmallGs points and kGsFuse vectors (642 points 45 -> 16 us a step,
+// where gs_in_one (642 points 45 -> 16 us a step,
 // mean over a cycle of 30), else four (64,200 points 46 -> 30 us, 76,800 points
 // 46 -> 27 us), or six past kGsFuse vectors.
 static void gs_step(bfm_ctx *c, double *V, int j, int64_t n, double *part, double *sm, const SmallLayout &L,
@@ -704,7 +714,7 @@ static void gs_step(bfm_ctx *c, double *V, int j, int64_t n, double *part, doubl
     hipStream_t st = c->stream;
     double *w = V + (int64_t)(j + 1) * n;
     const int nvec = j + 1;
-    if (n <= kSmallGs && nvec <= kGsFuse) {
+    if (gs_in_one(n, nvec)) {
         auto kern = nvec <= 4 ? k_gs_small<4> : (nvec <= 8 ? k_gs_small<8> : (nvec <= 16 ? k_gs_small<16> : k_gs_small<32>));
         kern<<<1, kSmallThreads, 0, st>>>(V, n, w, (int)n, sm, L, j, res);
         BFM_LAUNCHED();
