@@ -22,13 +22,14 @@
 // is shared by the waves (a single wave reads it straight into registers).
 // The results are rotated back in registers and added to the targets.
 //
-// The M2L is bound by the FP64 matrix units on large lists (69% busy at order
-// 20, five channels, at the 2.03 GHz the device keeps under them) and by the
-// latency of its chunk loop on small ones. Measured alone, against the dense
-// p^2 x p^2 kernel with atomic adds: 186,300 tasks, order 20, five channels,
-// reduced distant orders 2.22 -> 1.84 ms; the same tasks, order 16, one
-// channel 381 -> 278 us; 59,112 tasks, order 16 195 -> 134 us; 2504 tasks,
-// order 16 53 -> 31 us.
+// The M2L's products are bound by the FP64 matrix units on large lists (busy 66%
+// of the cycles at order 20, five channels, 62% at order 16, one channel) and by the
+// latency of the chunk loop on small ones; the stored results, written and read
+// once, add a third to the time of the five-channel list. Measured alone, against
+// the dense p^2 x p^2 kernel with atomic adds: 186,300 tasks, order 20, five
+// channels, reduced distant orders 2.22 -> 1.84 ms; the same tasks, order 16, one
+// channel 381 -> 278 us; 59,112 tasks, order 16 195 -> 134 us; 2504 tasks, order 16
+// 53 -> 31 us.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -631,11 +632,11 @@ void az_batch(const int *op_off, int op, int op1, int nch, int width, int64_t mo
 
 // Doubles of per-task M2L results held at once (1 GiB, one workspace of the handle
 // for both FP64 product groups, which run on one stream): longer lists run in
-// batches, each summed into the targets before the next, which costs about 60 us a
-// batch on 3.2 M points (reads and writes of the targets, short last waves). A solve
-// of that size with up to 4 GiB / 1 GiB / 512 / 256 / 128 / 64 MiB: 44.8 / 45.8 /
-// 47.1 / 49.7 / 53.0 / 58.1 ms; 642,000 points 9.03 / 9.03 / 9.05 / 9.14 / 9.31 /
-// 9.69.
+// batches, each summed into the targets before the next, which costs about 0.1 ms a
+// batch on 3.2 M points (the targets read and written once more, short last waves;
+// 11 batches in the diagonal pass). A solve of that size with up to 4 GiB / 1 GiB /
+// 512 / 256 / 128 / 64 MiB: 44.8 / 45.8 / 47.1 / 49.7 / 53.0 / 58.1 ms; 642,000
+// points 9.03 / 9.03 / 9.05 / 9.14 / 9.31 / 9.69.
 constexpr int64_t kAzPart = (int64_t)1024 << 17;
 
 // M2L of offsets op0 .. op1 - 1 at order P, added to (first: written over)
