@@ -50,7 +50,7 @@ def parse():
     ap.add_argument("--p-lo", type=int, default=None, help="order of the low-precision products (autotuned if unset)")
     ap.add_argument("--leaf", type=int, default=None)
     ap.add_argument("--lmax", type=int, default=None)
-    ap.add_argument("--m2l-shape", type=int, default=None, help="M2L launch shape 0..2 (dense), 3 (rotation-factored); -1: by size")
+    ap.add_argument("--m2l-shape", type=int, default=None, help="M2L launch shape 0..2, 3 (rotation-factored); -1: by size")
     ap.add_argument("--tol", type=float, default=None, help="GMRES tolerance of the tuned form")
     ap.add_argument("--plain-tol", type=float, default=None,
                     help="GMRES tolerance of the plain form (unpreconditioned GMRES needs 1e-8 to bring "

@@ -319,7 +319,7 @@ int bfm_direct_dev_noalloc(int64_t n, const double *xyz, const double *s, const 
  * the octree depth (the depth chosen from leaf_target and two levels
  * either side) that minimises one diagonal/right-hand-side pass plus the
  * products of a typical solve (ten FP64 products, or two FP64 and eight
- * low-precision ones), and the M2L launch shape (dense shapes 0..2 and the
+ * low-precision ones), and the M2L launch shape (0..2 and the
  * rotation-factored 3) with the fastest product at that depth, and the
  * near-field work item shape (when p2p_shape is -1: 0..2, or -1 where the rule
  * by size has items of its own) with the fastest near field

@@ -13,7 +13,8 @@
 // a lane share each LDS read of a constant or coefficient and each reduction of
 // the P2M. Against one wave per 128 points, alone: 642 points, order 16, P2M 27
 // -> 11 us, L2P 22 -> 9 us; 642,000 points, five channels, order 20, P2M 547 ->
-// 409 us, L2P 377 -> 185 us (VALU 63% busy in the P2M, 58% in the L2P).
+// 409 us, L2P 377 -> 185 us (VALU instructions alone are 59% of the P2M's time and
+// 56% of the L2P's).
 #include <cmath>
 #include <type_traits>
 #include <vector>
